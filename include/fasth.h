@@ -49,7 +49,10 @@ enum {
 
 /* Problem shape. Supported range: 1 <= d <= 16384, 1 <= n, 1 <= m <= 65535,
  * 1 <= k <= 128 and k divides n (the paper assumes the block size divides
- * the number of reflections, Section 3.1). n need not equal d. */
+ * the number of reflections, Section 3.1). n need not equal d. The result does
+ * not depend on k beyond rounding (Eq. 2 holds for any grouping of consecutive
+ * reflections), and for d <= 4096 the library regroups them into the blocks of
+ * 32, 64 or 128 its kernels are written for, padding the last one. */
 typedef struct fasth_shape {
   int d;          /* length of each Householder vector = rows of X */
   int n;          /* number of reflections = rows of V */
@@ -92,8 +95,9 @@ int fasth_set_wait_limit(int polls);
  * (block factors T_i, partial Gram matrices, the saved block inputs A_{i+1}
  * of Algorithm 1's Remark, the saved gradients dL/dA_i of Algorithm 2 Step 1,
  * the small per-block coefficient vectors and, for a small V against a wide
- * mini-batch, partial sums of dV). Returns 0 if the shape is invalid or
- * unsupported. */
+ * mini-batch, partial sums of dV; where d is no multiple of 4 or n no multiple
+ * of the library's blocks, a padded copy of V). Returns 0 if the shape is
+ * invalid or unsupported. */
 size_t fasth_workspace_bytes(const fasth_shape* shape);
 
 /* Algorithm 1. A = H X (or H^T X). Step 1 builds, for every block i, the

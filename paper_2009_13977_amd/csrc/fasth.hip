@@ -57,6 +57,9 @@ struct Product {  // one Householder product bound to its slice of a workspace
   int d, n, m, k;
   Layout L;
   char* ws;
+  // the rows the kernels read: the caller's, or the padded copy the factor kernels leave in the workspace
+  const float* rows(const float* V) const { return L.copy_v ? reinterpret_cast<const float*>(ws + L.off_V) : V; }
+  float* copy() const { return L.copy_v ? reinterpret_cast<float*>(ws + L.off_V) : nullptr; }
   float* T() const { return reinterpret_cast<float*>(ws + L.off_T); }
   float* Spart() const { return reinterpret_cast<float*>(ws + L.off_Spart); }
   unsigned* xch() const { return L.xch_words ? reinterpret_cast<unsigned*>(ws + L.off_xch) : nullptr; }
@@ -95,6 +98,7 @@ static int launch_factor_fused(const FactorPair& fp, int count, int kp, bool vec
 
 static void set_factor_slot(FactorPair& fp, int slot, const Product& P, const float* V) {
   fp.V[slot] = V; fp.T[slot] = P.T(); fp.d[slot] = P.d; fp.k[slot] = P.L.kf; fp.nb[slot] = P.L.nbf;
+  fp.n[slot] = P.n; fp.dp[slot] = P.L.dp; fp.copy[slot] = P.copy();
   fp.xch[slot] = P.xch(); fp.xch_words[slot] = (unsigned)P.L.xch_words;
 }
 
@@ -106,7 +110,8 @@ static TeamFactorArgs team_factor_args(const Product& P, const float* V) {
   a.ready = reinterpret_cast<unsigned long long*>(P.ws + P.L.off_ready);
   a.launch_id = g_launch_id.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
   if (a.launch_id == 0) a.launch_id = 1;
-  a.d = P.d; a.k = P.L.kf; a.kp = P.L.kpf; a.split = P.L.gram_split; a.wait_limit = wait_limit();
+  a.d = P.d; a.n = P.n; a.dp = P.L.dp; a.copy = P.copy();
+  a.k = P.L.kf; a.kp = P.L.kpf; a.split = P.L.gram_split; a.wait_limit = wait_limit();
   a.xch = P.xch(); a.xch_words = (unsigned)P.L.xch_words;
   a.S = reinterpret_cast<float*>(P.ws + P.L.off_S); a.nblocks = P.L.nbf; a.npair = P.L.npair;
   return a;
@@ -184,7 +189,7 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   // was cleared when they were built), if not P's own
   const Product& F = factors ? *factors : P;
   ChainArgs a;
-  a.V = V; a.T = F.T(); a.in = in; a.out = out;
+  a.V = F.rows(V); a.T = F.T(); a.in = in; a.out = out;
   a.xch = F.xch(); a.wait_limit = wait_limit(); a.parts = 0;
   a.S = reinterpret_cast<const float*>(F.ws + F.L.off_S);
   a.Tt = a.T + (size_t)F.L.nbf * F.L.kpf * F.L.kpf;
@@ -192,31 +197,35 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   a.save_c = !save ? nullptr : activation ? P.saveCa() : P.saveCg();
   a.in_scale = in_scale; a.in_scale_mode = in_scale_mode;
   a.in_rows = in_rows < 0 ? P.d : in_rows;
-  a.d = P.d; a.n = P.n; a.m = P.m; a.k = P.k; a.kp = P.L.kp; a.nb = P.L.nb;
+  a.out_rows = P.d;
+  a.d = P.L.dp; a.n = P.L.np; a.m = P.m; a.k = P.L.ki; a.kp = P.L.kp; a.nb = P.L.nb;
   a.transpose = transpose;
   a.sub = 1;
   a.ds_z1 = ds_z1; a.ds_out = ds_out; a.ds_rows = ds_rows;
   return launch_chain(a, stream);
 }
 
-static DvArgs dv_args(const Product& P, const float* V, float* dV, int transpose, bool accumulate) {
+static DvArgs dv_args(const Product& P, const float* V, float* dV, int transpose, bool accumulate,
+                      const Product* factors = nullptr) {
   DvArgs a;
   a.accumulate = accumulate ? 1 : 0;
-  a.V = V; a.saveA = P.saveA(); a.saveCa = P.saveCa(); a.saveG = P.saveG(); a.saveCg = P.saveCg(); a.dV = dV;
+  a.V = (factors ? *factors : P).rows(V); a.saveA = P.saveA(); a.saveCa = P.saveCa(); a.saveG = P.saveG(); a.saveCg = P.saveCg(); a.dV = dV;
   a.Z = P.Spart();  // the partial Gram matrices are dead once the factors exist; Z needs nb kp^2 of their floats
   a.msplit = P.L.dv_split;
   a.cols_per_part = ((P.m + a.msplit - 1) / a.msplit + kDvMChunk - 1) / kDvMChunk * kDvMChunk;
   a.dVpart = reinterpret_cast<float*>(P.ws + P.L.off_dVpart);
-  a.d = P.d; a.n = P.n; a.m = P.m; a.k = P.k; a.kp = P.L.kp; a.transpose = transpose;
+  a.d = P.L.dp; a.n = P.L.np; a.m = P.m; a.k = P.L.ki; a.kp = P.L.kp; a.transpose = transpose;
+  a.out_d = P.d; a.out_n = P.n;
   return a;
 }
 
 static int launch_dv(const DvPair& pair, int count, int kp, bool vec4, hipStream_t stream) {
   const size_t lds = dv_lds(kp);
-  int xt = (pair.a[0].d + kDvTile - 1) / kDvTile, nb = pair.a[0].n / pair.a[0].k;
+  auto blocks_of = [](const DvArgs& a) { return (a.out_n + a.k - 1) / a.k; };  // blocks of padding only have no gradient
+  int xt = (pair.a[0].d + kDvTile - 1) / kDvTile, nb = blocks_of(pair.a[0]);
   if (count == 2) {
     xt = std::max(xt, (pair.a[1].d + kDvTile - 1) / kDvTile);
-    nb = std::max(nb, pair.a[1].n / pair.a[1].k);
+    nb = std::max(nb, blocks_of(pair.a[1]));
   }
   const DvArgs& a0 = pair.a[0];
   const int msplit = a0.msplit;  // the same for both products of a launch (run_dv_pair checks)
@@ -264,8 +273,8 @@ static int launch_dv(const DvPair& pair, int count, int kp, bool vec4, hipStream
 #undef FASTH_LAUNCH_DV_
   FASTH_HIP(hipGetLastError());
   if (msplit > 1) {
-    size_t nd = (size_t)a0.n * a0.d;
-    if (count == 2) nd = std::max(nd, (size_t)pair.a[1].n * pair.a[1].d);
+    size_t nd = (size_t)a0.out_n * a0.out_d;
+    if (count == 2) nd = std::max(nd, (size_t)pair.a[1].out_n * pair.a[1].out_d);
     hipLaunchKernelGGL(dv_sum_kernel, dim3((unsigned)((nd + 255) / 256), count), dim3(256), 0, stream, pair);
     FASTH_HIP(hipGetLastError());
   }
@@ -273,21 +282,21 @@ static int launch_dv(const DvPair& pair, int count, int kp, bool vec4, hipStream
 }
 
 static int run_dv(const Product& P, const float* V, float* dV, int transpose, hipStream_t stream,
-                  bool accumulate = false) {
+                  bool accumulate = false, const Product* factors = nullptr) {
   DvPair pair;
-  pair.a[0] = pair.a[1] = dv_args(P, V, dV, transpose, accumulate);
-  return launch_dv(pair, 1, P.L.kp, P.d % 4 == 0, stream);
+  pair.a[0] = pair.a[1] = dv_args(P, V, dV, transpose, accumulate, factors);
+  return launch_dv(pair, 1, P.L.kp, P.L.dp % 4 == 0, stream);
 }
 
 // dV of two products with different outputs in one launch when both take the same template
 // arguments; otherwise one after the other.
 static int run_dv_pair(const Product& P0, const float* V0, float* dV0, int transpose0, const Product& P1,
                        const float* V1, float* dV1, int transpose1, hipStream_t stream) {
-  if (P0.L.kp == P1.L.kp && (P0.d % 4 == 0) == (P1.d % 4 == 0) && P0.L.dv_split == P1.L.dv_split) {
+  if (P0.L.kp == P1.L.kp && (P0.L.dp % 4 == 0) == (P1.L.dp % 4 == 0) && P0.L.dv_split == P1.L.dv_split) {
     DvPair pair;
     pair.a[0] = dv_args(P0, V0, dV0, transpose0, false);
     pair.a[1] = dv_args(P1, V1, dV1, transpose1, false);
-    return launch_dv(pair, 2, P0.L.kp, P0.d % 4 == 0, stream);
+    return launch_dv(pair, 2, P0.L.kp, P0.L.dp % 4 == 0, stream);
   }
   const int rc = run_dv(P0, V0, dV0, transpose0, stream);
   return rc != FASTH_OK ? rc : run_dv(P1, V1, dV1, transpose1, stream);
@@ -803,7 +812,7 @@ int svd_sym_apply_backward(const fasth_svd_shape* shape, int function, const flo
   const float* Z1 = reinterpret_cast<const float*>(ws + S.off_Z1);
   float* dZ2 = reinterpret_cast<float*>(ws + S.off_dZ2);
   if ((rc = run_chain(Pout, Uv, G, dZ2, 1, false, nullptr, 0, st, true, &Pin)) != FASTH_OK) return rc;
-  if ((rc = run_dv(Pout, Uv, dUv, 0, st)) != FASTH_OK) return rc;
+  if ((rc = run_dv(Pout, Uv, dUv, 0, st, false, &Pin)) != FASTH_OK) return rc;
   if ((rc = run_chain(Pin, Uv, dZ2, dX, 0, false, sigma, mode, st, true, nullptr, -1, Z1, dsigma, fs.d)) != FASTH_OK)
     return rc;
   return run_dv(Pin, Uv, dUv, 1, st, true);

@@ -41,6 +41,7 @@ struct ChainArgs {
   const float* in_scale;  // [d] or null: input row x is multiplied by diag_factor(in_scale_mode, in_scale[x])
   int in_scale_mode;
   int in_rows;            // rows of `in` that exist; rows in_rows..d-1 of the chain's input are zero
+  int out_rows;           // rows of `out` that exist: the caller's d, which the kernels' d may pad to a multiple of 4
   int d, n, m, k, kp, nb;
   int transpose;
   int sub;                // chain_pipe_kernel, chain_quad_kernel, chain_team_tile_kernel: steps per block (set by their launchers)
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(1024) chain_kernel(ChainArgs p) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int x = 4 * (tid + u * NT) + r;
-      if (x < d) p.out[(size_t)x * m + col] = a[u][r];
+      if (x < p.out_rows) p.out[(size_t)x * m + col] = a[u][r];
     }
   }
 }
@@ -499,7 +500,7 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
   if (s < nb) apply_block(block_of(s), ra, block_of(s), rb);
 #pragma unroll
   for (int r = 0; r < VW; ++r)
-    if (keep[r]) p.out[(size_t)(x0 + r) * m + col] = a.e[r];
+    if (keep[r] && x0 + r < (unsigned)p.out_rows) p.out[(size_t)(x0 + r) * m + col] = a.e[r];
 }
 
 template <int K, int VW, int NT, int RL = 0, int SUB = 1, bool PAD = false, int P1 = 0, bool UNAL = false, int XB = 0>
@@ -547,33 +548,9 @@ static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
     if (k == 64) return launch_chain_split_pair<2>(a, stream);
     return launch_chain_split_pair<4>(a, stream);
   }
-  if (chain_uses_pipe(a) && d % 4 != 0) {
-    // rows not 16-byte aligned: the general form of the kernels (any block size, short last step)
-    if (chain_pair_serves(a) && (a.m <= (d > 896 ? 176 : kComputeUnits) || d <= 512)) {  // as for aligned rows below
-      if (d <= 256) return launch_chain_pair<2, 0, 4, 4, 3, 2, true, true>(a, stream);
-      if (d <= 512) return launch_chain_pair<4, 0, 4, 4, 3, 2, true, true>(a, stream);
-      return launch_chain_pair<8, 0, 4, 4, 3, 2, true, true>(a, stream);
-    }
-    if (d <= 1024) {
-      if (k <= 8) return launch_chain_pipe<8, 4, 256, 2, 0, true, 0, true>(a, stream);
-      if (k <= 16) return launch_chain_pipe<16, 4, 256, 4, 0, true, 0, true>(a, stream);
-      return launch_chain_pipe<32, 4, 256, 8, 0, true, 7, true, 1>(a, stream);
-    } else if (d <= 2048) {
-      if (k <= 8) return launch_chain_pipe<8, 4, 512, 2, 0, true, 1, true, 1>(a, stream);
-      return launch_chain_pipe<16, 4, 512, 4, 0, true, 4, true, 1>(a, stream);
-    }
-    return launch_chain_pipe<8, 4, 1024, 2, 0, true, 1, true, 1>(a, stream);
-  }
   if (chain_uses_pipe(a)) {
-    // whole block in registers, two copies; a quarter of the next block is fetched during the reduction
-    if (k == 16 && d <= 256) return launch_chain_pipe<16, 1, 256, 4, 1, false, 4, false, 1>(a, stream);  // narrower lanes keep all four waves busy
-    if (k == 16 && d <= 512) return launch_chain_pipe<16, 2, 256, 4, 1, false, 4, false, 1>(a, stream);
-    if (k == 8 && d <= 256) return launch_chain_pipe<8, 1, 256, 2>(a, stream);
-    if (k == 8 && d <= 512) return launch_chain_pipe<8, 2, 256, 2>(a, stream);
-    if (k == 16 && d <= 1024) return launch_chain_pipe<16, 4, 256, 4, 1, false, 4, false, 1>(a, stream);
-    if (k == 16 && d <= 2048) return launch_chain_pipe<16, 4, 512, 4, 1, false, 4, false, 1>(a, stream);
-    // Blocks of 32, 64 or 128 rows, at most one column per compute unit: one wave per 128 elements of the column,
-    // pairs of lanes sharing a chunk (d = n = 1024, m = 32, k = 32: 108.6 -> 102.3 us per forward + backward against
+    // Steps of 32 rows by one wave per 128 elements of the column, pairs of lanes sharing a chunk, while there is at most
+    // a column per compute unit (d = n = 1024, m = 32, k = 32: 108.6 -> 102.3 us per forward + backward against
     // the kernels below; d = 512: 54.2 -> 44.8 us; d = 256: 30.4 -> 29.1 us)
     // (with more columns than compute units it stays the faster one up to d = 512, where two or four of its workgroups
     // share a unit: d = 512, m = 512: 108 -> 86 us, m = 1024: 194 -> 148 us; beyond, the 16-row steps further down win)
@@ -586,56 +563,53 @@ static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
   do {                                                                                    \
     if (k == 32) return launch_chain_pair<NW, 1, 4, 4, 3, 2>(a, stream);                  \
     if (k == 64) return launch_chain_pair<NW, 2, 4, 4, 3, 2>(a, stream);                  \
-    if (k == 128) return launch_chain_pair<NW, 4, 4, 4, 3, 2>(a, stream);                 \
-    if (k < 32) return launch_chain_pair<NW, 1, 4, 4, 3, 2, true>(a, stream);             \
-    if (k < 64) return launch_chain_pair<NW, 2, 4, 4, 3, 2, true>(a, stream);             \
-    if (k <= 96) return launch_chain_pair<NW, 3, 4, 4, 3, 2, true>(a, stream);            \
-    return launch_chain_pair<NW, 4, 4, 4, 3, 2, true>(a, stream);                         \
+    return launch_chain_pair<NW, 4, 4, 4, 3, 2>(a, stream);                               \
   } while (0)
       if (d <= 256) FASTH_LAUNCH_PAIR(2);
       if (d <= 512) FASTH_LAUNCH_PAIR(4);
       FASTH_LAUNCH_PAIR(8);
 #undef FASTH_LAUNCH_PAIR
     }
-    // More columns than compute units (and too few for the matrix-core kernel): steps of 16 rows take 166 registers
-    // against the 291 of 32-row steps, so three workgroups share a compute unit and fill each other's waits
-    // (d = 1024, k = 32, per forward + backward: m = 384: 233 -> 194 us, m = 512: 244 -> 222, m = 768: 356 -> 321;
-    // up to 256 columns the 32-row steps are the faster ones: 137 against 149 us at m = 256).
-    if (a.m > kComputeUnits && d > 512 && d <= 1024) {
-      if (k == 32) return launch_chain_pipe<16, 4, 256, 4, 2, false, 4, false, 1>(a, stream);
-      if (k == 64) return launch_chain_pipe<16, 4, 256, 4, 4, false, 4, false, 1>(a, stream);
-      if (k == 128) return launch_chain_pipe<16, 4, 256, 4, 8, false, 4, false, 1>(a, stream);
+    if (d % 4 == 0 && (k == 32 || k == 64 || k == 128)) {
+      // More columns than compute units (and too few for the matrix-core kernel): steps of 16 rows take 166 registers
+      // against the 291 of 32-row steps, so three workgroups share a compute unit and fill each other's waits
+      // (d = 1024, k = 32, per forward + backward: m = 384: 233 -> 194 us, m = 512: 244 -> 222, m = 768: 356 -> 321;
+      // up to 256 columns the 32-row steps are the faster ones: 137 against 149 us at m = 256).
+      if (a.m > kComputeUnits && d > 512 && d <= 1024) {
+        if (k == 32) return launch_chain_pipe<16, 4, 256, 4, 2, false, 4, false, 1>(a, stream);
+        if (k == 64) return launch_chain_pipe<16, 4, 256, 4, 4, false, 4, false, 1>(a, stream);
+        return launch_chain_pipe<16, 4, 256, 4, 8, false, 4, false, 1>(a, stream);
+      }
+      // (7 of the 32 rows of the next block fetched during the first product, 8 during the reduction, 4 next to the
+      // barriers, 13 during the update)
+      // Larger blocks and longer vectors: two register copies of the whole block do not fit, but the block can be
+      // applied as steps of 32 rows (d <= 1024), 16 rows (d <= 2048, two waves per SIMD) or 8 (16 waves), which is
+      // faster than one copy refilled in place or rows streamed twice (d = n = 2048: 178 us for k = 32, 64 and 128
+      // alike, against 222, 359 and 406 us)
+      if (d <= 1024) {
+        if (k == 32) return launch_chain_pipe<32, 4, 256, 8, 1, false, 7, false, 1>(a, stream);
+        if (k == 64) return launch_chain_pipe<32, 4, 256, 8, 2, false, 7, false, 1>(a, stream);
+        return launch_chain_pipe<32, 4, 256, 8, 4, false, 7, false, 1>(a, stream);
+      }
+      if (d <= 2048) {
+        if (k == 32) return launch_chain_pipe<16, 4, 512, 4, 2, false, 4, false, 1>(a, stream);  // fetch split 4 / 4 / 4 / 4
+        if (k == 64) return launch_chain_pipe<16, 4, 512, 4, 4, false, 4, false, 1>(a, stream);
+        return launch_chain_pipe<16, 4, 512, 4, 8, false, 4, false, 1>(a, stream);
+      }
+      return launch_chain_pipe<8, 4, 1024, 2, 0, false, 1, false, 1>(a, stream);
     }
-    // (7 of the 32 rows of the next block fetched during the first product, 8 during the reduction, 4 next to the
-    // barriers, 13 during the update)
-    if (k == 32 && d <= 1024) return launch_chain_pipe<32, 4, 256, 8, 1, false, 7, false, 1>(a, stream);
-    // Larger blocks and longer vectors: two register copies of the whole block do not fit, but the block can be
-    // applied as steps of 32 rows (d <= 1024) or 16 rows (d <= 2048, two waves per SIMD), which is faster than
-    // one copy refilled in place or rows streamed twice (d = n = 2048: 178 us for k = 32, 64 and 128 alike,
-    // against 222, 359 and 406 us)
+    // Rows as the caller has them, any length and any block size: only where fasth_forward_static has no room for the
+    // padded copy of V.
     if (d <= 1024) {
-      if (k == 64) return launch_chain_pipe<32, 4, 256, 8, 2, false, 7, false, 1>(a, stream);
-      if (k == 128) return launch_chain_pipe<32, 4, 256, 8, 4, false, 7, false, 1>(a, stream);
-      if (k == 8) return launch_chain_pipe<8, 4, 256, 2, 1, false, 1, false, 1>(a, stream);
-      // any other block size: steps of 8, 16 or 32 rows, the last one of a block short
-      if (k < 8) return launch_chain_pipe<8, 4, 256, 2, 1, true, 1, false, 1>(a, stream);
-      if (k < 16) return launch_chain_pipe<16, 4, 256, 4, 1, true, 4, false, 1>(a, stream);
-      if (k < 32) return launch_chain_pipe<32, 4, 256, 8, 1, true, 7, false, 1>(a, stream);  // one short step per block
-      if (k < 64) return launch_chain_pipe<32, 4, 256, 8, 2, true, 7, false, 1>(a, stream);  // a full step and a short one
-      if (k > 96) return launch_chain_pipe<32, 4, 256, 8, 4, true, 7, false, 1>(a, stream);
-      return launch_chain_pipe<32, 4, 256, 8, 0, true, 7, false, 1>(a, stream);
-    } else if (d <= 2048) {
-      if (k == 32) return launch_chain_pipe<16, 4, 512, 4, 2, false, 4, false, 1>(a, stream);  // fetch split 4 / 4 / 4 / 4
-      if (k == 64) return launch_chain_pipe<16, 4, 512, 4, 4, false, 4, false, 1>(a, stream);
-      if (k == 128) return launch_chain_pipe<16, 4, 512, 4, 8, false, 4, false, 1>(a, stream);
-      if (k == 8) return launch_chain_pipe<8, 4, 512, 2, 1, false, 1, false, 1>(a, stream);
-      if (k < 8) return launch_chain_pipe<8, 4, 512, 2, 0, true, 1, false, 1>(a, stream);
-      return launch_chain_pipe<16, 4, 512, 4, 0, true, 4, false, 1>(a, stream);
-    } else {
-      // 16 waves share 512 registers per lane: two copies of 8 rows
-      if (k % 8 == 0) return launch_chain_pipe<8, 4, 1024, 2, 0, false, 1, false, 1>(a, stream);
-      return launch_chain_pipe<8, 4, 1024, 2, 0, true, 1, false, 1>(a, stream);
+      if (k <= 8) return launch_chain_pipe<8, 4, 256, 2, 0, true, 0, true>(a, stream);
+      if (k <= 16) return launch_chain_pipe<16, 4, 256, 4, 0, true, 0, true>(a, stream);
+      return launch_chain_pipe<32, 4, 256, 8, 0, true, 7, true, 1>(a, stream);
     }
+    if (d <= 2048) {
+      if (k <= 8) return launch_chain_pipe<8, 4, 512, 2, 0, true, 1, true, 1>(a, stream);
+      return launch_chain_pipe<16, 4, 512, 4, 0, true, 4, true, 1>(a, stream);
+    }
+    return launch_chain_pipe<8, 4, 1024, 2, 0, true, 1, true, 1>(a, stream);
   }
   // longer vectors: the general kernel
   const int threads = 1024, nw = threads / 64;

@@ -39,12 +39,6 @@ struct PairRegs {
 };
 
 // SUB: steps of 32 rows per block (k = 32 SUB; the diagonal 32 x 32 blocks of T_i are the steps' factors).
-// PAD: k is not a multiple of 32 and SUB = ceil(k / 32): the last step of a block has fewer than 32 rows; its missing
-// rows repeat the last valid one and their inner products and coefficients are forced to zero.
-// UNAL (with PAD, and SUB = 0: the steps per block come from p.sub): d is not a multiple of 4, so rows are not
-// 16-byte aligned and a row's last chunk hangs over its end. Rows are then fetched through a buffer that spans the
-// step's block (4-byte alignment is enough for it, what lies beyond the block reads as zero); the overhanging
-// elements of `a` see the next row's values, so they are put back to zero after every update and never stored.
 // Three register copies of a step's rows (64 registers each): while step s is applied, the rows of step s + 2 are
 // fetched, so every fetch has more than a whole step to arrive and may be issued wherever it costs least.
 // Of a lane's 16 fetches per step, P1 are issued during the first product, RL during the reduction, XA after the
@@ -65,11 +59,9 @@ struct PairRegs {
 // XCD (workgroups b and b + 8), where the trip is shortest. Every wait is bounded: after p.wait_limit polls a wave
 // gives up for the rest of the launch, raises the library's status word and runs on with what it has, so the
 // kernel always ends; fasth_wait_status() tells the host.
-template <int NW, int SUB, int P1, int RL, int XA, int XC, bool PAD = false, bool UNAL = false, bool SPLIT = false>
+template <int NW, int SUB, int P1, int RL, int XA, int XC, bool SPLIT = false>
 __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
-  static_assert(!UNAL || (PAD && SUB == 0), "the unaligned form is the general one");
-  static_assert(!SPLIT || (NW == 8 && !PAD && !UNAL), "two halves of 1024 elements, whole steps, aligned rows");
-  static_assert(SUB > 0 || PAD, "steps per block");
+  static_assert(!SPLIT || NW == 8, "two halves of 1024 elements");
   typedef PairLanes Lanes;
   constexpr int K = 32, KH = 16, G = 2 * NW, LPT = K / G;  // G threads share a row of op(T), LPT entries each
   typedef PairRegs<LPT> Regs;
@@ -133,35 +125,13 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
   const int sel = ((lane & 32) ? 8 : 0) + ((lane & 16) ? 4 : 0) + ((lane & Lanes::M0) ? 2 : 0) + ((lane & Lanes::M1) ? 1 : 0);
   const bool writer = (lane & Lanes::M2) == 0;
   auto block_of = [&](int s) { return p.transpose ? s : nb - 1 - s; };  // step index of the s-th step applied
-  const int sub = SUB > 0 ? SUB : p.sub;
-  auto step_block = [&](int i) { return SUB == 1 ? i : i / sub; };
-  auto step_part = [&](int i) { return SUB == 1 ? 0 : i % sub; };
-  bool keep[4];  // elements of this lane's chunk that exist
-#pragma unroll
-  for (int r = 0; r < 4; ++r) keep[r] = ok && (!UNAL || x0 + r < (unsigned)d);
-  auto rows_valid = [&](int i) { return PAD ? min(K, p.k - step_part(i) * K) : K; };
+  auto step_block = [&](int i) { return i / SUB; };
+  auto step_part = [&](int i) { return i % SUB; };
   auto load_row = [&](int i, int jj, Chunk<4>& dst) {
-    if constexpr (PAD) {
-      // rows 2jj and 2jj + 1 of the step, clamped to its last valid row (scalar arithmetic but for one select)
-      const int kv = rows_valid(i);
-      const int row0 = step_block(i) * p.k + step_part(i) * K + min(2 * jj, kv - 1);
-      const unsigned off = 2 * jj + 1 < kv ? lane_off : x0;
-      if constexpr (UNAL) {
-        // the buffer spans the step's block of k rows (at most 512 KiB), so V itself may be of any size
-        const BufferDesc vdesc = make_buffer(p.V + (size_t)step_block(i) * p.k * d, (size_t)p.k * d * sizeof(float));
-        const unsigned row = (unsigned)(step_part(i) * K + min(2 * jj, kv - 1));
-        const BufVec<4> v = buffer_load<4>(vdesc, off * 4u, row * (unsigned)d * 4u);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dst.e[r] = v.e[r];
-      } else {
-        dst = load_chunk<4>(p.V + (size_t)row0 * (size_t)d + off);
-      }
-    } else {
-      dst = load_chunk<4>(p.V + ((size_t)i * K + 2 * jj) * (size_t)d + lane_off);
-    }
+    dst = load_chunk<4>(p.V + ((size_t)i * K + 2 * jj) * (size_t)d + lane_off);
   };
   auto load_t = [&](int i, Regs& r) {
-    const int LDT = PAD ? p.kp : K * SUB;  // row stride of the stored factor
+    constexpr int LDT = K * SUB;  // row stride of the stored factor
     const float* Ti = (p.transpose ? p.Tt : p.T) + (size_t)step_block(i) * LDT * LDT + (size_t)step_part(i) * (K * LDT + K);
     const float* src = Ti + trow * LDT + LPT * tg;
     if constexpr (LPT == 2) {
@@ -178,17 +148,8 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
 
   // Applies step i held in `cur` while fetching step ifetch (two steps on) into `dst`.
   auto apply_step = [&](int i, Regs& cur, int ifetch, Regs& dst) {
-    if (p.save_in && ok && h == 0 && (SUB == 1 || step_part(i) == (p.transpose ? 0 : sub - 1))) {
-      float* dst_in = p.save_in + ((size_t)step_block(i) * m + col) * d + x0;
-      if constexpr (UNAL) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (keep[r]) dst_in[r] = a.e[r];
-      } else {
-        store_chunk<4>(dst_in, a);
-      }
-    }
-    const int kv = rows_valid(i);
+    if (p.save_in && ok && h == 0 && (SUB == 1 || step_part(i) == (p.transpose ? 0 : SUB - 1)))
+      store_chunk<4>(p.save_in + ((size_t)step_block(i) * m + col) * d + x0, a);
     float pj[KH];
 #pragma unroll
     for (int jj = 0; jj < KH; ++jj) {
@@ -199,7 +160,7 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
       float acc = 0.f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc = fmaf(cur.v[jj].e[r], a.e[r], acc);
-      pj[jj] = (PAD && 2 * jj + h >= kv) ? 0.f : acc;
+      pj[jj] = acc;
     }
     load_t(ifetch, dst);
     auto prefetch = [&](int t) {
@@ -280,14 +241,9 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
 #pragma unroll
       for (int e = 0; e < LPT; ++e) c = fmaf(cur.t[e], bs[e], c);
       c = group_sum<G>(c);
-      if (PAD && trow >= kv) c = 0.f;
       if (tg == 0) {
         Cv[trow & 1][trow >> 1] = c;
-        if constexpr (PAD) {
-          if (p.save_c && trow < kv) p.save_c[(size_t)col * p.n + (size_t)step_block(i) * p.k + step_part(i) * K + trow] = c;
-        } else {
-          if (p.save_c && half == 0) p.save_c[(size_t)col * p.n + (size_t)i * K + trow] = c;
-        }
+        if (p.save_c && half == 0) p.save_c[(size_t)col * p.n + (size_t)i * K + trow] = c;
       }
     }
     lds_barrier();
@@ -326,7 +282,7 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float sum = acc[r] + Lanes::partner(acc[r]);
-      a.e[r] = keep[r] ? sum : 0.f;
+      a.e[r] = ok ? sum : 0.f;
     }
   };
 
@@ -357,26 +313,25 @@ __global__ void __launch_bounds__(64 * NW) chain_pair_kernel(ChainArgs p) {
   if (ok) {
     // each lane of a pair stores two of the chunk's four elements
     const float o0 = h ? a.e[2] : a.e[0], o1 = h ? a.e[3] : a.e[1];
-    if (!UNAL || x0 + 2 * h < (unsigned)d) p.out[(size_t)(x0 + 2 * h) * m + col] = o0;
-    if (!UNAL || x0 + 2 * h + 1 < (unsigned)d) p.out[(size_t)(x0 + 2 * h + 1) * m + col] = o1;
+    if (x0 + 2 * h < (unsigned)p.out_rows) p.out[(size_t)(x0 + 2 * h) * m + col] = o0;
+    if (x0 + 2 * h + 1 < (unsigned)p.out_rows) p.out[(size_t)(x0 + 2 * h + 1) * m + col] = o1;
   }
 }
 
-// Blocks of more than 16 rows (smaller ones would mostly fetch repeated rows in a 32-row step).
-static bool chain_pair_serves(const ChainArgs& a) { return a.d <= 1024 && a.k > 16; }
+static bool chain_pair_serves(const ChainArgs& a) {
+  return a.d <= 1024 && a.d % 4 == 0 && (a.k == 32 || a.k == 64 || a.k == 128);
+}
 
-template <int NW, int SUB, int P1, int RL, int XA, int XC, bool PAD = false, bool UNAL = false>
+template <int NW, int SUB, int P1, int RL, int XA, int XC>
 static int launch_chain_pair(const ChainArgs& args, hipStream_t stream) {
   ChainArgs a = args;
-  a.sub = (args.k + 31) / 32;
+  a.sub = args.k / 32;
   a.nb = args.nb * a.sub;
-  if (!chain_pair_serves(a) || a.d > 128 * NW || (SUB > 0 && SUB != a.sub) || (!PAD && (a.k % 32 != 0 || a.kp != a.k)) ||
-      32 * a.sub > a.kp || (!UNAL && a.d % 4 != 0))
-    return FASTH_EINVAL;
+  if (!chain_pair_serves(a) || a.d > 128 * NW || SUB != a.sub || a.kp != a.k) return FASTH_EINVAL;
   const int side = a.ds_out ? (a.ds_rows + NW - 1) / NW : 0;
-  static const std::string name = variant_name("chain_pair_kernel", {NW, SUB, P1, RL, XA, XC, PAD, UNAL});
+  static const std::string name = variant_name("chain_pair_kernel", {NW, SUB, P1, RL, XA, XC, 0});
   prof::Scope ps_(FASTH_KERNEL_CHAIN, stream, name.c_str());
-  hipLaunchKernelGGL((chain_pair_kernel<NW, SUB, P1, RL, XA, XC, PAD, UNAL>), dim3(a.m + side), dim3(64 * NW), 0, stream, a);
+  hipLaunchKernelGGL((chain_pair_kernel<NW, SUB, P1, RL, XA, XC>), dim3(a.m + side), dim3(64 * NW), 0, stream, a);
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;
 }
@@ -392,9 +347,9 @@ static int launch_chain_split_pair(const ChainArgs& args, hipStream_t stream) {
   a.sub = a.k / 32;
   a.nb = args.nb * a.sub;
   if (!chain_uses_split_pair(a) || SUB != a.sub || a.kp != a.k) return FASTH_EINVAL;
-  static const std::string name = variant_name("chain_pair_kernel", {8, SUB, 4, 4, 3, 2, 0, 0, 1});
+  static const std::string name = variant_name("chain_pair_kernel", {8, SUB, 4, 4, 3, 2, 1});
   prof::Scope ps_(FASTH_KERNEL_CHAIN, stream, name.c_str());
-  hipLaunchKernelGGL((chain_pair_kernel<8, SUB, 4, 4, 3, 2, false, false, true>), dim3(16 * ((a.m + 7) / 8)), dim3(512), 0,
+  hipLaunchKernelGGL((chain_pair_kernel<8, SUB, 4, 4, 3, 2, true>), dim3(16 * ((a.m + 7) / 8)), dim3(512), 0,
                      stream, a);
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;

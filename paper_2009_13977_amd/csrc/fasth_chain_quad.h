@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(64 * kQuadWaves) chain_quad_kernel(ChainArgs p
 #pragma unroll
   for (int s2 = 0; s2 < XS; ++s2) {
     const int x = xw + 64 * s2 + lane;
-    if (x < d) {
+    if (x < p.out_rows) {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (col0 + c < m) p.out[(size_t)x * m + col0 + c] = a[s2][c];

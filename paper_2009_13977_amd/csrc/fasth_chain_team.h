@@ -312,7 +312,7 @@ __global__ void __launch_bounds__(512) chain_team_kernel(ChainArgs p) {
   if (ok) {
     // each of the four lanes of a chunk stores one of its elements
     const float o = q == 0 ? a.e[0] : q == 1 ? a.e[1] : q == 2 ? a.e[2] : a.e[3];
-    p.out[(size_t)(x0 + q) * m + col] = o;
+    if (x0 + q < (unsigned)p.out_rows) p.out[(size_t)(x0 + q) * m + col] = o;
   }
 }
 
@@ -646,7 +646,7 @@ __global__ void __launch_bounds__(512) chain_team_wide_kernel(ChainArgs p) {
   if (ok && q < 4) {
     // four of the eight lanes of a chunk store one of its elements each
     const float o = q == 0 ? a.e[0] : q == 1 ? a.e[1] : q == 2 ? a.e[2] : a.e[3];
-    p.out[(size_t)(x0 + q) * m + col] = o;
+    if (x0 + q < (unsigned)p.out_rows) p.out[(size_t)(x0 + q) * m + col] = o;
   }
 }
 

@@ -350,7 +350,7 @@ __global__ void __launch_bounds__(512) chain_team_tile_kernel(ChainArgs p) {
   if (part == 0 && tid == 0) __builtin_amdgcn_raw_buffer_store_b32(tag0 + (unsigned)ns, hdesc, 0u, 0, 16);
   if (gave_up && lane == 0) __hip_atomic_store(&g_wait_gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   {
-    const BufferDesc odesc = make_buffer(p.out, (size_t)d * m * sizeof(float));
+    const BufferDesc odesc = make_buffer(p.out, (size_t)p.out_rows * m * sizeof(float));
 #pragma unroll
     for (int r = 0; r < NT; ++r) {
 #pragma unroll
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(512) chain_team_tile_kernel(ChainArgs p) {
         const int x = x_w + F * q + NT * j + r;
         BufVec<1> v;
         v.e[0] = A[r][j];
-        buffer_store<1>(odesc, col_ok && x < d ? ((unsigned)x * (unsigned)m + (unsigned)col) * 4u : kOob, 0, v);
+        buffer_store<1>(odesc, col_ok && x < p.out_rows ? ((unsigned)x * (unsigned)m + (unsigned)col) * 4u : kOob, 0, v);
       }
     }
   }

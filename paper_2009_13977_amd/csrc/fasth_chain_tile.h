@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(64 * NW) chain_tile_kernel(ChainArgs p) {
     for (int kk = 0; kk < 4; ++kk) tcur[kk] = tnxt[kk];
     blk = blkn; part = partn;
   }
-  const BufferDesc odesc = make_buffer(p.out, (size_t)d * m * sizeof(float));
+  const BufferDesc odesc = make_buffer(p.out, (size_t)p.out_rows * m * sizeof(float));
 #pragma unroll
   for (int g = 0; g < kTileGroups; ++g) {
 #pragma unroll

@@ -40,11 +40,16 @@ static int padded_block(int k) {
 }
 
 struct Layout {
+  // What the kernels see: vectors padded to dp elements (a multiple of 4), np >= n rows in nb = np / ki blocks of ki rows.
+  // A row of V that does not exist is a zero row whose diagonal entry of the block's triangular matrix is one: its
+  // coefficients are zero and nothing downstream changes.
+  int dp, np, ki;
+  bool copy_v;       // the kernels read a padded copy of V (off_V) that the factor kernels write
   int kp, nb, gram_split, dv_split;
   int kf, kpf, nbf;  // rows of a factor as stored (several of the caller's blocks when a team kernel merges them), padded; their number
   int team_wide;     // parts per column if chain_team_wide_kernel serves the shape (factors stored in its order), else 0
   int npair;         // pairs of blocks whose rows' product V_a V_b^T is formed beside the factors (chain_team_wide_kernel), else 0
-  size_t off_T, off_S, off_Spart, off_ready, off_xch, off_saveA, off_saveCa, off_saveG, off_saveCg, off_dVpart, total;
+  size_t off_V, off_T, off_S, off_Spart, off_ready, off_xch, off_saveA, off_saveCa, off_saveG, off_saveCg, off_dVpart, total;
   size_t xch_words;  // 32-bit words of the hand-off area between workgroups that share a column (0: none)
 };
 
@@ -151,10 +156,36 @@ static bool factor_is_fused(int kp, int d) { return kp <= 32 || (kp == 64 && d <
 #ifndef FASTH_GRAM_SPLIT_128
 #define FASTH_GRAM_SPLIT_128 8
 #endif
-// shared = false: the layout without any kernel in which workgroups share columns (no hand-off area, the caller's own
-// block size for the factors), for a caller whose room for factors is limited.
+// The result does not depend on how consecutive reflections are grouped into blocks (Eq. 2 holds for any grouping), so
+// the caller's block size only says where the library starts from: blocks of 32 rows for k <= 32, of 128 for k = 128, of
+// 64 otherwise, which are what the fast kernels are written for. The last block is filled up with zero rows, and vectors
+// whose length is not a multiple of 4 with zeros, in a copy of V that the factor kernels write as they fetch the rows.
+// Without it such shapes ran on the general kernels (short steps, rows that are not 16-byte aligned, no matrix cores).
+// Forward + backward before and after, us: d = n = 784, k = 28, m = 32: 90.7 -> 71.6, m = 200: 103.9 -> 93.7;
+// d = n = 1000, k = 50, m = 32: 156 -> 82, m = 600: 569 -> 225, m = 2000: 1534 -> 542; d = n = 1023, k = 33, m = 32: 232 -> 81;
+// d = 511, n = 500, k = 25, m = 64: 76.5 -> 49.2; d = n = 2047, k = 23, m = 32: 570 -> 179; d = n = 1024, k = 16, m = 32: 121 -> 75.
+static int inner_block(int k) { return k <= 32 ? 32 : k == kMaxBlock ? kMaxBlock : 64; }
+static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multiple * multiple; }
+
+// shared = false: the layout without any kernel in which workgroups share columns (no hand-off area) and without the
+// padded copy of V (the caller's own block size), for a caller whose room is limited. Vectors too long for the
+// register-resident kernels keep the caller's block size too.
+constexpr int kMaxPaddedD = 4096;
 static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
   Layout L;
+  L.dp = d; L.np = n; L.ki = k;
+  if (shared && d <= kMaxPaddedD) {
+    L.dp = (d + 3) & ~3;
+    L.ki = inner_block(k);
+    const int r128 = padded_rows(n, kWideRows), r64 = padded_rows(n, L.ki < 64 ? 64 : L.ki);
+    // a step of 128 rows takes less than twice as long as one of 64 (2.65 against 1.95 us at d = 1024), so only up to
+    // 64 rows are better padded to 64
+    if (n > 64 && team_wide_parts(L.dp, r128, m, L.ki)) L.np = r128;
+    else if (team_parts(L.dp, r64, m, L.ki) || team_tile_parts(L.dp, r64, m, L.ki)) L.np = r64;
+    else L.np = padded_rows(n, L.ki);
+  }
+  L.copy_v = L.dp != d || L.np != n;
+  d = L.dp; n = L.np; k = L.ki;
   L.kp = padded_block(k);
   L.nb = n / k;
   const int team = shared ? team_parts(d, n, m, k) : 0, wide = shared ? team_wide_parts(d, n, m, k) : 0;
@@ -177,6 +208,7 @@ static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
     off = align_up(off + floats * sizeof(float), 256);
     return o;
   };
+  L.off_V = take(L.copy_v ? (size_t)n * d : 0);
   L.off_T = take(2 * (size_t)L.nbf * L.kpf * L.kpf);  // the factors and, behind them, their transposes
   // partial Gram matrices (later the dV kernel's per-block matrices Z, nb kp^2 floats, which they always cover) and,
   // where the Gram product is split over workgroups, an 8-byte "ready" word per partial matrix

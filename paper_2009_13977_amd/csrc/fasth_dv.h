@@ -33,6 +33,7 @@ struct DvArgs {
   int cols_per_part;    // columns per such workgroup, a multiple of the chunk of 32 (m rounded up if msplit = 1)
   int d, n, m, k, kp;
   int transpose;        // of the forward product
+  int out_d, out_n;     // columns and rows of dV that exist (d and n may be padded)
   int accumulate;       // add to dV instead of overwriting it (a factor that enters a layer twice)
 };
 
@@ -49,7 +50,7 @@ __global__ void __launch_bounds__(256) dv_z_kernel(DvPair pair) {
   __shared__ __align__(16) float part[4][256];
   const DvArgs p = pair.a[blockIdx.z];
   const int k = p.k, kp = p.kp, m = p.m, n = p.n, kt = kp / 16;
-  if ((int)blockIdx.y * k >= n || (int)blockIdx.x >= kt * kt) return;  // whole workgroup, before the barrier
+  if ((int)blockIdx.y * k >= p.out_n || (int)blockIdx.x >= kt * kt) return;  // whole workgroup, before the barrier
   const int i = blockIdx.y, ti = blockIdx.x / kt, tj = blockIdx.x % kt;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, q = lane >> 4;
   const BufferDesc cgdesc = make_buffer(p.saveCg, (size_t)m * n * sizeof(float));
@@ -92,7 +93,7 @@ __global__ void __launch_bounds__(256) dv_kernel(DvPair pair) {
   const int msplit = pair.a[0].msplit, which = (int)blockIdx.z >= msplit ? 1 : 0, part = (int)blockIdx.z - which * msplit;
   const DvArgs p = pair.a[which];
   const int k = p.k, d = p.d, m = p.m, n = p.n;
-  if ((int)blockIdx.y * k >= n || (int)blockIdx.x * kDvTile >= d) return;  // whole workgroup, before any barrier
+  if ((int)blockIdx.y * k >= p.out_n || (int)blockIdx.x * kDvTile >= d) return;  // whole workgroup, before any barrier
   // this workgroup's columns: whole chunks of kDvMChunk (cols_per_part comes from the host)
   const int m_begin = part * p.cols_per_part, m_end = min(m, m_begin + p.cols_per_part);
   constexpr int LDE = kp + 4, LDC = kDvMChunk + 4, LDX = kDvTile + 4;
@@ -268,12 +269,12 @@ __global__ void __launch_bounds__(256) dv_kernel(DvPair pair) {
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
         const int j = ti * 16 + 4 * q + jj, x = x0 + tx * 16 + li;
-        if (j < k && x < d) {
+        if (j < k && i * k + j < p.out_n && x < p.out_d) {
           const float val = ev[jj] - acc[w][jj];
           if (msplit > 1) {
-            p.dVpart[((size_t)part * n + (size_t)i * k + j) * d + x] = val;  // summed by dv_sum_kernel
+            p.dVpart[((size_t)part * p.out_n + (size_t)i * k + j) * p.out_d + x] = val;  // summed by dv_sum_kernel
           } else {
-            float* dst = p.dV + ((size_t)i * k + j) * d + x;
+            float* dst = p.dV + ((size_t)i * k + j) * p.out_d + x;
             *dst = p.accumulate ? *dst + val : val;
           }
         }
@@ -285,7 +286,7 @@ __global__ void __launch_bounds__(256) dv_kernel(DvPair pair) {
 // dV = sum of the mini-batch parts (fixed order), for up to two products: blockIdx.y picks the product.
 __global__ void __launch_bounds__(256) dv_sum_kernel(DvPair pair) {
   const DvArgs p = pair.a[blockIdx.y];
-  const size_t nd = (size_t)p.n * p.d, idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t nd = (size_t)p.out_n * p.out_d, idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= nd) return;
   float sum = p.dVpart[idx];
   for (int part = 1; part < p.msplit; ++part) sum += p.dVpart[(size_t)part * nd + idx];

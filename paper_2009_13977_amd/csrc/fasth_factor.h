@@ -195,7 +195,10 @@ struct TeamFactorArgs {
   float* T;                    // [2][nb][kp][kp]
   unsigned long long* ready;   // [nb][split]
   unsigned long long launch_id;
-  int d, k, kp, split, wait_limit;
+  int d, n, k, kp, split, wait_limit;
+  // padded copy of V for the later kernels, [nblocks k][dp] (null: they read V): written by whoever fetches a block's rows
+  float* copy;
+  int dp;
   unsigned* xch;               // hand-off area of the chain kernels, cleared here
   unsigned xch_words;
   // For chain_team_wide_kernel (kp = 64 only): npair > 0 adds, per pair p of consecutive blocks, the product
@@ -215,7 +218,7 @@ __global__ void __launch_bounds__(8 * KP) team_factor_kernel(TeamFactorPair pair
   const TeamFactorArgs& p = pair.a[blockIdx.z];
   const int LD = kGramChunk + 4;
   constexpr int kp = KP;
-  const int d = p.d, k = p.k, split = p.split;
+  const int d = p.d, split = p.split;
   const int i = blockIdx.y, s = blockIdx.x;
   const int tid = threadIdx.x, nthreads = blockDim.x, wave = tid >> 6, nwaves = nthreads >> 6, lane = tid & 63;
   clear_exchange_area(p.xch, p.xch_words, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -224,6 +227,7 @@ __global__ void __launch_bounds__(8 * KP) team_factor_kernel(TeamFactorPair pair
   // twice as much and are the last to start otherwise, when the launch has more workgroups than run at once.
   const bool pair_job = KP == 64 && i < p.npair;
   const int bi = i - p.npair;  // a block's workgroups: the block
+  const int k = max(0, min(p.k, p.n - bi * p.k));  // its rows that exist (the last block may be padded)
   {
     float* Vs = smem;  // [kp][LD], a pair's [2 kp][LD]
     const int chunk = ((d + split - 1) / split + 3) & ~3;
@@ -236,8 +240,11 @@ __global__ void __launch_bounds__(8 * KP) team_factor_kernel(TeamFactorPair pair
 #pragma unroll
     for (int w = 0; w < kMaxTilesPerWave; ++w) acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the block's k rows as one buffer: rows k .. kp - 1 of the padded block lie beyond it and read as zero
-    const BufferDesc vdesc = pair_job ? make_buffer(p.V + (size_t)i * 2 * kp * d, (size_t)2 * kp * d * sizeof(float))
-                                      : make_buffer(p.V + (size_t)bi * k * d, (size_t)k * d * sizeof(float));
+    const BufferDesc vdesc = pair_job ? make_buffer(p.V + (size_t)i * 2 * kp * d, (size_t)max(0, min(2 * kp, p.n - i * 2 * kp)) * d * sizeof(float))
+                                      : make_buffer(p.V + (size_t)bi * p.k * d, (size_t)k * d * sizeof(float));
+    const bool copies = p.copy != nullptr && !pair_job;
+    const int cend = min(p.dp, xbeg + chunk);
+    const BufferDesc cdesc = make_buffer(p.copy + (size_t)(pair_job ? 0 : bi) * p.k * p.dp, (size_t)p.k * p.dp * sizeof(float));
     constexpr int XV = kGramChunk / VEC;  // loads per slab row
     constexpr int PER1 = 16 / VEC;        // loads per thread and slab: kp XV / nthreads with nthreads = 8 kp
     constexpr int PER = KP == 64 ? 2 * PER1 : PER1;  // room for a pair's rows; a block's workgroups use the first half
@@ -265,6 +272,13 @@ __global__ void __launch_bounds__(8 * KP) team_factor_kernel(TeamFactorPair pair
       for (int it = 0; it < PER; ++it) {
         const int idx = tid + it * nthreads;
         if (it < nper) lds_store<VEC>(Vs + (idx / XV) * LD + (idx % XV) * VEC, stage[it]);
+      }
+      if (copies) {
+#pragma unroll
+        for (int it = 0; it < PER1; ++it) {
+          const int idx = tid + it * nthreads, j = idx / XV, x = x0 + (idx % XV) * VEC;
+          buffer_store<VEC>(cdesc, x < cend ? (unsigned)(j * p.dp + x) * 4u : kOob, 0, stage[it]);
+        }
       }
       __syncthreads();
       if (x0 + kGramChunk < xend) fetch_slab(x0 + kGramChunk);
@@ -413,6 +427,8 @@ struct FactorPair {
   const float* V[2];  // [n][d]
   float* T[2];        // [2][nb][kp][kp]: the factors, then their transposes
   int d[2], k[2], nb[2];
+  int n[2], dp[2];    // rows that exist (the last block may be padded); row length of the padded copy
+  float* copy[2];     // padded copy of V for the later kernels, [nb k][dp], or null
   unsigned* xch[2];   // hand-off area of the product's workspace, cleared here
   unsigned xch_words[2];
 };
@@ -424,7 +440,7 @@ __global__ void __launch_bounds__(512) factor_fused_kernel(FactorPair fp) {
   clear_exchange_area(fp.xch[which], fp.xch_words[which], blockIdx.x, fp.nb[which]);
   const float* __restrict__ V = fp.V[which];
   float* __restrict__ T = fp.T[which];
-  const int d = fp.d[which], k = fp.k[which];
+  const int d = fp.d[which];
   constexpr int kp = 16 * KT, LD = kGramChunk + 4, NTILE = KT * (KT + 1) / 2, NW = 8, LDM = kp + 4;
   constexpr int PER = kp * kGramChunk / 512 / VEC;  // loads per thread and slab
   constexpr int XV = kGramChunk / VEC;              // loads per slab row
@@ -438,7 +454,11 @@ __global__ void __launch_bounds__(512) factor_fused_kernel(FactorPair fp) {
   const int i = blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, q = lane >> 4;
   // the block's k rows as one buffer: rows k .. kp - 1 of the padded block lie beyond it and read as zero
-  const BufferDesc vdesc = make_buffer(V + (size_t)i * k * d, (size_t)k * d * sizeof(float));
+  const int k = max(0, min(fp.k[which], fp.n[which] - i * fp.k[which]));  // rows of the block that exist (none: padding only)
+  const BufferDesc vdesc = make_buffer(V + (size_t)i * fp.k[which] * d, (size_t)k * d * sizeof(float));
+  const int dp = fp.dp[which];
+  const bool copies = fp.copy[which] != nullptr;
+  const BufferDesc cdesc = make_buffer(fp.copy[which] + (size_t)i * fp.k[which] * dp, (size_t)fp.k[which] * dp * sizeof(float));
   f32x4 acc[NTILE];
 #pragma unroll
   for (int t = 0; t < NTILE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -465,6 +485,13 @@ __global__ void __launch_bounds__(512) factor_fused_kernel(FactorPair fp) {
         for (int it = 0; it < PER; ++it) {
           const int idx = tid + it * 512;
           lds_store<VEC>(Vs + (idx / XV) * LD + (idx % XV) * VEC, stage[sl][it]);
+        }
+        if (copies) {
+#pragma unroll
+          for (int it = 0; it < PER; ++it) {
+            const int idx = tid + it * 512, j = idx / XV, x = xs + sl * kGramChunk + (idx % XV) * VEC;
+            buffer_store<VEC>(cdesc, x < dp ? (unsigned)(j * dp + x) * 4u : kOob, 0, stage[sl][it]);
+          }
         }
         __syncthreads();
         // This wave's 16 columns of the slab, one 16-byte read per 16-row group: lane (i, q) holds
