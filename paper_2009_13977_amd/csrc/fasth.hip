@@ -20,7 +20,7 @@
 //   seq_*                the one-reflection-at-a-time comparison
 //   dsigma_kernel        the diagonal step of the SVD layer
 // The kernels live in fasth_factor.h, fasth_chain.h (+ fasth_chain_team.h, fasth_chain_pair.h, fasth_chain_quad.h,
-// fasth_chain_tile.h), fasth_dv.h and fasth_sequential.h (helpers in fasth_common.h and fasth_device.h); this file holds
+// fasth_chain_tile.h, fasth_chain_trio.h, fasth_chain_teamtile.h), fasth_dv.h and fasth_sequential.h (helpers in fasth_common.h and fasth_device.h); this file holds
 // the host drivers and the C entry points.
 #include <hip/hip_runtime.h>
 
@@ -60,6 +60,7 @@ struct Product {  // one Householder product bound to its slice of a workspace
   // the rows the kernels read: the caller's, or the padded copy the factor kernels leave in the workspace
   const float* rows(const float* V) const { return L.copy_v ? reinterpret_cast<const float*>(ws + L.off_V) : V; }
   float* copy() const { return L.copy_v ? reinterpret_cast<float*>(ws + L.off_V) : nullptr; }
+  char* frag() const { return L.trio.parts ? ws + L.off_frag : nullptr; }
   float* T() const { return reinterpret_cast<float*>(ws + L.off_T); }
   float* Spart() const { return reinterpret_cast<float*>(ws + L.off_Spart); }
   unsigned* xch() const { return L.xch_words ? reinterpret_cast<unsigned*>(ws + L.off_xch) : nullptr; }
@@ -69,10 +70,10 @@ struct Product {  // one Householder product bound to its slice of a workspace
   float* saveCg() const { return reinterpret_cast<float*>(ws + L.off_saveCg); }
 };
 
-static Product bind(int d, int n, int m, int k, void* ws, bool shared = true) {
+static Product bind(int d, int n, int m, int k, void* ws, LayoutLevel level = kLayoutTrio) {
   Product P;
   P.d = d; P.n = n; P.m = m; P.k = k;
-  P.L = make_layout(d, n, m, k, shared);
+  P.L = make_layout(d, n, m, k, level);
   P.ws = static_cast<char*>(ws);
   return P;
 }
@@ -143,7 +144,23 @@ static int launch_team_factor(const TeamFactorPair& pair, int count, int nbf, hi
   return FASTH_OK;
 }
 
-static int build_factors(const Product& P, const float* V, hipStream_t stream) {
+// The rows of V as chain_trio_kernel's operands, for up to two products in one launch.
+static int launch_trio_rows(const Product& P0, const float* V0, const Product* P1, const float* V1, hipStream_t stream) {
+  TrioRowsPair pair;
+  auto bind_rows = [](const Product& P, const float* V) {
+    return TrioRowsArgs{V, P.frag(), P.d, P.n, P.L.trio.parts ? (P.L.dp + 31) / 32 : 0, P.L.trio.parts ? P.L.np / 64 : 0};
+  };
+  pair.a[0] = bind_rows(P0, V0);
+  pair.a[1] = P1 ? bind_rows(*P1, V1) : TrioRowsArgs{};
+  const int xb = std::max(pair.a[0].xblocks, pair.a[1].xblocks), steps = std::max(pair.a[0].steps, pair.a[1].steps);
+  if (xb == 0) return FASTH_OK;
+  prof::Scope ps_(FASTH_KERNEL_RESERVED, stream, "trio_rows_kernel");
+  hipLaunchKernelGGL(trio_rows_kernel, dim3(xb, steps, P1 ? 2 : 1), dim3(256), 0, stream, pair);
+  FASTH_HIP(hipGetLastError());
+  return FASTH_OK;
+}
+
+static int build_factors_only(const Product& P, const float* V, hipStream_t stream) {
   const int kp = P.L.kpf;
   if (factor_is_fused(kp, P.d)) {
     FactorPair fp;
@@ -157,10 +174,17 @@ static int build_factors(const Product& P, const float* V, hipStream_t stream) {
   return launch_team_factor(pair, 1, P.L.nbf, stream);
 }
 
+static int build_factors(const Product& P, const float* V, hipStream_t stream) {
+  const int rc = launch_trio_rows(P, V, nullptr, nullptr, stream);
+  return rc != FASTH_OK ? rc : build_factors_only(P, V, stream);
+}
+
 // Factors of two products (independent of each other) in one launch when both take the fused
 // kernel with the same template arguments; otherwise one after the other.
 static int build_factors_pair(const Product& P0, const float* V0, const Product& P1, const float* V1,
                               hipStream_t stream) {
+  const int rows_rc = launch_trio_rows(P0, V0, &P1, V1, stream);
+  if (rows_rc != FASTH_OK) return rows_rc;
   if (factor_is_fused(P0.L.kpf, P0.d) && factor_is_fused(P1.L.kpf, P1.d) && P0.L.kpf == P1.L.kpf &&
       (P0.d % 4 == 0) == (P1.d % 4 == 0)) {
     FactorPair fp;
@@ -175,8 +199,8 @@ static int build_factors_pair(const Product& P0, const float* V0, const Product&
     pair.a[1] = team_factor_args(P1, V1);
     return launch_team_factor(pair, 2, P0.L.nbf, stream);
   }
-  const int rc = build_factors(P0, V0, stream);
-  return rc != FASTH_OK ? rc : build_factors(P1, V1, stream);
+  const int rc = build_factors_only(P0, V0, stream);
+  return rc != FASTH_OK ? rc : build_factors_only(P1, V1, stream);
 }
 
 // A = H in (transpose = 0) or H^T in (transpose = 1); activation = true saves into the activation
@@ -195,6 +219,7 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   a.Tt = a.T + (size_t)F.L.nbf * F.L.kpf * F.L.kpf;
   a.save_in = !save ? nullptr : activation ? P.saveA() : P.saveG();
   a.save_c = !save ? nullptr : activation ? P.saveCa() : P.saveCg();
+  a.frag = F.frag();
   a.in_scale = in_scale; a.in_scale_mode = in_scale_mode;
   a.in_rows = in_rows < 0 ? P.d : in_rows;
   a.out_rows = P.d;
@@ -210,13 +235,31 @@ static DvArgs dv_args(const Product& P, const float* V, float* dV, int transpose
   DvArgs a;
   a.accumulate = accumulate ? 1 : 0;
   a.V = (factors ? *factors : P).rows(V); a.saveA = P.saveA(); a.saveCa = P.saveCa(); a.saveG = P.saveG(); a.saveCg = P.saveCg(); a.dV = dV;
-  a.Z = P.Spart();  // the partial Gram matrices are dead once the factors exist; Z needs nb kp^2 of their floats
+  // the partial Gram matrices are dead once the factors exist; Z needs nb kp^2 of their floats
+  a.Z = P.L.dv_trio && P.L.dv_split > 1 ? reinterpret_cast<float*>(P.ws + P.L.off_Zpart) : P.Spart();
   a.msplit = P.L.dv_split;
   a.cols_per_part = ((P.m + a.msplit - 1) / a.msplit + kDvMChunk - 1) / kDvMChunk * kDvMChunk;
+  a.msplit = (P.m + a.cols_per_part - 1) / a.cols_per_part;  // no empty part
   a.dVpart = reinterpret_cast<float*>(P.ws + P.L.off_dVpart);
   a.d = P.L.dp; a.n = P.L.np; a.m = P.m; a.k = P.L.ki; a.kp = P.L.kp; a.transpose = transpose;
   a.out_d = P.d; a.out_n = P.n;
   return a;
+}
+
+static int launch_dv_trio(const DvPair& pair, int count, hipStream_t stream) {
+  int xt = 0, nb = 0;
+  for (int c = 0; c < count; ++c) {
+    xt = std::max(xt, (pair.a[c].out_d + kDvTrioTile - 1) / kDvTrioTile);
+    nb = std::max(nb, (pair.a[c].out_n + kDvTrioRows - 1) / kDvTrioRows);
+  }
+  prof::Scope ps_(FASTH_KERNEL_DV, stream, "dv_trio_kernel");
+  hipLaunchKernelGGL(dv_trio_kernel, dim3(xt, nb, count * pair.a[0].msplit), dim3(512), 0, stream, pair);
+  FASTH_HIP(hipGetLastError());
+  if (pair.a[0].msplit == 1) return FASTH_OK;
+  static_assert(kDvTrioTile == 4 * kDvTile, "workgroups of dv_finish_kernel");
+  hipLaunchKernelGGL(dv_finish_kernel, dim3(4 * xt, nb, count), dim3(256), 0, stream, pair);
+  FASTH_HIP(hipGetLastError());
+  return FASTH_OK;
 }
 
 static int launch_dv(const DvPair& pair, int count, int kp, bool vec4, hipStream_t stream) {
@@ -285,6 +328,7 @@ static int run_dv(const Product& P, const float* V, float* dV, int transpose, hi
                   bool accumulate = false, const Product* factors = nullptr) {
   DvPair pair;
   pair.a[0] = pair.a[1] = dv_args(P, V, dV, transpose, accumulate, factors);
+  if (P.L.dv_trio) return launch_dv_trio(pair, 1, stream);
   return launch_dv(pair, 1, P.L.kp, P.L.dp % 4 == 0, stream);
 }
 
@@ -292,10 +336,11 @@ static int run_dv(const Product& P, const float* V, float* dV, int transpose, hi
 // arguments; otherwise one after the other.
 static int run_dv_pair(const Product& P0, const float* V0, float* dV0, int transpose0, const Product& P1,
                        const float* V1, float* dV1, int transpose1, hipStream_t stream) {
-  if (P0.L.kp == P1.L.kp && (P0.L.dp % 4 == 0) == (P1.L.dp % 4 == 0) && P0.L.dv_split == P1.L.dv_split) {
+  if (P0.L.kp == P1.L.kp && (P0.L.dp % 4 == 0) == (P1.L.dp % 4 == 0) && P0.L.dv_split == P1.L.dv_split && P0.L.dv_trio == P1.L.dv_trio) {
     DvPair pair;
     pair.a[0] = dv_args(P0, V0, dV0, transpose0, false);
     pair.a[1] = dv_args(P1, V1, dV1, transpose1, false);
+    if (P0.L.dv_trio) return launch_dv_trio(pair, 2, stream);
     return launch_dv(pair, 2, P0.L.kp, P0.L.dp % 4 == 0, stream);
   }
   const int rc = run_dv(P0, V0, dV0, transpose0, stream);
@@ -484,7 +529,7 @@ int fasth_wait_status(void* stream) {
 const char* fasth_kernel_name(int id) {
   switch (id) {
     case FASTH_KERNEL_TEAM_FACTOR: return "team_factor_kernel";
-    case FASTH_KERNEL_RESERVED: return "";
+    case FASTH_KERNEL_RESERVED: return "trio_rows_kernel";
     case FASTH_KERNEL_CHAIN: return "chain_kernel";
     case FASTH_KERNEL_DV: return "dv_kernel";
     case FASTH_KERNEL_SEQ_FORWARD: return "seq_forward_kernel";
@@ -592,16 +637,16 @@ int fasth_forward_static(const fasth_shape* shape, const float* V, const float* 
   // only the regions Step 1 writes and Step 2 reads: nothing is saved for a backward pass
   // (where the kernels in which workgroups share columns would need more room than the array has, the layout without
   // them: no hand-off area and the caller's own block size, and the chain runs on the other kernels)
-  bool shared = true;
-  Layout L = make_layout(shape->d, shape->n, shape->m, shape->k, true);
-  if (L.off_saveA > FASTH_STATIC_SCRATCH_BYTES) {
-    shared = false;
-    L = make_layout(shape->d, shape->n, shape->m, shape->k, false);
+  LayoutLevel level = kLayoutTrio;
+  Layout L = make_layout(shape->d, shape->n, shape->m, shape->k, level);
+  while (level != kLayoutPlain && L.off_saveA > FASTH_STATIC_SCRATCH_BYTES) {
+    level = level == kLayoutTrio ? kLayoutShared : kLayoutPlain;
+    L = make_layout(shape->d, shape->n, shape->m, shape->k, level);
   }
   if (L.off_saveA > FASTH_STATIC_SCRATCH_BYTES) return FASTH_EUNSUPPORTED;
   void* ws = nullptr;
   if ((rc = static_scratch(&ws)) != FASTH_OK) return rc;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, ws, shared);
+  const Product P = bind(shape->d, shape->n, shape->m, shape->k, ws, level);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = build_factors(P, V, st)) != FASTH_OK) return rc;
   return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st, false);

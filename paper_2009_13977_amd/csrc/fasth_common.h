@@ -39,6 +39,8 @@ static int padded_block(int k) {
   return kp;
 }
 
+struct TrioPlan { int xt, ct, parts; };  // chain_trio_kernel: template arguments and workgroups per tile (0: not used)
+
 struct Layout {
   // What the kernels see: vectors padded to dp elements (a multiple of 4), np >= n rows in nb = np / ki blocks of ki rows.
   // A row of V that does not exist is a zero row whose diagonal entry of the block's triangular matrix is one: its
@@ -46,10 +48,13 @@ struct Layout {
   int dp, np, ki;
   bool copy_v;       // the kernels read a padded copy of V (off_V) that the factor kernels write
   int kp, nb, gram_split, dv_split;
+  bool dv_trio;      // dv_trio_kernel forms dV
   int kf, kpf, nbf;  // rows of a factor as stored (several of the caller's blocks when a team kernel merges them), padded; their number
   int team_wide;     // parts per column if chain_team_wide_kernel serves the shape (factors stored in its order), else 0
   int npair;         // pairs of blocks whose rows' product V_a V_b^T is formed beside the factors (chain_team_wide_kernel), else 0
-  size_t off_V, off_T, off_S, off_Spart, off_ready, off_xch, off_saveA, off_saveCa, off_saveG, off_saveCg, off_dVpart, total;
+  TrioPlan trio;     // .parts > 0 if chain_trio_kernel serves the shape
+  size_t off_frag;   // the rows of V as that kernel's operands
+  size_t off_V, off_T, off_S, off_Spart, off_ready, off_xch, off_saveA, off_saveCa, off_saveG, off_saveCg, off_dVpart, off_Zpart, total;
   size_t xch_words;  // 32-bit words of the hand-off area between workgroups that share a column (0: none)
 };
 
@@ -130,6 +135,49 @@ static int team_tile_parts(int d, int n, int m, int k) {
   return np >= 2 && team_fits((m + 15) / 16, np) ? np : 0;
 }
 
+// chain_trio_kernel: tiles of 16 ct columns on the bf16 matrix cores at fp32 precision, each shared by `parts` workgroups
+// of 128 xt elements, for more than 1024 columns, or 2048 where chain_team_tile_kernel with its shorter parts serves and is
+// as fast (us, nothing saved: d = 1024, m = 1024: 74 against 76; forward + backward: d = 512, m = 2000: 152 against 157), and two
+// steps or more (d = 1024, n = 64, m = 2000: 76 us without against 83). Every workgroup of a team needs a compute unit on the
+// team's XCD. Short parts and narrow tiles have the least to do per step (us per forward + backward, k = 32, {xt, ct}):
+// d = 512, m = 4096: {4, 1} 179, {4, 2} 205; d = 1024, m = 2048: {4, 1} 324, {4, 2} 376; but 16 columns of 1024 elements keep the
+// matrix cores waiting for V: d = 1024, m = 4096: {4, 2} 647, {8, 1} 699, {8, 2} 833; d = 2048, m = 2048: {4, 2} 1242,
+// {8, 1} 1272, {8, 2} 1506.
+// Before (chain_tile_kernel, dv_kernel), us per forward + backward: d = 256, m = 4096: 118 -> 101; d = 512, m = 4096: 311 -> 184;
+// d = 1024, m = 1100: 481 -> 271, 2048: 574 -> 324, 4096: 751 -> 555; d = 2048, m = 1100: 1782 -> 935, 4096: 2651 -> 1995.
+constexpr int kTrioMaxD = 2048;
+constexpr unsigned trio_words(int np, int ct) { return (unsigned)(kTeamHeadBytes + np * 2 * np * 512 * 16 * ct) / 4u; }
+static TrioPlan trio_plan(int d, int n, int m) {
+  if (m <= (d > 256 && d <= 512 ? 2048 : 1024) || d > kTrioMaxD || n <= 64) return TrioPlan{0, 0, 0};
+  const int narrow = (m + 15) / 16, wide = (m + 31) / 32, np4 = (d + 511) / 512, np8 = (d + 1023) / 1024;
+  if (d <= 512) return TrioPlan{d <= 256 ? 2 : 4, narrow <= kComputeUnits ? 1 : 2, 1};
+  if (team_fits(narrow, np4)) return TrioPlan{4, 1, np4};
+  if (team_fits(wide, np4)) return TrioPlan{4, 2, np4};
+  return d <= 1024 || team_fits(wide, np8) ? TrioPlan{8, 2, np8} : TrioPlan{0, 0, 0};
+}
+
+// dv_trio_kernel: blocks of 64 rows, from 449 columns on and once the products are worth its longer start (us per forward +
+// backward with it and without: d = n = 512, m = 512: 100, 88; d = n = 512, m = 800: 141, 135; d = n = 1024, m = 420: 193, 189;
+// m = 600: 206, 207; m = 800: 220, 244; m = 1024: 239, 272; d = n = 2048, m = 700: 680, 912).
+static bool dv_trio_serves(int d, int n, int m, int k) {
+  return m >= 449 && (double)n * d * m >= 4e8 && k == 64 && d % 2 == 0 &&
+         (size_t)m * n * sizeof(float) < 0x80000000u && (size_t)m * d * sizeof(float) < 0x80000000u && (size_t)n * d * sizeof(float) < 0x80000000u;
+}
+constexpr int kDvTrioTile = 256;  // elements per workgroup
+// Parts of the mini-batch: what a part adds (its partial sums written and read again, the start of its workgroups)
+// against fuller rounds of workgroups.
+static int dv_trio_split(int d, int n, int m) {
+  const int wgs = (d + kDvTrioTile - 1) / kDvTrioTile * (n / 64), chunks = (m + 31) / 32;
+  int best = 1;
+  double best_us = 1e30;
+  for (int s = 1; s <= 16 && s <= (chunks + 1) / 2; ++s) {
+    const double rounds = (wgs * s + kComputeUnits - 1) / kComputeUnits;
+    const double us = rounds * (3.0 + 1.6 * ((chunks + s - 1) / s)) + (s > 1 ? 4.0 + 8e-6 / 4.0 * s * (double)n * d : 0.0);
+    if (us < best_us) { best_us = us; best = s; }
+  }
+  return best;
+}
+
 // The dV kernel has one workgroup per (64-column tile of dV, block). When that is too few to fill the chip and the
 // mini-batch is wide (a short, narrow V against many columns: a 1 x 1 convolution with few channels), the
 // mini-batch is split over up to 32 workgroups whose partial sums meet in a buffer of the workspace.
@@ -171,12 +219,22 @@ static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multip
 // padded copy of V (the caller's own block size), for a caller whose room is limited. Vectors too long for the
 // register-resident kernels keep the caller's block size too.
 constexpr int kMaxPaddedD = 4096;
-static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
+enum LayoutLevel { kLayoutPlain, kLayoutShared, kLayoutTrio };
+static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayoutTrio) {
+  const bool shared = level >= kLayoutShared;
   Layout L;
   L.dp = d; L.np = n; L.ki = k;
-  if (shared && d <= kMaxPaddedD) {
+  L.trio = level == kLayoutTrio ? trio_plan((d + 3) & ~3, n, m) : TrioPlan{0, 0, 0};
+  if (L.trio.parts) {
+    L.dp = (d + 3) & ~3;
+    L.ki = 64;
+    L.np = padded_rows(n, 64);
+  } else if (shared && d <= kMaxPaddedD) {
     L.dp = (d + 3) & ~3;
     L.ki = inner_block(k);
+    // dv_trio_kernel takes 64 rows; blocks of 32 would save twice as many inputs, and the chain kernels for so many columns
+    // take 64 rows per step whatever the block
+    if (dv_trio_serves(L.dp, n, m, 64)) L.ki = 64;
     const int r128 = padded_rows(n, kWideRows), r64 = padded_rows(n, L.ki < 64 ? 64 : L.ki);
     // a step of 128 rows takes less than twice as long as one of 64 (2.65 against 1.95 us at d = 1024), so only up to
     // 64 rows are better padded to 64
@@ -188,12 +246,13 @@ static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
   d = L.dp; n = L.np; k = L.ki;
   L.kp = padded_block(k);
   L.nb = n / k;
-  const int team = shared ? team_parts(d, n, m, k) : 0, wide = shared ? team_wide_parts(d, n, m, k) : 0;
-  const int ttile = shared ? team_tile_parts(d, n, m, k) : 0;
+  const bool others = shared && !L.trio.parts;
+  const int team = others ? team_parts(d, n, m, k) : 0, wide = others ? team_wide_parts(d, n, m, k) : 0;
+  const int ttile = others ? team_tile_parts(d, n, m, k) : 0;
   // The kernels in which workgroups share columns take 64 rows (32: the shared tiles at d > 1024) of factor per step
   // whatever the caller's block size: two blocks of 32 merged by Lemma 1, or the diagonal blocks of a larger block's
   // factor, which are the factors of its row groups; so only those are built.
-  L.kf = wide || team ? 64 : ttile ? (d <= 1024 ? 64 : 32) : k;
+  L.kf = wide || team || L.trio.parts ? 64 : ttile ? (d <= 1024 ? 64 : 32) : k;
   L.team_wide = wide;
   L.npair = wide ? n / kWideRows : 0;
   L.kpf = padded_block(L.kf);
@@ -209,6 +268,7 @@ static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
     return o;
   };
   L.off_V = take(L.copy_v ? (size_t)n * d : 0);
+  L.off_frag = take(L.trio.parts ? (size_t)(n / 64) * ((d + 31) / 32) * (24 * 1024 / 4) : 0);
   L.off_T = take(2 * (size_t)L.nbf * L.kpf * L.kpf);  // the factors and, behind them, their transposes
   // partial Gram matrices (later the dV kernel's per-block matrices Z, nb kp^2 floats, which they always cover) and,
   // where the Gram product is split over workgroups, an 8-byte "ready" word per partial matrix
@@ -218,14 +278,17 @@ static Layout make_layout(int d, int n, int m, int k, bool shared = true) {
   L.xch_words = wide ? (size_t)m * team_wide_words_per_column(wide)
               : team ? (size_t)m * team_words_per_column(team)
               : ttile ? (size_t)((m + 15) / 16) * team_tile_words(ttile)
-              : shared && split_pair_serves(d, m, k) ? (size_t)m * kSplitPairWords : 0;
+              : L.trio.parts > 1 ? (size_t)((m + 16 * L.trio.ct - 1) / (16 * L.trio.ct)) * trio_words(L.trio.parts, L.trio.ct)
+              : others && split_pair_serves(d, m, k) ? (size_t)m * kSplitPairWords : 0;
   L.off_xch = take(L.xch_words);
   L.off_saveA = take((size_t)L.nb * m * d);
   L.off_saveCa = take((size_t)m * n);
   L.off_saveG = take((size_t)L.nb * m * d);
   L.off_saveCg = take((size_t)m * n);
-  L.dv_split = dv_minibatch_split(d, n, m, k);
+  L.dv_trio = shared && dv_trio_serves(d, n, m, k);
+  L.dv_split = L.dv_trio ? dv_trio_split(d, n, m) : dv_minibatch_split(d, n, m, k);
   L.off_dVpart = take(L.dv_split > 1 ? (size_t)L.dv_split * n * d : 0);
+  L.off_Zpart = take(L.dv_trio && L.dv_split > 1 ? (size_t)L.dv_split * n * k : 0);
   L.total = off;
   return L;
 }

@@ -259,4 +259,60 @@ __device__ __forceinline__ constexpr int reduce_writer_mask() {
   return (kWave / NV) - 1;
 }
 
+// ---- fp32 operands as three bf16 pieces ---------------------------------------------------
+// x = h + m + l up to 2^-25 of x: h is x cut off after 8 significant bits (cut, not rounded, so that it cannot
+// overflow), m and l round what is left, so the three products that are left out of six (m l, l m, l l) are
+// at most 2^-24 of a product and of either sign. Inf becomes NaN.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ unsigned round_bf16_pair(float x0, float x1) {
+  bf16x2 r;
+  r[0] = (__bf16)x0;
+  r[1] = (__bf16)x1;
+  return __builtin_bit_cast(unsigned, r);
+}
+// Two numbers; a piece's low half belongs to x0.
+__device__ __forceinline__ void split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  const unsigned u0 = __float_as_uint(x0) & 0xffff0000u, u1 = __float_as_uint(x1) & 0xffff0000u;
+  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+  const float r0 = x0 - __uint_as_float(u0), r1 = x1 - __uint_as_float(u1);
+  m = round_bf16_pair(r0, r1);
+  l = round_bf16_pair(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+struct Trio {
+  bf16x8 p[3];  // h, m, l: a lane's eight inner indices of v_mfma_f32_16x16x32_bf16
+};
+__device__ __forceinline__ Trio split8(const float (&v)[8]) {
+  u32x4 h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    unsigned a, b, c;
+    split2(v[2 * e], v[2 * e + 1], a, b, c);
+    h[e] = a; m[e] = b; l[e] = c;
+  }
+  Trio t;
+  t.p[0] = __builtin_bit_cast(bf16x8, h);
+  t.p[1] = __builtin_bit_cast(bf16x8, m);
+  t.p[2] = __builtin_bit_cast(bf16x8, l);
+  return t;
+}
+// R left operands times CT right operands each, over 32 inner indices: the leading products into hi, the rest into
+// lo. The accumulators take turns so that no instruction waits for the one before it.
+template <int R, int CT>
+__device__ __forceinline__ void trio_mma(const Trio (&v)[R], const Trio* (&a)[R], f32x4* (&hi)[R], f32x4 (&lo)[R][CT]) {
+  constexpr int kLeft[6] = {2, 0, 1, 0, 1, 0}, kRight[6] = {0, 2, 1, 0, 0, 1};  // (0, 0): the leading product
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        f32x4& acc = u == 3 ? hi[r][ct] : lo[r][ct];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v[r].p[kLeft[u]], a[r][ct].p[kRight[u]], acc, 0, 0, 0);
+      }
+    }
+  }
+}
+
 }  // namespace fasth

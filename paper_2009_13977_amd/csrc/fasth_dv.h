@@ -283,6 +283,242 @@ __global__ void __launch_bounds__(256) dv_kernel(DvPair pair) {
   }
 }
 
+// The same products on the bf16 matrix cores at fp32 precision (Trio operands), for mini-batches of some hundred columns
+// and more: 512 threads, a workgroup forms the 64 rows of a block times 256 elements over its part of the mini-batch, 32
+// columns at a time. Wave w owns 32 elements: lane (q, i) fetches two adjacent ones of the columns 8 q .. 8 q + 7 (8 bytes
+// of 8 rows of the saved states, 128 bytes per 16 lanes), which is what it supplies as the right operand of two 16 x 16 tiles, so
+// the states go from memory to the matrix cores without LDS and are split once. The coefficients, the left operands, are
+// common to the waves: each wave splits one 16 x 32 piece of Ca or Cg into LDS (two buffers, one barrier per 32 columns).
+// The same pieces are both operands of Z = Cg Ca^T, whose tiles the waves share out.
+// The fetches of round r + 1 go out as soon as round r's numbers are split and the order is pinned: left to the scheduler, which
+// splits everything first, a round waited for memory and computed in turns (d = n = 1024, m = 4096: 168 -> 150 us; two rounds in
+// flight need more registers than there are: 234 us).
+// A whole mini-batch (msplit = 1): Z passes through LDS and E V_i runs as more rounds of the same kind, -E as left and the
+// block's rows as right operand. A part of it: the part's sums and its Z go to the workspace and dv_finish_kernel ends.
+// With dv_finish_kernel, d = n = 1024: m = 1024 60 -> 45 us (dv_kernel), m = 4096 276 -> 162 us (blocks of 64 instead of 32 rows save
+// half of the states). Of the 150 us of this kernel at m = 4096 the matrix instructions and the operands they read from LDS
+// take 83 (61 at the instructions' rate), waiting for memory 38 (measured with the products left out, and with every round on the same rows).
+constexpr int kDvTrioRows = 64;  // rows of a block
+__global__ void __launch_bounds__(512) dv_trio_kernel(DvPair pair) {
+  constexpr int k = kDvTrioRows, RT = k / 16, LDE = k + 1;
+  __shared__ __align__(16) char left[2][2 * RT * 3 * 1024];
+  const int msplit = pair.a[0].msplit, which = (int)blockIdx.z >= msplit ? 1 : 0, part = (int)blockIdx.z - which * msplit;
+  const DvArgs p = pair.a[which];
+  const int d = p.d, m = p.m, n = p.n;
+  if ((int)blockIdx.y * k >= p.out_n || (int)blockIdx.x * kDvTrioTile >= p.out_d) return;  // whole workgroup, before any barrier
+  const int m_begin = part * p.cols_per_part;
+  const int rounds = (min(m, m_begin + p.cols_per_part) - m_begin + 31) / 32;  // no part is empty
+  const int blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63, q = lane >> 4, i = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x = blockIdx.x * kDvTrioTile + 32 * wave + 2 * i;
+  const size_t state = (size_t)m * d;
+  const BufferDesc gdesc = make_buffer(p.saveG + (size_t)blk * state, state * sizeof(float));
+  const BufferDesc adesc = make_buffer(p.saveA + (size_t)blk * state, state * sizeof(float));
+  // wave w fetches row tile w % RT of Ca (w / RT even) or Cg (odd)
+  const int lrow = 16 * (wave % RT) + i;
+  const BufferDesc cdesc = make_buffer(wave >= RT ? p.saveCg : p.saveCa, (size_t)m * n * sizeof(float));
+  const unsigned l_off = ((unsigned)(8 * q) * (unsigned)n + (unsigned)(blk * k + lrow)) * 4u;
+  const unsigned x_off = (unsigned)(8 * q * d + x) * 4u;
+  struct Round { float2 g[8], a[8]; float l[8]; };
+  Round r0;
+  // columns beyond the mini-batch lie beyond the buffers, elements beyond d (even) are sent there
+  auto fetch = [&](BufferDesc desc, int row0, float2 (&v)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(desc, x < d ? x_off + (unsigned)(row0 + e) * (unsigned)d * 4u : kOob, 0, 0);
+      v[e] = make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
+    }
+  };
+  auto fetch_left = [&](int col0) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r0.l[e] = buffer_load<1>(cdesc, l_off + (unsigned)(col0 + e) * (unsigned)n * 4u, 0).e[0];
+  };
+  f32x4 hi[RT][2], lo[RT][2], zhi[1][2], zlo[1][2];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) hi[r][0] = hi[r][1] = lo[r][0] = lo[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  zhi[0][0] = zhi[0][1] = zlo[0][0] = zlo[0][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto split_pair = [&](const float2 (&v)[8], Trio (&t)[2]) {
+    float v0[8], v1[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { v0[e] = v[e].x; v1[e] = v[e].y; }
+    t[0] = split8(v0);
+    t[1] = split8(v1);
+  };
+  auto read_left = [&](const char* src, Trio& t) {
+#pragma unroll
+    for (int pc = 0; pc < 3; ++pc) t.p[pc] = *reinterpret_cast<const bf16x8*>(src + pc * 1024 + lane * 16);
+  };
+  auto write_left = [&](char* dst, const float (&lv)[8]) {
+    const Trio t = split8(lv);
+#pragma unroll
+    for (int pc = 0; pc < 3; ++pc) *reinterpret_cast<bf16x8*>(dst + pc * 1024 + lane * 16) = t.p[pc];
+  };
+  auto multiply = [&](const char* src, const Trio (&right)[2]) {
+    Trio l[RT];
+    const Trio* rt[RT];
+    f32x4* lead[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      read_left(src + r * 3072, l[r]);
+      rt[r] = right;
+      lead[r] = hi[r];
+    }
+    trio_mma<RT, 2>(l, rt, lead, lo);
+  };
+  const int zr = wave >> 1, zc = 2 * (wave & 1);  // tiles of Z of this wave: (zr, zc) and (zr, zc + 1)
+  fetch_left(m_begin);
+  fetch(gdesc, m_begin, r0.g);
+  fetch(adesc, m_begin, r0.a);
+  for (int it = 0; it < rounds; ++it) {
+    char* buf = left[it & 1];
+    const int next = m_begin + 32 * (it + 1 < rounds ? it + 1 : it);  // the last round's fetches are not used
+    write_left(buf + wave * 3072, r0.l);
+    fetch_left(next);
+    Trio right[2];
+    split_pair(r0.g, right);
+    fetch(gdesc, next, r0.g);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    multiply(buf, right);
+    __builtin_amdgcn_sched_barrier(0);
+    split_pair(r0.a, right);
+    fetch(adesc, next, r0.a);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(buf + RT * 3072, right);
+    {
+      Trio l[1], r2[2];
+      read_left(buf + (RT + zr) * 3072, l[0]);
+      read_left(buf + zc * 3072, r2[0]);
+      read_left(buf + (zc + 1) * 3072, r2[1]);
+      const Trio* rt[1] = {r2};
+      f32x4* lead[1] = {zhi[0]};
+      trio_mma<1, 2>(l, rt, lead, zlo);
+    }
+  }
+  if (msplit == 1) {
+    // E: the carrying triangle of Z mirrored, through LDS; then -E V_i, 32 rows at a time
+    const BufferDesc vdesc = make_buffer(p.V + (size_t)blk * k * d, (size_t)k * d * sizeof(float));
+    fetch(vdesc, 0, r0.g);
+    __syncthreads();
+    float* Zs = reinterpret_cast<float*>(left[0]);
+    static_assert(sizeof(float) * k * LDE <= sizeof(left[0]), "Z fits the first buffer, the operands of -E the second");
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const f32x4 z = zhi[0][c] + zlo[0][c];
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) Zs[(16 * zr + 4 * q + jj) * LDE + 16 * (zc + c) + i] = z[jj];
+    }
+    for (int kb = 0; kb < k / 32; ++kb) {
+      __syncthreads();
+      if (wave < RT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int c = 32 * kb + 8 * q + e;
+          const bool own = p.transpose ? lrow >= c : lrow <= c;  // the entry itself carries, else its mirror image does
+          r0.l[e] = -(own ? Zs[lrow * LDE + c] : Zs[c * LDE + lrow]);
+        }
+        write_left(left[1] + wave * 3072, r0.l);
+      }
+      __syncthreads();
+      Trio right[2];
+      split_pair(r0.g, right);
+      if (kb + 1 < k / 32) fetch(vdesc, 32 * (kb + 1), r0.g);
+      multiply(left[1], right);
+    }
+  } else if (blockIdx.x == 0) {
+    float* Zp = p.Z + ((size_t)part * (p.n / k) + blk) * k * k;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const f32x4 z = zhi[0][c] + zlo[0][c];
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) Zp[(16 * zr + 4 * q + jj) * k + 16 * (zc + c) + i] = z[jj];
+    }
+  }
+  // dV_i = -(Ca g^T + Cg a^T - E V_i)
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const f32x4 s0 = -(hi[r][0] + lo[r][0]), s1 = -(hi[r][1] + lo[r][1]);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int row = blk * k + 16 * r + 4 * q + jj;
+      if (row < p.out_n) {
+        float* dst = (msplit > 1 ? p.dVpart + (size_t)part * p.out_n * p.out_d : p.dV) + (size_t)row * p.out_d + x;
+        const bool add = msplit == 1 && p.accumulate;
+        if (x < p.out_d) dst[0] = add ? dst[0] + s0[jj] : s0[jj];
+        if (x + 1 < p.out_d) dst[1] = add ? dst[1] + s1[jj] : s1[jj];
+      }
+    }
+  }
+}
+
+// The end of a split mini-batch: dV_i = sum of the parts (fixed order) + E V_i, grid (ceil(d / 64), nb, products), 256 threads.
+__global__ void __launch_bounds__(256) dv_finish_kernel(DvPair pair) {
+  constexpr int k = kDvTrioRows, RT = k / 16, LDE = k + 4, LDX = kDvTile + 4;
+  __shared__ __align__(16) float Es[k * LDE];
+  __shared__ __align__(16) float Vs[k * LDX];
+  const DvArgs p = pair.a[blockIdx.z];
+  const int blk = blockIdx.y, x0 = blockIdx.x * kDvTile;
+  if (blk * k >= p.out_n || x0 >= p.out_d) return;  // whole workgroup
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, q = lane >> 4;
+  const BufferDesc vdesc = make_buffer(p.V + (size_t)blk * k * p.d, (size_t)k * p.d * sizeof(float));
+#pragma unroll
+  for (int it = 0; it < k * kDvTile / 256; ++it) {
+    const int idx = tid + it * 256, j = idx / kDvTile, x = x0 + idx % kDvTile;
+    Vs[j * LDX + idx % kDvTile] = buffer_load<1>(vdesc, x < p.d ? (unsigned)(j * p.d + x) * 4u : kOob, 0).e[0];
+  }
+  // the parts one after the other, all of a part's entries in flight
+  float z[k * k / 256];
+  f32x4 sum[RT];
+  const size_t nd = (size_t)p.out_n * p.out_d;
+  const int x = x0 + wave * 16 + li;
+  auto at = [&](int r, int jj) {
+    const int row = blk * k + 16 * r + 4 * q + jj;
+    return row < p.out_n && x < p.out_d ? (unsigned)(row * p.out_d + x) * 4u : kOob;
+  };
+#pragma unroll
+  for (int it = 0; it < k * k / 256; ++it) z[it] = 0.f;
+#pragma unroll
+  for (int r = 0; r < RT; ++r) sum[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int part = 0; part < p.msplit; ++part) {
+    const BufferDesc zdesc = make_buffer(p.Z + ((size_t)part * p.n + (size_t)blk * k) * k, (size_t)k * k * sizeof(float));
+    const BufferDesc pdesc = make_buffer(p.dVpart + (size_t)part * nd, nd * sizeof(float));
+    float zp[k * k / 256], sp[RT][4];
+#pragma unroll
+    for (int it = 0; it < k * k / 256; ++it) {
+      const int idx = tid + it * 256, r = idx / k, c = idx % k;
+      zp[it] = buffer_load<1>(zdesc, (unsigned)((p.transpose ? r >= c : r <= c) ? idx : c * k + r) * 4u, 0).e[0];
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) sp[r][jj] = buffer_load<1>(pdesc, at(r, jj), 0).e[0];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int it = 0; it < k * k / 256; ++it) z[it] += zp[it];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) sum[r][jj] += sp[r][jj];
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < k * k / 256; ++it) Es[(tid + it * 256) / k * LDE + (tid + it * 256) % k] = z[it];
+  __syncthreads();
+  const BufferDesc odesc = make_buffer(p.dV, nd * sizeof(float));
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    sum[r] += tile_mma_rows<k>(Es + r * 16 * LDE, LDE, Vs + wave * 16, LDX, f32x4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      BufVec<1> v;
+      v.e[0] = sum[r][jj];
+      if (p.accumulate) v.e[0] += buffer_load<1>(odesc, at(r, jj), 0).e[0];
+      buffer_store<1>(odesc, at(r, jj), 0, v);
+    }
+  }
+}
+
 // dV = sum of the mini-batch parts (fixed order), for up to two products: blockIdx.y picks the product.
 __global__ void __launch_bounds__(256) dv_sum_kernel(DvPair pair) {
   const DvArgs p = pair.a[blockIdx.y];
