@@ -205,14 +205,24 @@ static bool factor_is_fused(int kp, int d) { return kp <= 32 || (kp == 64 && d <
 #define FASTH_GRAM_SPLIT_128 8
 #endif
 // The result does not depend on how consecutive reflections are grouped into blocks (Eq. 2 holds for any grouping), so
-// the caller's block size only says where the library starts from: blocks of 32 rows for k <= 32, of 128 for k = 128, of
-// 64 otherwise, which are what the fast kernels are written for. The last block is filled up with zero rows, and vectors
-// whose length is not a multiple of 4 with zeros, in a copy of V that the factor kernels write as they fetch the rows.
-// Without it such shapes ran on the general kernels (short steps, rows that are not 16-byte aligned, no matrix cores).
+// the library takes the grouping that costs least, whatever the caller's block size. The last block is filled up with zero
+// rows, and vectors whose length is not a multiple of 4 with zeros, in a copy of V that the factor kernels write as they fetch
+// the rows. Without it such shapes ran on the general kernels (short steps, rows that are not 16-byte aligned, no matrix cores).
 // Forward + backward before and after, us: d = n = 784, k = 28, m = 32: 90.7 -> 71.6, m = 200: 103.9 -> 93.7;
 // d = n = 1000, k = 50, m = 32: 156 -> 82, m = 600: 569 -> 225, m = 2000: 1534 -> 542; d = n = 1023, k = 33, m = 32: 232 -> 81;
 // d = 511, n = 500, k = 25, m = 64: 76.5 -> 49.2; d = n = 2047, k = 23, m = 32: 570 -> 179; d = n = 1024, k = 16, m = 32: 121 -> 75.
-static int inner_block(int k) { return k <= 32 ? 32 : k == kMaxBlock ? kMaxBlock : 64; }
+// Blocks of 32 rows have the cheapest factors and the smallest product E V_i; the chain kernels take 32, 64 or 128 rows per step
+// whatever the block. Blocks of 64 save half as many inputs, which pays once the two chains' saved inputs are well beyond
+// the 256 MB of the memory-side cache, and are what dv_trio_kernel takes. us per forward + backward with blocks of 32, 64 and 128
+// rows: d = n = 128, m = 100: 25, 37, 67; d = n = 512, m = 64: 46, 59, -; m = 300: 72, 88, -; d = n = 1024, m = 32: 72, 73, 86; m = 200:
+// 122, 132, 174; d = n = 2048, m = 64: 184, 185, 208; m = 440 (231 MB of saved inputs per chain): 809, 779, -; d = n = 2560, m = 200
+// (164 MB): 705, 727, -; d = n = 3072, m = 130 (153 MB): 861, 877, -; m = 200 (236 MB): 1064, 923, -.
+// A caller's larger blocks become blocks of 64 for vectors of more than 1536 elements: d = n = 2048, m = 64, inputs and workspace new to
+// the caches in each pass: 189.7 us with blocks of 32, 184.6 with 64 (alike when repeated on the same ones).
+constexpr double kManySavedBytes = 2e8;
+static int inner_block(int d, int n, int m, int k) {
+  return (d > 1536 && k > 32) || 4.0 * ((n + 31) / 32) * m * d >= kManySavedBytes ? 64 : 32;
+}
 static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multiple * multiple; }
 
 // shared = false: the layout without any kernel in which workgroups share columns (no hand-off area) and without the
@@ -231,7 +241,7 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
     L.np = padded_rows(n, 64);
   } else if (shared && d <= kMaxPaddedD) {
     L.dp = (d + 3) & ~3;
-    L.ki = inner_block(k);
+    L.ki = inner_block(L.dp, n, m, k);
     // dv_trio_kernel takes 64 rows; blocks of 32 would save twice as many inputs, and the chain kernels for so many columns
     // take 64 rows per step whatever the block
     if (dv_trio_serves(L.dp, n, m, 64)) L.ki = 64;
