@@ -66,3 +66,20 @@ def test_wide_magnitudes():
     err = np.linalg.norm((A - A0) / scale, axis=0) / np.linalg.norm(A0 / scale, axis=0)
     # operand pieces below 2^-126 keep their place, results do not: 1e-35 is 2^10 above the smallest normal number
     assert err.max() <= 1e-4, (err.argmax(), err.max())
+
+
+@pytest.mark.parametrize("d,n,m,k", [(250, 128, 1100, 32), (600, 130, 1040, 13), (1024, 1024, 2048, 32)])
+def test_wide_static_forward(d, n, m, k):
+    """The entry point that allocates nothing: with the operands in its array, and (the last shape) without room for them."""
+    import torch
+    from helpers import to_gpu
+    from paper_2009_13977_amd import binding as B
+    print(f"wide static d={d} n={n} m={m} k={k}", flush=True)
+    p = synthetic.householder_problem(d, n, m, seed=35000 + d)
+    V, X = to_gpu(p["V"]), to_gpu(p["X"])
+    A = torch.full_like(X, float("nan"))
+    for _ in range(2):
+        B.fasth_forward_static(V, X, A, k)
+        torch.cuda.synchronize()
+        assert B.fasth_wait_status() == B.FASTH_OK
+        assert_close(A.cpu().numpy(), orc.product_apply(p["V"], p["X"]), "A")
