@@ -275,10 +275,10 @@ static int launch_dv(const DvPair& pair, int count, int kp, bool vec4, hipStream
   const dim3 grid(xt, nb, count * msplit);
   // Many columns and blocks of 64 rows or more: Z of every block once, by a launch of its own (measured at
   // d = n = 1024, m = 4096: dV 374 -> 326 us at k = 64, 853 -> 545 us at k = 128, but 294 -> 309 us at k = 32, where
-  // the rebuild is a fifth of the work). Same condition for both products of a pair: they share m and k.
-  // A split mini-batch needs it too: no workgroup sees all columns.
-  const bool z_fits = (size_t)a0.m * a0.n * sizeof(float) < kOob && a0.Z != nullptr &&
-                      (count == 1 || (pair.a[1].m == a0.m && pair.a[1].k == a0.k && pair.a[1].Z != nullptr));
+  // the rebuild is a fifth of the work). Same condition for both products of a pair: run_dv_pair joins only products
+  // that share m and the library's k. A split mini-batch needs it too: no workgroup sees all columns.
+  auto z_addressable = [](const DvArgs& a) { return (size_t)a.m * a.n * sizeof(float) < kOob && a.Z != nullptr; };
+  const bool z_fits = z_addressable(a0) && (count == 1 || z_addressable(pair.a[1]));
   if (msplit > 1 && !z_fits) return FASTH_EINVAL;  // dv_minibatch_split never chooses a split for such a shape
   const bool prez = z_fits && (msplit > 1 || (a0.k >= 64 && (size_t)a0.m * a0.k >= 32768));
   static const std::string names[16] = {
@@ -333,10 +333,11 @@ static int run_dv(const Product& P, const float* V, float* dV, int transpose, hi
 }
 
 // dV of two products with different outputs in one launch when both take the same template
-// arguments; otherwise one after the other.
+// arguments and the same rows per block (a product of vectors beyond kMaxPaddedD elements keeps the caller's block size,
+// its partner does not); otherwise one after the other.
 static int run_dv_pair(const Product& P0, const float* V0, float* dV0, int transpose0, const Product& P1,
                        const float* V1, float* dV1, int transpose1, hipStream_t stream) {
-  if (P0.L.kp == P1.L.kp && (P0.L.dp % 4 == 0) == (P1.L.dp % 4 == 0) && P0.L.dv_split == P1.L.dv_split && P0.L.dv_trio == P1.L.dv_trio) {
+  if (P0.L.ki == P1.L.ki && P0.L.kp == P1.L.kp && (P0.L.dp % 4 == 0) == (P1.L.dp % 4 == 0) && P0.L.dv_split == P1.L.dv_split && P0.L.dv_trio == P1.L.dv_trio) {
     DvPair pair;
     pair.a[0] = dv_args(P0, V0, dV0, transpose0, false);
     pair.a[1] = dv_args(P1, V1, dV1, transpose1, false);
