@@ -57,6 +57,9 @@ struct Product {  // one Householder product bound to its slice of a workspace
   int d, n, m, k;
   Layout L;
   char* ws;
+  // Calls on this workspace never overlap on the GPU: they save into it, or the header says so for the shape. Cleared by
+  // fasth_apply without saving, whose calls may overlap except for the header's list of shapes.
+  bool exclusive = true;
   // the rows the kernels read: the caller's, or the padded copy the factor kernels leave in the workspace
   const float* rows(const float* V) const { return L.copy_v ? reinterpret_cast<const float*>(ws + L.off_V) : V; }
   float* copy() const { return L.copy_v ? reinterpret_cast<float*>(ws + L.off_V) : nullptr; }
@@ -214,7 +217,9 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   const Product& F = factors ? *factors : P;
   ChainArgs a;
   a.V = F.rows(V); a.T = F.T(); a.in = in; a.out = out;
-  a.xch = F.xch(); a.wait_limit = wait_limit(); a.parts = 0;
+  // wide mini-batches: calls that may overlap on one workspace cannot hand sums over through it
+  a.xch = F.L.trio.parts && !P.exclusive ? nullptr : F.xch();
+  a.wait_limit = wait_limit(); a.parts = 0;
   a.S = reinterpret_cast<const float*>(F.ws + F.L.off_S);
   a.Tt = a.T + (size_t)F.L.nbf * F.L.kpf * F.L.kpf;
   a.save_in = !save ? nullptr : activation ? P.saveA() : P.saveG();
@@ -669,8 +674,9 @@ int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float*
   if (rc != FASTH_OK) return rc;
   if (!V || !X || !A || !workspace) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(X) || !aligned16(A) || !aligned16(workspace)) return FASTH_EALIGN;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
+  Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
   if (workspace_bytes < P.L.total) return FASTH_EWORKSPACE;
+  P.exclusive = save_for_backward != 0;
   return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, static_cast<hipStream_t>(stream),
                    save_for_backward != 0);
 }

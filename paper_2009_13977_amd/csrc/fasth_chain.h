@@ -533,13 +533,13 @@ namespace fasth {
 
 // chain_pipe_kernel serves every d up to 4096; it also takes the side product along.
 static bool chain_uses_pipe(const ChainArgs& a) {
-  return !chain_uses_tile(a) && !chain_uses_quad(a) && !chain_uses_team_tile(a) && !chain_uses_team_wide(a) && !chain_uses_team(a) && !chain_uses_split_pair(a) && a.d <= 4096;
+  return !chain_uses_trio(a) && !chain_uses_tile(a) && !chain_uses_quad(a) && !chain_uses_team_tile(a) && !chain_uses_team_wide(a) && !chain_uses_team(a) && !chain_uses_split_pair(a) && a.d <= 4096;
 }
-static bool chain_takes_side_product(const ChainArgs& a) { return a.frag || chain_uses_pipe(a) || chain_uses_team(a) || chain_uses_team_wide(a) || chain_uses_team_tile(a); }
+static bool chain_takes_side_product(const ChainArgs& a) { return chain_uses_trio(a) || chain_uses_pipe(a) || chain_uses_team(a) || chain_uses_team_wide(a) || chain_uses_team_tile(a); }
 
 static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
   const int d = a.d, k = a.k;
-  if (a.frag) return launch_chain_trio(a, stream);
+  if (chain_uses_trio(a)) return launch_chain_trio(a, stream);
   if (chain_uses_team_tile(a)) return launch_chain_team_tile(a, stream);
   if (chain_uses_tile(a)) return launch_chain_tile(a, stream);
   if (chain_uses_quad(a)) return launch_chain_quad(a, stream);

@@ -444,9 +444,16 @@ __global__ void __launch_bounds__(512) chain_trio_kernel(ChainArgs p) {
   }
 }
 
+// No hand-off area: the call may overlap with others on its workspace.
+static TrioPlan chain_trio_plan(const ChainArgs& a) {
+  if (!a.frag) return TrioPlan{0, 0, 0};
+  return a.xch ? trio_plan(a.d, a.n, a.m) : trio_solo_plan(a.d, a.n, a.m);
+}
+static bool chain_uses_trio(const ChainArgs& a) { return chain_trio_plan(a).parts > 0; }
+
 static int launch_chain_trio(const ChainArgs& args, hipStream_t stream) {
   ChainArgs a = args;
-  const TrioPlan plan = trio_plan(a.d, a.n, a.m);
+  const TrioPlan plan = chain_trio_plan(a);
   if (plan.parts == 0 || a.k % 64 != 0 || a.n % 64 != 0 || (plan.parts > 1 && !a.xch)) return FASTH_EINVAL;
   a.parts = plan.parts;
   a.sub = a.k / 64;
@@ -468,6 +475,7 @@ static int launch_chain_trio(const ChainArgs& args, hipStream_t stream) {
   else if (plan.xt == 4 && plan.ct == 1) FASTH_LAUNCH_TRIO(4, 1, true);
   else if (plan.xt == 4 && !team) FASTH_LAUNCH_TRIO(4, 2, false);
   else if (plan.xt == 4) FASTH_LAUNCH_TRIO(4, 2, true);
+  else if (plan.ct == 1) FASTH_LAUNCH_TRIO(8, 1, false);
   else if (!team) FASTH_LAUNCH_TRIO(8, 2, false);
   else FASTH_LAUNCH_TRIO(8, 2, true);
 #undef FASTH_LAUNCH_TRIO

@@ -155,6 +155,15 @@ static TrioPlan trio_plan(int d, int n, int m) {
   if (team_fits(wide, np4)) return TrioPlan{4, 2, np4};
   return d <= 1024 || team_fits(wide, np8) ? TrioPlan{8, 2, np8} : TrioPlan{0, 0, 0};
 }
+// The same operands without teams, for calls that may overlap on one workspace: 1024 elements in one workgroup (at most 4096
+// columns: a team served them), beyond that chain_tile_kernel. us per fasth_apply, nothing saved, chain_tile_kernel, this and teams:
+// d = n = 1024: m = 1100: 174, 130, 94; m = 2048: 175, 128, 97; m = 4096: 178, 139, 120; d = n = 1536, m = 2048: 364, -, 177
+// (256 elements per wave need more registers than there are).
+static TrioPlan trio_solo_plan(int d, int n, int m) {
+  const TrioPlan plan = trio_plan(d, n, m);
+  if (plan.parts <= 1) return plan;
+  return d <= 1024 ? TrioPlan{8, 1, 1} : TrioPlan{0, 0, 0};
+}
 
 // dv_trio_kernel: blocks of 64 rows, from 449 columns on and once the products are worth its longer start (us per forward +
 // backward with it and without: d = n = 512, m = 512: 100, 88; d = n = 512, m = 800: 141, 135; d = n = 1024, m = 420: 193, 189;
