@@ -12,7 +12,7 @@ namespace fasth {
 // The fp32 matrix instructions of this GPU run at 157 TFLOP/s, the bf16 ones at 2.5 PFLOP/s with fp32 accumulation. An
 // fp32 number is the sum of three bf16 numbers (device helper split8), and a product of two such sums without its three
 // smallest terms is six bf16 products: 2.4 times the fp32 rate measured (2.0 PFLOP/s / 6 against 146 TFLOP/s).
-// The leading products h h accumulate by themselves, the five others, at most 2^-7 of them, in a second accumulator,
+// The leading products h h accumulate by themselves, the five others, together about 2^-7 of them at most, in a second accumulator,
 // and the two are added once at the end: a sum then has one rounding of full size per 32 terms where the fp32
 // instruction has one per 4, and its error is SMALLER (2-norm against fp64, normal operands: 64 terms 5.5e-8 against
 // 8.4e-8, 256 terms 9.1e-8 against 1.5e-7, 1024 terms 1.9e-7 against 2.9e-7; all six in one accumulator: 4.9e-7).
@@ -41,6 +41,7 @@ namespace fasth {
 // ------------------------------------------------------------------------------------------
 constexpr int kTrioOperand = 1024;                      // bytes of one operand
 constexpr int kTrioCell = 24 * kTrioOperand;            // bytes per 64 rows x 32 elements
+constexpr int kTrioTicketWord = 32;                     // of a tile's head, on a line of its own: the starting order of an XCD's workgroups
 
 struct TrioRowsArgs {
   const float* V;   // [n][d], the caller's
@@ -102,16 +103,31 @@ __global__ void __launch_bounds__(512) chain_trio_kernel(ChainArgs p) {
   const int q = lane >> 4, i = lane & 15;
   const int m = p.m, d = p.d, n = p.n;
   const int tiles = (m + COLS - 1) / COLS;
-  // workgroups b, b + 8, ... (one XCD) are the parts of tile 8 (b / (8 NP)) + b % 8
   const int chain_wgs = TEAM ? 8 * NP * ((tiles + 7) / 8) : tiles;
   if ((int)blockIdx.x >= chain_wgs) {  // the side product, on compute units the chain leaves idle
     const int row = ((int)blockIdx.x - chain_wgs) * 8 + wave;
     if (row < p.ds_rows) dsigma_row(p.in, p.ds_z1, p.in_scale, p.ds_out, row, m, p.in_scale_mode);
     return;
   }
-  const int part = TEAM ? (int)(blockIdx.x >> 3) % NP : 0;
-  const int tile = TEAM ? (int)(blockIdx.x >> 3) / NP * 8 + (int)(blockIdx.x & 7) : (int)blockIdx.x;
-  if (tile >= tiles) return;
+  int part = 0, tile = (int)blockIdx.x;
+  if constexpr (TEAM) {
+    // Workgroups b, b + 8, ... (one XCD) share out the teams of tiles b % 8, b % 8 + 8, ... in the order in which they START:
+    // the next ticket is the next part of the next tile. So only the youngest team of an XCD can lack a part, whatever else runs
+    // on the GPU: all others are complete, end, and make room for its missing parts. Whoever draws the last ticket puts
+    // the counter back for the next launch (one counter per XCD, in the heads of the first eight tiles).
+    __shared__ unsigned ticket;
+    const unsigned group = blockIdx.x & 7u;
+    if (tid == 0) {
+      unsigned* counter = p.xch + (size_t)group * trio_words(NP, CT) + kTrioTicketWord;
+      ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (ticket == (unsigned)chain_wgs / 8u - 1u) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    const int drawn = __builtin_amdgcn_readfirstlane((int)ticket);
+    part = drawn % NP;
+    tile = drawn / NP * 8 + (int)group;
+    if ((unsigned)tile >= (unsigned)tiles) return;
+  }
   const int col0 = tile * COLS + i;  // column tile ct: col0 + 16 ct
   const int x_w = (part * 8 + wave) * XW;  // this wave's first element
   auto x_of = [&](int t, int jj) { return x_w + 32 * (t >> 1) + 8 * q + 4 * (t & 1) + jj; };
@@ -201,12 +217,14 @@ __global__ void __launch_bounds__(512) chain_trio_kernel(ChainArgs p) {
     }
     unsigned peer_xcc = my_xcc;
     const unsigned hs_from = 32u + (unsigned)(lane < NP ? lane : part) * 8u;
-    int polls = 0;
+    // a part that has not started waits for a compute unit, for which kernels of other streams may take their time
+    const long long start_limit = 64ll * p.wait_limit;
+    long long polls = 0;
     for (;;) {
       const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(hdesc, hs_from, 0, 16);
       peer_xcc = w.x;
       if (__all(w.y == hs_tag)) break;
-      if (polls++ >= p.wait_limit) { gave_up = true; break; }
+      if (polls++ >= start_limit) { gave_up = true; break; }
       asm volatile("" ::: "memory");
     }
     same_xcd = !gave_up && __all(peer_xcc == my_xcc);
