@@ -260,9 +260,13 @@ __device__ __forceinline__ constexpr int reduce_writer_mask() {
 }
 
 // ---- fp32 operands as three bf16 pieces ---------------------------------------------------
-// x = h + m + l up to 2^-25 of x: h is x cut off after 8 significant bits (cut, not rounded, so that it cannot
-// overflow), m and l round what is left, so the three products that are left out of six (m l, l m, l l) are
-// at most 2^-24 of a product and of either sign. Inf becomes NaN.
+// x = h + m + l exactly (down to 2^-133): h is x rounded to 8 significant bits, m and l round what is left, so that |m| <= 2^-8 |x|
+// and |l| <= 2^-17 |x|. Of the nine products of two such sums the three smallest are left out (m l, l m, l l): together at most
+// 2^-24 of the product of two numbers and of either sign (2^-24.2 found over 4 million pairs in [1, 2), rms 2^-27.5: the
+// rounding of an fp32 product is 2^-24, rms 2^-25.2). Cutting h off instead would leave pieces twice and four times as large
+// (2^-22, rms 2^-25.5), which sums of a few terms do show. Only numbers beyond the largest bf16 (3.39e38) are cut to it, as rounding would
+// make them infinite. An infinite x becomes NaN, and NaN stays NaN: B = V A of a column with either has no finite entry, the zeros
+// of the triangular factor make C = op(T) B NaN throughout, and so the column, in fp32 arithmetic too.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -274,9 +278,9 @@ __device__ __forceinline__ unsigned round_bf16_pair(float x0, float x1) {
 }
 // Two numbers; a piece's low half belongs to x0.
 __device__ __forceinline__ void split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
-  const unsigned u0 = __float_as_uint(x0) & 0xffff0000u, u1 = __float_as_uint(x1) & 0xffff0000u;
-  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-  const float r0 = x0 - __uint_as_float(u0), r1 = x1 - __uint_as_float(u1);
+  const float largest = __uint_as_float(0x7f7f0000u);
+  h = round_bf16_pair(__builtin_amdgcn_fmed3f(x0, -largest, largest), __builtin_amdgcn_fmed3f(x1, -largest, largest));
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
   m = round_bf16_pair(r0, r1);
   l = round_bf16_pair(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
