@@ -51,8 +51,9 @@ enum {
  * 1 <= k <= 128 and k divides n (the paper assumes the block size divides
  * the number of reflections, Section 3.1). n need not equal d. The result does
  * not depend on k beyond rounding (Eq. 2 holds for any grouping of consecutive
- * reflections), and for d <= 4096 the library regroups them into blocks of 32 or
- * 64 whatever k, padding the last one. */
+ * reflections), and for d <= 4096 the library regroups them into blocks of its
+ * own, 32 or 64 rows (8, 16 or 24 for few reflections in small blocks, k < 32),
+ * padding the last one. */
 typedef struct fasth_shape {
   int d;          /* length of each Householder vector = rows of X */
   int n;          /* number of reflections = rows of V */

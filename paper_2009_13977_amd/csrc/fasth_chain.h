@@ -599,8 +599,22 @@ static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
         if (k == 64) return launch_chain_pipe<16, 4, 512, 4, 4, false, 4, false, 1>(a, stream);
         return launch_chain_pipe<16, 4, 512, 4, 8, false, 4, false, 1>(a, stream);
       }
-      return launch_chain_pipe<8, 4, 1024, 2, 0, false, 1, false, 1>(a, stream);
     }
+    // Few reflections (blocks of 8 or 16 rows): two copies of a whole block in registers, a quarter of the next block fetched during
+    // the reduction; narrower lanes for short vectors keep all four waves busy
+    if (d % 4 == 0 && k == 16) {
+      if (d <= 256) return launch_chain_pipe<16, 1, 256, 4, 1, false, 4, false, 1>(a, stream);
+      if (d <= 512) return launch_chain_pipe<16, 2, 256, 4, 1, false, 4, false, 1>(a, stream);
+      if (d <= 1024) return launch_chain_pipe<16, 4, 256, 4, 1, false, 4, false, 1>(a, stream);
+      if (d <= 2048) return launch_chain_pipe<16, 4, 512, 4, 1, false, 4, false, 1>(a, stream);
+    }
+    if (d % 4 == 0 && k == 8) {
+      if (d <= 256) return launch_chain_pipe<8, 1, 256, 2>(a, stream);
+      if (d <= 512) return launch_chain_pipe<8, 2, 256, 2>(a, stream);
+      if (d <= 1024) return launch_chain_pipe<8, 4, 256, 2, 1, false, 1, false, 1>(a, stream);
+      if (d <= 2048) return launch_chain_pipe<8, 4, 512, 2, 1, false, 1, false, 1>(a, stream);
+    }
+    if (d % 4 == 0 && k % 8 == 0 && d > 2048) return launch_chain_pipe<8, 4, 1024, 2, 0, false, 1, false, 1>(a, stream);
     // Rows as the caller has them, any length and any block size: only where fasth_forward_static has no room for the
     // padded copy of V.
     if (d <= 1024) {

@@ -137,23 +137,30 @@ static int team_tile_parts(int d, int n, int m, int k) {
 
 // chain_trio_kernel: tiles of 16 ct columns on the bf16 matrix cores at fp32 precision, each shared by `parts` workgroups
 // of 128 xt elements, for more than 1024 columns, or 2048 where chain_team_tile_kernel with its shorter parts serves and is
-// as fast (us, nothing saved: d = 1024, m = 1024: 74 against 76; forward + backward: d = 512, m = 2000: 152 against 157), and two
-// steps or more (d = 1024, n = 64, m = 2000: 76 us without against 83). Every workgroup of a team needs a compute unit on the
+// as fast (us, nothing saved: d = 1024, m = 1024: 74 against 76; forward + backward: d = 512, m = 2000: 152 against 157). Every workgroup of a team needs a compute unit on the
 // team's XCD. Short parts and narrow tiles have the least to do per step (us per forward + backward, k = 32, {xt, ct}):
 // d = 512, m = 4096: {4, 1} 179, {4, 2} 205; d = 1024, m = 2048: {4, 1} 324, {4, 2} 376; but 16 columns of 1024 elements keep the
 // matrix cores waiting for V: d = 1024, m = 4096: {4, 2} 647, {8, 1} 699, {8, 2} 833; d = 2048, m = 2048: {4, 2} 1242,
 // {8, 1} 1272, {8, 2} 1506.
 // Before (chain_tile_kernel, dv_kernel), us per forward + backward: d = 256, m = 4096: 118 -> 101; d = 512, m = 4096: 311 -> 184;
 // d = 1024, m = 1100: 481 -> 271, 2048: 574 -> 324, 4096: 751 -> 555; d = 2048, m = 1100: 1782 -> 935, 4096: 2651 -> 1995.
+// Few steps do not pay for the operands of V, and rounding n up to whole steps weighs more: us per forward + backward without and
+// with, d = 256, m = 1500: n = 96: 63, 69; n = 128: 71, 68; d = 640, m = 3000: n = 96: 80, 98; n = 128: 98, 105; n = 192: 136, 132;
+// d = 1024, m = 3000: n = 96: 91, 102; n = 112: 108, 103; d = 1280, m = 1500: n = 80: 89, 89; n = 112: 109, 90; with 1024 elements per
+// workgroup ({8, 2}): d = 1536, m = 4096: n = 128: 180, 222; n = 192: 242, 254; n = 256: 303, 280; d = 2048: n = 128: 215, 242.
+// Up to 1280 columns of 513 to 768 elements chain_team_tile_kernel's three shorter parts serve: d = 640, m = 1100, n = 512: 138 against 159.
 constexpr int kTrioMaxD = 2048;
 constexpr unsigned trio_words(int np, int ct) { return (unsigned)(kTeamHeadBytes + np * 2 * np * 512 * 16 * ct) / 4u; }
 static TrioPlan trio_plan(int d, int n, int m) {
-  if (m <= (d > 256 && d <= 512 ? 2048 : 1024) || d > kTrioMaxD || n <= 64) return TrioPlan{0, 0, 0};
+  const TrioPlan none{0, 0, 0};
+  if (m <= (d > 256 && d <= 512 ? 2048 : d > 512 && d <= 768 ? 1280 : 1024) || d > kTrioMaxD) return none;
+  if (n <= (d <= 512 ? (m > 2048 ? 96 : 112) : d <= 768 && m > 2048 ? 160 : d <= 1024 ? 96 : 64)) return none;
   const int narrow = (m + 15) / 16, wide = (m + 31) / 32, np4 = (d + 511) / 512, np8 = (d + 1023) / 1024;
   if (d <= 512) return TrioPlan{d <= 256 ? 2 : 4, narrow <= kComputeUnits ? 1 : 2, 1};
   if (team_fits(narrow, np4)) return TrioPlan{4, 1, np4};
   if (team_fits(wide, np4)) return TrioPlan{4, 2, np4};
-  return d <= 1024 || team_fits(wide, np8) ? TrioPlan{8, 2, np8} : TrioPlan{0, 0, 0};
+  if (d <= 1024) return TrioPlan{8, 2, 1};
+  return n > 192 && team_fits(wide, np8) ? TrioPlan{8, 2, np8} : none;
 }
 // The same operands without teams, for calls that may overlap on one workspace: 1024 elements in one workgroup (at most 4096
 // columns: a team served them), beyond that chain_tile_kernel. us per fasth_apply, nothing saved, chain_tile_kernel, this and teams:
@@ -228,11 +235,78 @@ static bool factor_is_fused(int kp, int d) { return kp <= 32 || (kp == 64 && d <
 // (164 MB): 705, 727, -; d = n = 3072, m = 130 (153 MB): 861, 877, -; m = 200 (236 MB): 1064, 923, -.
 // A caller's larger blocks become blocks of 64 for vectors of more than 1536 elements: d = n = 2048, m = 64, inputs and workspace new to
 // the caches in each pass: 189.7 us with blocks of 32, 184.6 with 64 (alike when repeated on the same ones).
-constexpr double kManySavedBytes = 2e8;
-static int inner_block(int d, int n, int m, int k) {
-  return (d > 1536 && k > 32) || 4.0 * ((n + 31) / 32) * m * d >= kManySavedBytes ? 64 : 32;
-}
+// From 897 columns on, where the chains run on the matrix cores and hardly wait, half the saved inputs pay from 25 MB per chain on: blocks
+// of 32 and 64, d = 1024, m = 1000: n = 192 (25 MB): 94, 92; n = 256: 114, 107; d = 512, m = 1500: n = 384 (37 MB): 126, 122; n = 512:
+// 156, 140; d = 2048, m = 1000: n = 128 (33 MB): 142, 132; but m = 800: d = 512, n = 768: 173, 187; d = 640, n = 576: 135, 142.
+// Never where rounding n up to 64 adds a step of 32 that matters: d = 2048, m = 4096, n = 32: 114, 140; d = 3072, m = 800, n = 160: 281, 309;
+// n = 288: 416, 437; it matters least on the matrix cores: d = 2048, m = 1000, n = 288: 200, 173; m = 4096, n = 160: 311, 286.
+constexpr double kManySavedBytes = 2e8, kManySavedBytesTiles = 2.5e7;
 static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multiple * multiple; }
+static bool fills_64(int d, int n, int m) {
+  return n > 320 || padded_rows(n, 64) == padded_rows(n, 32) || (d <= 2048 && (m > 2048 ? n > 128 : m > 896 ? n > 192 : m > 768 && n > 256));
+}
+static int inner_block(int d, int n, int m, int k) {
+  const double saved = 4.0 * ((n + 31) / 32) * m * d;
+  return fills_64(d, n, m) && ((d > 1536 && k > 32) || saved >= (m > 896 ? kManySavedBytesTiles : kManySavedBytes)) ? 64 : 32;
+}
+
+// Few reflections in small blocks (the caller's k < 32): blocks of 16 rows, whose factors cost least, and steps of 16 rows on the kernels
+// for one column per workgroup and on chain_tile_kernel, without hand-overs and with the least padding. How many are few depends on
+// what serves otherwise. us per forward + backward with blocks of 16 and with the best other choice, d: m: (n: blocks of 16, other):
+// 256: 128: (112: 24, 26), (160: 27.5, 27.7); 300: (160: 38, 39), (192: 41, 41); 1000: (112: 49.5, 50), (128: 51, 50); 1500: (112: 65, 69)
+// 512: 128: (128: 29, 30), (160: 31, 31); 600: (112: 56, 59), (128: 61, 58); 1500: (64: 59, 83), (128: 77, 86), (160: 89, 84)
+// 1024: 32: (128: 29, 31), (192: 35, 37), (224: 38, 37); 300: (128: 51, 58), (320: 79, 82); 600: (80: 62, 67), (112: 69, 67);
+//       1000: (48: 69, 70), (64: 76, 71); 1500: (48: 73, 81), (64: 84, 81)
+// 1280: 64: (160: 38, 43), (192: 44, 43); 100: (192: 48, 51); 1100: (64: 88, 103)
+// 2048: 32: (112: 36, 37), (128: 38, 35); 300: (224: 119, 122), (256: 132, 132); 1000: (32: 115, 131), (48: 129, 132), (64: 145, 131)
+// 4096: 32: (16: 32, 35), (24: 41, 38); 128: (256: 128, 131); 300: (192: 201, 203); 600: (128: 237, 239); 1500: (48: 361, 419), (64: 409, 382)
+// Short columns and few of them: a launch each whatever the blocks, and fewer steps with 32 rows (d = 64, m = 32, n = 64: 21.5, 20).
+constexpr int kFewRows = 16;
+static bool few_reflections(int d, int n, int m) {
+  if (d <= 256 && m <= 128) return false;
+  if (d <= 256 && m <= 2048) return n <= (m <= 512 ? 160 : 112);
+  if (d <= 512) return m > 2048 ? n <= 48 || (n > 64 && n <= 80) : n <= (m <= 256 || m > 896 ? 128 : 112);
+  if (m > 2048) return n <= 16 || (n > 32 && n <= 48 && d <= 1536);  // 48: a third of the second 32 would be padding
+  if (m > 1024 && d > 2048) return n <= 16 || (n > 32 && n <= 48);
+  if (m > 1024) return n <= (m > 1280 || d > 1536 ? 48 : d <= 768 ? 80 : d <= 1024 ? 48 : 64);
+  if (d <= 1024) return n <= (m <= 256 ? 192 : m <= 480 ? 576 : m <= 768 ? 96 : d <= 896 ? 80 : 48);
+  if (d <= 2048) return n <= (m <= 64 ? (d <= 1536 ? 160 : 112) : m <= 128 ? (d <= 1536 ? 192 : 128) : m < 640 ? 256 : 48);
+  if (team_fits(m, (d + kTeamSlice - 1) / kTeamSlice)) return n <= (d <= 3072 ? 32 : 16);
+  return n <= (m <= 256 ? 256 : m <= 512 ? 192 : 112);
+}
+// Blocks of 8 rows (the caller's k <= 8) where a sixth or more of the blocks of 16 would be padding, and where steps of 8 rows keep twice as
+// many workgroups on a compute unit: us with blocks of 8 and of 16: d = 1024, m = 800: n = 8: 49, 54; n = 24: 56, 61; d = 2048, m = 32:
+// n = 24: 23, 26; m = 449: n = 8: 50, 59; n = 64: 71, 77; n = 128: 98, 98; d = 1280, m = 300: n = 64: 49, 54; n = 160: 71, 75;
+// d = 64, m = 1100: n = 64: 35, 46 (tiles); n = 128: 44, 60; d = 256, m = 1100: n = 96: 55, 57.
+static bool fewest_rows(int d, int n, int m) {
+  if ((n - 1) % 16 < 8) {
+    if (d > 2048) return n <= (m > 1024 ? 8 : team_fits(m, (d + kTeamSlice - 1) / kTeamSlice) ? 24 : 72);
+    if (n <= 40) return m <= 1024 || (d <= 256 && m <= 1280);
+  }
+  if (d > 1024 && d <= 2048 && m > 256 && m <= 1024) return n <= (m > 480 ? 48 : d <= 1280 ? 360 : d <= 1536 ? 160 : 120);
+  return d <= 256 && m > 1024 && (d <= 128 ? m <= 1536 && n <= 256 : m <= 1280 && n <= 128);
+}
+// Vectors of more than 2048 elements take steps of 8 rows, so blocks of 24 save padding: us with blocks of 24 and of 16 or 32: d = 3072,
+// m = 300: n = 24: 80, 86; n = 72: 102, 116; n = 360: 259, 271.
+static int least_padding(int d, int n, int rows) {
+  return d > 2048 && 25 * padded_rows(n, 24) <= 24 * padded_rows(n, rows) ? 24 : rows;
+}
+
+// Rows as the kernels see them, blocks of k. The kernels in which workgroups share columns need whole steps of 64 or 128 rows, and
+// padding n up to them pays where they gain more than the padding costs. us per forward + backward without and with:
+// columns of up to 1024 elements: d = 1024, m = 32: n = 160: 33, 37; n = 288: 42, 44; n = 448: 61, 50 (128); longer columns always;
+// tiles of 16 columns: d = 512, m = 1000: n = 160: 75, 85; n = 224: 87, 92; m = 1500: n = 224: 107, 100; d = 1024, m = 449: n = 288: 71, 73;
+// m = 600: n = 160: 84, 79; m = 800: n = 96: 76, 73; d = 640, m = 800: n = 96: 62, 65; beyond 1024 elements they take
+// steps of 32, two at least: d = 2048, m = 1000: n = 32: 170, 132.
+// Steps of 128 rows take less than twice as long as steps of 64 (2.65 against 1.95 us at d = 1024) but their launch more: d = 2048,
+// m = 32: n = 192: 40 with steps of 64, 45 padded to 256; n = 320: 50, 55; n = 576: 76, 72.
+static int steps_rows(int d, int n, int m, int k) {
+  const int own = padded_rows(n, k), r64 = padded_rows(n, k < 64 ? 64 : k), r128 = padded_rows(n, kWideRows);
+  if (team_tile_parts(d, r64, m, k)) return (d > 1024 && n > 32) || n <= (d > 1024 ? 0 : d <= 512 ? (m <= 1024 ? 256 : 192) : m < 512 ? 320 : d <= 896 ? 96 : 64) ? own : r64;
+  if (d <= 1024 && (m <= 64 ? n <= 192 || (n > 256 && n <= 288) : n <= 320)) return own;
+  if (n > 448 && team_wide_parts(d, r128, m, k)) return r128;
+  return team_parts(d, r64, m, k) || team_wide_parts(d, r64, m, k) ? r64 : own;
+}
 
 // shared = false: the layout without any kernel in which workgroups share columns (no hand-off area) and without the
 // padded copy of V (the caller's own block size), for a caller whose room is limited. Vectors too long for the
@@ -243,23 +317,25 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
   const bool shared = level >= kLayoutShared;
   Layout L;
   L.dp = d; L.np = n; L.ki = k;
-  L.trio = level == kLayoutTrio ? trio_plan((d + 3) & ~3, n, m) : TrioPlan{0, 0, 0};
+  const int d4 = (d + 3) & ~3;
+  const bool fewest = k <= 8 && fewest_rows(d4, n, m);
+  L.trio = level == kLayoutTrio && !fewest ? trio_plan(d4, n, m) : TrioPlan{0, 0, 0};
   if (L.trio.parts) {
-    L.dp = (d + 3) & ~3;
+    L.dp = d4;
     L.ki = 64;
     L.np = padded_rows(n, 64);
   } else if (shared && d <= kMaxPaddedD) {
-    L.dp = (d + 3) & ~3;
-    L.ki = inner_block(L.dp, n, m, k);
+    L.dp = d4;
+    L.ki = fewest ? 8 : k < 32 && few_reflections(d4, n, m) ? kFewRows : inner_block(d4, n, m, k);
     // dv_trio_kernel takes 64 rows; blocks of 32 would save twice as many inputs, and the chain kernels for so many columns
     // take 64 rows per step whatever the block
-    if (dv_trio_serves(L.dp, n, m, 64)) L.ki = 64;
-    const int r128 = padded_rows(n, kWideRows), r64 = padded_rows(n, L.ki < 64 ? 64 : L.ki);
-    // a step of 128 rows takes less than twice as long as one of 64 (2.65 against 1.95 us at d = 1024), so only up to
-    // 64 rows are better padded to 64
-    if (n > 64 && team_wide_parts(L.dp, r128, m, L.ki)) L.np = r128;
-    else if (team_parts(L.dp, r64, m, L.ki) || team_tile_parts(L.dp, r64, m, L.ki)) L.np = r64;
-    else L.np = padded_rows(n, L.ki);
+    if (L.ki > kFewRows && fills_64(d4, n, m) && dv_trio_serves(d4, n, m, 64)) L.ki = 64;
+    L.np = L.ki <= kFewRows ? padded_rows(n, L.ki) : steps_rows(d4, n, m, L.ki);
+    // (no kernel with shared columns: those have taken whole steps)
+    if ((L.ki == kFewRows || L.ki == 32) && !team_parts(d4, L.np, m, L.ki) && least_padding(d4, n, L.ki) == 24) {
+      L.ki = 24;
+      L.np = padded_rows(n, 24);
+    }
   }
   L.copy_v = L.dp != d || L.np != n;
   d = L.dp; n = L.np; k = L.ki;

@@ -21,8 +21,8 @@ ALL_SIX = 1.2e-6
 
 
 @pytest.mark.parametrize("d,n,m,transpose", [
-    (256, 128, 1100, False), (512, 256, 2100, True), (600, 128, 5300, False),   # one workgroup per tile
-    (700, 192, 1100, True), (1000, 160, 3000, False)])                          # teams; from the third on dv_trio_kernel but for the fourth
+    (256, 128, 1100, False), (512, 256, 2100, True), (800, 128, 5300, False),   # one workgroup per tile
+    (780, 192, 1100, True), (1000, 160, 3000, False)])                          # teams; from the third on dv_trio_kernel but for the fourth
 def test_every_product_counts(d, n, m, transpose):
     print(f"split products d={d} n={n} m={m} transpose={transpose}", flush=True)
     p = synthetic.householder_problem(d, n, m, seed=71000 + d)
@@ -40,7 +40,7 @@ def test_sums_of_one_term():
     difference once, and twice the left-out part of each of the two products (rms 2^-27.5, at most 2^-24):
     rms 1.05e-7, largest 2^-24 (2 * 6 + 1) = 7.7e-7. With the leading piece cut off instead of rounded: rms 1.3e-7 measured.
     Entries that no row reaches stay as they are, also those beyond the largest bf16 number."""
-    d, n, m = 600, 128, 1040
+    d, n, m = 800, 128, 1040
     rng = np.random.default_rng(72000)
     V = np.zeros((n, d), np.float32)
     V[np.arange(n), rng.permutation(d)[:n]] = (1 + rng.random(n)) * rng.choice([-1.0, 1.0], n)
@@ -58,7 +58,7 @@ def test_sums_of_one_term():
 
 def test_columns_of_any_magnitude():
     """Away from the ends of the range every column is as exact as the others."""
-    d, n, m = 600, 128, 1040
+    d, n, m = 800, 128, 1040
     p = synthetic.householder_problem(d, n, m, seed=73000)
     scale = 10.0 ** np.linspace(-25, 25, m)
     X = (p["X"] * scale).astype(np.float32)
@@ -69,7 +69,7 @@ def test_columns_of_any_magnitude():
     assert err.max() <= ALL_SIX
 
 
-@pytest.mark.parametrize("d,n,m", [(250, 128, 1100), (600, 128, 1040), (600, 128, 5300)])
+@pytest.mark.parametrize("d,n,m", [(250, 128, 1100), (800, 128, 1040), (800, 128, 5300)])
 def test_bad_columns_stay_alone(d, n, m):
     """An infinity or NaN in X, or one in G, spoils its own column and no other."""
     import torch

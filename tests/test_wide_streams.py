@@ -10,7 +10,7 @@ from paper_2009_13977_amd import synthetic
 pytestmark = pytest.mark.gpu
 
 # two parts (16 and 32 columns per tile, the launch as large as the GPU or larger), three, two parts of 1024 elements, no team
-SHAPES = [(600, 128, 1040, 32), (1021, 200, 4097, 50), (1500, 130, 1100, 13), (2048, 128, 4096, 64), (512, 128, 2100, 32), (1030, 65, 4200, 13)]
+SHAPES = [(800, 128, 1040, 32), (1021, 200, 3000, 50), (1500, 130, 1100, 13), (2048, 193, 4096, 1), (512, 128, 2100, 32), (1030, 65, 4200, 13)]
 
 
 def _two_streams():
