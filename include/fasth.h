@@ -131,11 +131,11 @@ int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float*
  * with the block factors in a fixed array of FASTH_STATIC_SCRATCH_BYTES that is part of the library's
  * GPU code (one copy per GPU, held until the process ends) instead of a caller's workspace. Nothing is
  * saved for a backward pass. The call allocates and frees nothing; its first use on a device looks up
- * the array's address. Shapes whose factors, partial Gram matrices and hand-off words need more than the array
- * holds (about 4 n kp (2 + min(16, ceil(d / 128))) bytes, kp = k rounded up to a power of two >= 16; for the
- * shapes of fasth_wait_status's comment kp = 64 whatever k, half as much again where a step takes 128 rows, and up
- * to 129 KiB more per column: 10 MiB at d = n = 2048, m = 64, 17.5 MiB at m = 32; where that is too much the call
- * does without those kernels and needs the first figure only) return FASTH_EUNSUPPORTED before any GPU call. Every call on one GPU uses the same array: calls that overlap
+ * the array's address. What a large V needs beyond the array (the library's factors and hand-off words, a padded copy
+ * of V) is reused: the reflections are applied in segments, one after the other. Shapes whose factors and partial Gram
+ * matrices in the caller's own blocks need more than the array holds (about 4 n kp (2 + min(16, ceil(d / 128))) bytes,
+ * kp = k rounded up to a power of two >= 16), and the library's layout too, return FASTH_EUNSUPPORTED before any
+ * GPU call. Every call on one GPU uses the same array: calls that overlap
  * on one GPU (different streams or threads) race; calls on one stream do not. */
 #define FASTH_STATIC_SCRATCH_BYTES (24u << 20)
 int fasth_forward_static(const fasth_shape* shape, const float* V, const float* X, float* A, void* stream);

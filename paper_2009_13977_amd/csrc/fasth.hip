@@ -640,22 +640,38 @@ int fasth_forward_static(const fasth_shape* shape, const float* V, const float* 
   if (rc != FASTH_OK) return rc;
   if (!V || !X || !A) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(X) || !aligned16(A)) return FASTH_EALIGN;
-  // only the regions Step 1 writes and Step 2 reads: nothing is saved for a backward pass
-  // (where the kernels in which workgroups share columns would need more room than the array has, the layout without
-  // them: no hand-off area and the caller's own block size, and the chain runs on the other kernels)
+  // Only the regions Step 1 writes and Step 2 reads: nothing is saved for a backward pass. Where the operands of V for wide
+  // mini-batches do not fit, the layout without them. Where that does not fit either (a large V that is copied or whose shared-column
+  // kernels need much), the reflections go in segments, one after the other on the same array and in place: H X = H_1 ... H_s (H_{s+1}
+  // ... H_n X). us, the rows as the caller has them and segments: d = 1000, n = 6000, m = 32, k = 50: 515, 192; d = 1023, n = 7000,
+  // m = 32, k = 28: 519, 234; d = 1000, n = 6000, m = 600, k = 24: 1540, 463; d = 2048, n = 6400, m = 32, k = 32: 494, 258. The caller's
+  // own blocks decide what is refused, and serve vectors that no layout pads.
+  const int d = shape->d, n = shape->n, m = shape->m, k = shape->k;
+  auto fits = [&](int rows, LayoutLevel l) { return make_layout(d, rows, m, k, l).off_saveA <= FASTH_STATIC_SCRATCH_BYTES; };
   LayoutLevel level = kLayoutTrio;
-  Layout L = make_layout(shape->d, shape->n, shape->m, shape->k, level);
-  while (level != kLayoutPlain && L.off_saveA > FASTH_STATIC_SCRATCH_BYTES) {
-    level = level == kLayoutTrio ? kLayoutShared : kLayoutPlain;
-    L = make_layout(shape->d, shape->n, shape->m, shape->k, level);
+  int rows = n;  // of a segment; the last one has what is left
+  if (!fits(n, level)) {
+    level = kLayoutShared;
+    if (!fits(n, level)) {
+      if (!fits(n, kLayoutPlain)) return FASTH_EUNSUPPORTED;
+      if (d > kMaxPaddedD) level = kLayoutPlain;
+      else
+        for (int parts = 2; rows > kWideRows && !(fits(rows, level) && fits(n - (n - 1) / rows * rows, level)); ++parts)
+          rows = padded_rows((n + parts - 1) / parts, kWideRows);
+    }
   }
-  if (L.off_saveA > FASTH_STATIC_SCRATCH_BYTES) return FASTH_EUNSUPPORTED;
   void* ws = nullptr;
   if ((rc = static_scratch(&ws)) != FASTH_OK) return rc;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, ws, level);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if ((rc = build_factors(P, V, st)) != FASTH_OK) return rc;
-  return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st, false);
+  const int segments = (n + rows - 1) / rows;
+  for (int i = 0; i < segments; ++i) {
+    const int first = (shape->transpose ? i : segments - 1 - i) * rows;
+    const Product P = bind(d, std::min(rows, n - first), m, k, ws, level);
+    const float* Vs = V + (size_t)first * d;
+    if ((rc = build_factors(P, Vs, st)) != FASTH_OK) return rc;
+    if ((rc = run_chain(P, Vs, i == 0 ? X : A, A, shape->transpose, true, nullptr, 0, st, false)) != FASTH_OK) return rc;
+  }
+  return FASTH_OK;
 }
 
 int fasth_prepare(const fasth_shape* shape, const float* V, void* workspace, size_t workspace_bytes, void* stream) {
