@@ -271,18 +271,13 @@ struct PipeRegs {
 // are the factors of the row groups (T_i is triangular and the groups are consecutive reflections), the
 // coefficients of the steps put together are T_i V_i a, and the block's input is saved at its first step,
 // so nothing downstream sees the difference; p.nb counts the steps. SUB is the number of steps per block
-// (0: taken from p.sub at run time). PAD: k is not a multiple of K, so a block's last step has fewer than K
-// rows; the missing rows repeat the last one and their inner products and coefficients are forced to zero.
+// (0: taken from p.sub at run time).
 // RL: rows of the next block fetched during the reduction; P1: during the first product (0: half of the rest);
 // XB: at each of four points next to the two barriers (before and after each), where a wave waits anyway: for the
 // other waves, or for the LDS reads it has just issued. A fetch keeps the issuing wave from its arithmetic for ~35
 // clocks, so the fewer of them sit between the multiply-adds the better (d = 4096: 1.61 -> 1.40 ms per forward +
 // backward with XB = 1, d = 2048: 396 -> 372 us, d = 1024: 113.7 -> 112.2 us).
-// UNAL: d is not a multiple of VW, so rows are not 16-byte aligned and the last chunk of a row hangs over its end.
-// Rows are then fetched through a buffer that spans the block (4-byte alignment is enough for it, and what lies
-// beyond the block reads as zero); the overhanging elements see the next row's values, so they are put back to
-// zero after every update and never stored.
-template <int K, int VW, int NT, int RL = 0, int SUB = 1, bool PAD = false, int P1 = 0, bool UNAL = false, int XB = 0>
+template <int K, int VW, int NT, int RL = 0, int SUB = 1, int P1 = 0, int XB = 0>
 __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
   typedef PipeRegs<K, VW, NT> Regs;
   constexpr int NW = NT / 64, G = Regs::G, LPT = Regs::LPT;
@@ -321,40 +316,15 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
   const bool ok = VW * tid < d;
   const unsigned x0 = ok ? VW * tid : 0;
   Chunk<VW> a = load_column_chunk<VW>(p, col, x0, ok);
-  bool keep[VW];  // elements of this thread's chunk that exist
-#pragma unroll
-  for (int r = 0; r < VW; ++r) keep[r] = ok && (!UNAL || x0 + r < (unsigned)d);
   const int sel = reduce_sel<K>(lane);
   auto block_of = [&](int s) { return p.transpose ? s : nb - 1 - s; };
   const int sub = SUB > 0 ? SUB : p.sub;
   auto step_block = [&](int i) { return SUB == 1 ? i : i / sub; };
   auto step_part = [&](int i) { return SUB == 1 ? 0 : i % sub; };
-  auto rows_valid = [&](int i) { return PAD ? min(K, p.k - step_part(i) * K) : K; };
   // uniform row base (scalar registers) + 32-bit per-lane offset
-  auto row_ptr = [&](int i, int j) {
-    if constexpr (PAD) {
-      const int row = step_block(i) * p.k + step_part(i) * K + min(j, rows_valid(i) - 1);
-      return p.V + (size_t)row * (size_t)d + x0;
-    } else {
-      return p.V + ((size_t)i * K + j) * (size_t)d + x0;
-    }
-  };
-  auto load_row = [&](int i, int j) {
-    if constexpr (UNAL) {
-      // the buffer spans the step's block of k rows (at most 2 MiB), so V itself may be of any size
-      const BufferDesc vdesc = make_buffer(p.V + (size_t)step_block(i) * p.k * d, (size_t)p.k * d * sizeof(float));
-      const unsigned row = (unsigned)(step_part(i) * K + (PAD ? min(j, rows_valid(i) - 1) : j));
-      const BufVec<VW> v = buffer_load<VW>(vdesc, x0 * 4u, row * (unsigned)d * 4u);
-      Chunk<VW> c;
-#pragma unroll
-      for (int r = 0; r < VW; ++r) c.e[r] = v.e[r];
-      return c;
-    } else {
-      return load_chunk<VW>(row_ptr(i, j));
-    }
-  };
+  auto load_row = [&](int i, int j) { return load_chunk<VW>(p.V + ((size_t)i * K + j) * (size_t)d + x0); };
   auto load_t = [&](int i, Regs& r) {
-    const int LDT = (SUB > 0 && !PAD && K * SUB >= 16) ? K * SUB : p.kp;  // row stride of the stored factor
+    const int LDT = (SUB > 0 && K * SUB >= 16) ? K * SUB : p.kp;  // row stride of the stored factor
     // rows of op(T): of the factor itself or of its stored transpose, so a thread's LPT entries are consecutive in
     // memory either way (one 16-byte fetch for every four) as its partial sums are in LDS
     const float* Ti = (p.transpose ? p.Tt : p.T) + (size_t)step_block(i) * LDT * LDT + (size_t)step_part(i) * (K * LDT + K);
@@ -373,17 +343,8 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
 
   // Applies block i held in `cur` while fetching block inext into `nxt`.
   auto apply_block = [&](int i, Regs& cur, int inext, Regs& nxt) {
-    if (p.save_in && ok && (SUB == 1 || step_part(i) == (p.transpose ? 0 : sub - 1))) {
-      float* dst = p.save_in + ((size_t)step_block(i) * m + col) * d + x0;
-      if constexpr (UNAL) {
-#pragma unroll
-        for (int r = 0; r < VW; ++r)
-          if (keep[r]) dst[r] = a.e[r];
-      } else {
-        store_chunk<VW>(dst, a);
-      }
-    }
-    const int kv = rows_valid(i);
+    if (p.save_in && ok && (SUB == 1 || step_part(i) == (p.transpose ? 0 : sub - 1)))
+      store_chunk<VW>(p.save_in + ((size_t)step_block(i) * m + col) * d + x0, a);
     float pj[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
@@ -394,7 +355,7 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
       float acc = 0.f;
 #pragma unroll
       for (int r = 0; r < VW; ++r) acc = fmaf(cur.v[j].e[r], a.e[r], acc);
-      pj[j] = (PAD && j >= kv) ? 0.f : acc;
+      pj[j] = acc;
     }
     load_t(inext, nxt);
     if constexpr (RL > 0) {
@@ -445,14 +406,9 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
         }
       }
       c = group_sum<G>(c);
-      if (PAD && trow >= kv) c = 0.f;
       if (tg == 0) {
         Cv[trow] = c;
-        if constexpr (PAD) {
-          if (p.save_c && trow < kv) p.save_c[(size_t)col * p.n + (size_t)step_block(i) * p.k + step_part(i) * K + trow] = c;
-        } else {
-          if (p.save_c) p.save_c[(size_t)col * p.n + (size_t)i * K + trow] = c;
-        }
+        if (p.save_c) p.save_c[(size_t)col * p.n + (size_t)i * K + trow] = c;
       }
     }
     fetch_at_barrier(2);
@@ -486,7 +442,7 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
     }
 #pragma unroll
     for (int r = 0; r < VW; ++r)
-      if (!keep[r]) a.e[r] = 0.f;
+      if (!ok) a.e[r] = 0.f;
   };
 
   Regs ra, rb;
@@ -501,21 +457,19 @@ __global__ void __launch_bounds__(NT) chain_pipe_kernel(ChainArgs p) {
   if (s < nb) apply_block(block_of(s), ra, block_of(s), rb);
 #pragma unroll
   for (int r = 0; r < VW; ++r)
-    if (keep[r] && x0 + r < (unsigned)p.out_rows) p.out[(size_t)(x0 + r) * m + col] = a.e[r];
+    if (ok && x0 + r < (unsigned)p.out_rows) p.out[(size_t)(x0 + r) * m + col] = a.e[r];
 }
 
-template <int K, int VW, int NT, int RL = 0, int SUB = 1, bool PAD = false, int P1 = 0, bool UNAL = false, int XB = 0>
+template <int K, int VW, int NT, int RL = 0, int SUB = 1, int P1 = 0, int XB = 0>
 static int launch_chain_pipe(const ChainArgs& args, hipStream_t stream) {
   ChainArgs a = args;
   a.sub = SUB > 0 ? SUB : (args.k + K - 1) / K;
   a.nb = args.nb * a.sub;
-  if ((size_t)VW * NT < (size_t)a.d || (PAD ? (a.sub * K > a.kp || a.sub != (a.k + K - 1) / K) : a.sub * K != a.k) ||
-      (!UNAL && a.d % VW != 0))
-    return FASTH_EINVAL;
+  if ((size_t)VW * NT < (size_t)a.d || a.sub * K != a.k || a.d % 4 != 0) return FASTH_EINVAL;
   const int side = a.ds_out ? (a.ds_rows + NT / 64 - 1) / (NT / 64) : 0;
-  static const std::string name = variant_name("chain_pipe_kernel", {K, VW, NT, RL, SUB, PAD, P1, UNAL, XB});
+  static const std::string name = variant_name("chain_pipe_kernel", {K, VW, NT, RL, SUB, P1, XB});
   prof::Scope ps_(FASTH_KERNEL_CHAIN, stream, name.c_str());
-  hipLaunchKernelGGL((chain_pipe_kernel<K, VW, NT, RL, SUB, PAD, P1, UNAL, XB>), dim3(a.m + side), dim3(NT), 0, stream, a);
+  hipLaunchKernelGGL((chain_pipe_kernel<K, VW, NT, RL, SUB, P1, XB>), dim3(a.m + side), dim3(NT), 0, stream, a);
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;
 }
@@ -579,9 +533,9 @@ static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
       // (d = 1024, k = 32, per forward + backward: m = 384: 233 -> 194 us, m = 512: 244 -> 222, m = 768: 356 -> 321;
       // up to 256 columns the 32-row steps are the faster ones: 137 against 149 us at m = 256).
       if (a.m > kComputeUnits && d > 512 && d <= 1024) {
-        if (k == 32) return launch_chain_pipe<16, 4, 256, 4, 2, false, 4, false, 1>(a, stream);
-        if (k == 64) return launch_chain_pipe<16, 4, 256, 4, 4, false, 4, false, 1>(a, stream);
-        return launch_chain_pipe<16, 4, 256, 4, 8, false, 4, false, 1>(a, stream);
+        if (k == 32) return launch_chain_pipe<16, 4, 256, 4, 2, 4, 1>(a, stream);
+        if (k == 64) return launch_chain_pipe<16, 4, 256, 4, 4, 4, 1>(a, stream);
+        return launch_chain_pipe<16, 4, 256, 4, 8, 4, 1>(a, stream);
       }
       // (7 of the 32 rows of the next block fetched during the first product, 8 during the reduction, 4 next to the
       // barriers, 13 during the update)
@@ -590,43 +544,32 @@ static int launch_chain_kernel(const ChainArgs& a, hipStream_t stream) {
       // faster than one copy refilled in place or rows streamed twice (d = n = 2048: 178 us for k = 32, 64 and 128
       // alike, against 222, 359 and 406 us)
       if (d <= 1024) {
-        if (k == 32) return launch_chain_pipe<32, 4, 256, 8, 1, false, 7, false, 1>(a, stream);
-        if (k == 64) return launch_chain_pipe<32, 4, 256, 8, 2, false, 7, false, 1>(a, stream);
-        return launch_chain_pipe<32, 4, 256, 8, 4, false, 7, false, 1>(a, stream);
+        if (k == 32) return launch_chain_pipe<32, 4, 256, 8, 1, 7, 1>(a, stream);
+        if (k == 64) return launch_chain_pipe<32, 4, 256, 8, 2, 7, 1>(a, stream);
+        return launch_chain_pipe<32, 4, 256, 8, 4, 7, 1>(a, stream);
       }
       if (d <= 2048) {
-        if (k == 32) return launch_chain_pipe<16, 4, 512, 4, 2, false, 4, false, 1>(a, stream);  // fetch split 4 / 4 / 4 / 4
-        if (k == 64) return launch_chain_pipe<16, 4, 512, 4, 4, false, 4, false, 1>(a, stream);
-        return launch_chain_pipe<16, 4, 512, 4, 8, false, 4, false, 1>(a, stream);
+        if (k == 32) return launch_chain_pipe<16, 4, 512, 4, 2, 4, 1>(a, stream);  // fetch split 4 / 4 / 4 / 4
+        if (k == 64) return launch_chain_pipe<16, 4, 512, 4, 4, 4, 1>(a, stream);
+        return launch_chain_pipe<16, 4, 512, 4, 8, 4, 1>(a, stream);
       }
     }
     // Few reflections (blocks of 8 or 16 rows): two copies of a whole block in registers, a quarter of the next block fetched during
     // the reduction; narrower lanes for short vectors keep all four waves busy
     if (d % 4 == 0 && k == 16) {
-      if (d <= 256) return launch_chain_pipe<16, 1, 256, 4, 1, false, 4, false, 1>(a, stream);
-      if (d <= 512) return launch_chain_pipe<16, 2, 256, 4, 1, false, 4, false, 1>(a, stream);
-      if (d <= 1024) return launch_chain_pipe<16, 4, 256, 4, 1, false, 4, false, 1>(a, stream);
-      if (d <= 2048) return launch_chain_pipe<16, 4, 512, 4, 1, false, 4, false, 1>(a, stream);
+      if (d <= 256) return launch_chain_pipe<16, 1, 256, 4, 1, 4, 1>(a, stream);
+      if (d <= 512) return launch_chain_pipe<16, 2, 256, 4, 1, 4, 1>(a, stream);
+      if (d <= 1024) return launch_chain_pipe<16, 4, 256, 4, 1, 4, 1>(a, stream);
+      if (d <= 2048) return launch_chain_pipe<16, 4, 512, 4, 1, 4, 1>(a, stream);
     }
     if (d % 4 == 0 && k == 8) {
       if (d <= 256) return launch_chain_pipe<8, 1, 256, 2>(a, stream);
       if (d <= 512) return launch_chain_pipe<8, 2, 256, 2>(a, stream);
-      if (d <= 1024) return launch_chain_pipe<8, 4, 256, 2, 1, false, 1, false, 1>(a, stream);
-      if (d <= 2048) return launch_chain_pipe<8, 4, 512, 2, 1, false, 1, false, 1>(a, stream);
+      if (d <= 1024) return launch_chain_pipe<8, 4, 256, 2, 1, 1, 1>(a, stream);
+      if (d <= 2048) return launch_chain_pipe<8, 4, 512, 2, 1, 1, 1>(a, stream);
     }
-    if (d % 4 == 0 && k % 8 == 0 && d > 2048) return launch_chain_pipe<8, 4, 1024, 2, 0, false, 1, false, 1>(a, stream);
-    // Rows as the caller has them, any length and any block size: only where fasth_forward_static has no room for the
-    // padded copy of V.
-    if (d <= 1024) {
-      if (k <= 8) return launch_chain_pipe<8, 4, 256, 2, 0, true, 0, true>(a, stream);
-      if (k <= 16) return launch_chain_pipe<16, 4, 256, 4, 0, true, 0, true>(a, stream);
-      return launch_chain_pipe<32, 4, 256, 8, 0, true, 7, true, 1>(a, stream);
-    }
-    if (d <= 2048) {
-      if (k <= 8) return launch_chain_pipe<8, 4, 512, 2, 0, true, 1, true, 1>(a, stream);
-      return launch_chain_pipe<16, 4, 512, 4, 0, true, 4, true, 1>(a, stream);
-    }
-    return launch_chain_pipe<8, 4, 1024, 2, 0, true, 1, true, 1>(a, stream);
+    if (d % 4 == 0 && k % 8 == 0 && d > 2048) return launch_chain_pipe<8, 4, 1024, 2, 0, 1, 1>(a, stream);
+    return FASTH_EUNSUPPORTED;  // no layout has such blocks
   }
   // longer vectors: the general kernel
   const int threads = 1024, nw = threads / 64;
