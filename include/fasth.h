@@ -53,7 +53,8 @@ enum {
  * not depend on k beyond rounding (Eq. 2 holds for any grouping of consecutive
  * reflections), and for d <= 4096 the library regroups them into blocks of its
  * own, 32 or 64 rows (8, 16 or 24 for few reflections in small blocks, k < 32),
- * padding the last one. */
+ * padding the last one. A larger k still bounds the memory: where blocks of 32 or
+ * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. */
 typedef struct fasth_shape {
   int d;          /* length of each Householder vector = rows of X */
   int n;          /* number of reflections = rows of V */
@@ -103,8 +104,9 @@ int fasth_set_wait_limit(int polls);
  * of Algorithm 1's Remark, the saved gradients dL/dA_i of Algorithm 2 Step 1,
  * the small per-block coefficient vectors and, for a small V against a wide
  * mini-batch, partial sums of dV; where d is no multiple of 4 or n no multiple
- * of the library's blocks, a padded copy of V). Returns 0 if the shape is
- * invalid or unsupported. */
+ * of the library's blocks, a padded copy of V; for more than 1024 columns of up to
+ * 2048 elements a copy of V as operands of the matrix cores, 12 bytes per
+ * element). Returns 0 if the shape is invalid or unsupported. */
 size_t fasth_workspace_bytes(const fasth_shape* shape);
 
 /* Algorithm 1. A = H X (or H^T X). Step 1 builds, for every block i, the

@@ -228,7 +228,10 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   a.in_scale = in_scale; a.in_scale_mode = in_scale_mode;
   a.in_rows = in_rows < 0 ? P.d : in_rows;
   a.out_rows = P.d;
-  a.d = P.L.dp; a.n = P.L.np; a.m = P.m; a.k = P.L.ki; a.kp = P.L.kp; a.nb = P.L.nb;
+  a.d = P.L.dp; a.n = P.L.np; a.m = P.m;
+  // where nothing is saved, the factors' own blocks (chain_trio_kernel's are 64 rows, also of larger blocks)
+  a.k = P.L.trio.parts && !save ? P.L.kf : P.L.ki;
+  a.kp = padded_block(a.k); a.nb = P.L.np / a.k;
   a.transpose = transpose;
   a.sub = 1;
   a.ds_z1 = ds_z1; a.ds_out = ds_out; a.ds_rows = ds_rows;

@@ -249,6 +249,17 @@ static int inner_block(int d, int n, int m, int k) {
   const double saved = 4.0 * ((n + 31) / 32) * m * d;
   return fills_64(d, n, m) && ((d > 1536 && k > 32) || saved >= (m > 896 ? kManySavedBytesTiles : kManySavedBytes)) ? 64 : 32;
 }
+// A caller's larger blocks bound the memory for the saved inputs (n / k of them per chain): smaller ones than the caller's are taken
+// only while the workspace grows by no more than this.
+constexpr double kExtraSavedBytes = 1073741824.0;
+static int bounded_block(int d, int n, int m, int k, int block) {
+  auto saved = [&](int rows) { return 8.0 * ((n + rows - 1) / rows) * m * d; };
+  while (block >= 32 && block < 128 && block < k && saved(block) - saved(k) > kExtraSavedBytes) block *= 2;
+  return block;
+}
+// Blocks are a grid dimension of the factor and dV launches (n / 64 of them and n / 128 pairs at most): beyond this many reflections
+// blocks of 128 rows and nothing shared.
+constexpr int kMaxBlocks = 65535, kManyReflections = 64 * (kMaxBlocks / 2);
 
 // Few reflections in small blocks (the caller's k < 32): blocks of 16 rows, whose factors cost least, and steps of 16 rows on the kernels
 // for one column per workgroup and on chain_tile_kernel, without hand-overs and with the least padding. How many are few depends on
@@ -319,17 +330,23 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
   L.dp = d; L.np = n; L.ki = k;
   const int d4 = (d + 3) & ~3;
   const bool fewest = k <= 8 && fewest_rows(d4, n, m);
-  L.trio = level == kLayoutTrio && !fewest ? trio_plan(d4, n, m) : TrioPlan{0, 0, 0};
+  const bool many = n > kManyReflections && d <= kMaxPaddedD;
+  L.trio = level == kLayoutTrio && !fewest && !many ? trio_plan(d4, n, m) : TrioPlan{0, 0, 0};
   if (L.trio.parts) {
     L.dp = d4;
-    L.ki = 64;
-    L.np = padded_rows(n, 64);
+    L.ki = bounded_block(d4, n, m, k, 64);
+    L.np = padded_rows(n, L.ki);
+  } else if (shared && many) {
+    L.dp = d4;
+    L.ki = kMaxBlock;
+    L.np = padded_rows(n, kMaxBlock);
   } else if (shared && d <= kMaxPaddedD) {
     L.dp = d4;
     L.ki = fewest ? 8 : k < 32 && few_reflections(d4, n, m) ? kFewRows : inner_block(d4, n, m, k);
     // dv_trio_kernel takes 64 rows; blocks of 32 would save twice as many inputs, and the chain kernels for so many columns
     // take 64 rows per step whatever the block
     if (L.ki > kFewRows && fills_64(d4, n, m) && dv_trio_serves(d4, n, m, 64)) L.ki = 64;
+    L.ki = bounded_block(d4, n, m, k, L.ki);
     L.np = L.ki <= kFewRows ? padded_rows(n, L.ki) : steps_rows(d4, n, m, L.ki);
     // (no kernel with shared columns: those have taken whole steps)
     if ((L.ki == kFewRows || L.ki == 32) && !team_parts(d4, L.np, m, L.ki) && least_padding(d4, n, L.ki) == 24) {
@@ -341,7 +358,7 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
   d = L.dp; n = L.np; k = L.ki;
   L.kp = padded_block(k);
   L.nb = n / k;
-  const bool others = shared && !L.trio.parts;
+  const bool others = shared && !L.trio.parts && !many;
   const int team = others ? team_parts(d, n, m, k) : 0, wide = others ? team_wide_parts(d, n, m, k) : 0;
   const int ttile = others ? team_tile_parts(d, n, m, k) : 0;
   // The kernels in which workgroups share columns take 64 rows (32: the shared tiles at d > 1024) of factor per step
@@ -365,9 +382,9 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
   L.off_V = take(L.copy_v ? (size_t)n * d : 0);
   L.off_frag = take(L.trio.parts ? (size_t)(n / 64) * ((d + 31) / 32) * (24 * 1024 / 4) : 0);
   L.off_T = take(2 * (size_t)L.nbf * L.kpf * L.kpf);  // the factors and, behind them, their transposes
-  // partial Gram matrices (later the dV kernel's per-block matrices Z, nb kp^2 floats, which they always cover) and,
+  // partial Gram matrices, later the dV kernel's per-block matrices Z (nb kp^2 floats), and,
   // where the Gram product is split over workgroups, an 8-byte "ready" word per partial matrix
-  L.off_Spart = take((size_t)(L.nbf + L.npair) * L.gram_split * L.kpf * L.kpf);
+  L.off_Spart = take(std::max((size_t)(L.nbf + L.npair) * L.gram_split * L.kpf * L.kpf, (size_t)L.nb * L.kp * L.kp));
   L.off_ready = take(factor_is_fused(L.kpf, d) ? 0 : (size_t)(L.nbf + L.npair) * L.gram_split * 2);
   L.off_S = take(2 * (size_t)L.npair * L.kpf * L.kpf);  // per pair V_a V_b^T and its transpose
   L.xch_words = wide ? (size_t)m * team_wide_words_per_column(wide)
@@ -394,7 +411,7 @@ static int check_shape(const fasth_shape* s) {
   if (s->n % s->k != 0) return FASTH_EINVAL;
   if (s->transpose != 0 && s->transpose != 1) return FASTH_EINVAL;
   if (s->k > kMaxBlock || s->d > kMaxD || s->m > 65535) return FASTH_EUNSUPPORTED;
-  if (s->n / s->k > 65535) return FASTH_EUNSUPPORTED;  // blocks are a grid dimension of the factor and dV launches
+  if (s->n / s->k > kMaxBlocks) return FASTH_EUNSUPPORTED;
   return FASTH_OK;
 }
 
