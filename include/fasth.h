@@ -152,9 +152,12 @@ int fasth_backward(const fasth_shape* shape, const float* V, const float* G,
                    float* dV, float* dX, void* workspace, size_t workspace_bytes, void* stream);
 
 /* Section 3.3 "Trade-off": the block size k trades total work against the number of sequential
- * steps, and the paper picks it by trying the candidates once on the hardware at hand. This call
- * times fasth_forward + fasth_backward (`repetitions` >= 1 timed passes after one untimed pass) for
- * every candidate block size and writes the fastest to *best_k and its milliseconds per pass to
+ * steps, and the paper picks it by trying the candidates once on the hardware at hand. For d <= 4096 this library
+ * regroups the reflections by itself (see fasth_shape), so most block sizes lead to the same blocks and k matters for
+ * few reflections (k < 32, k <= 8) and for the memory (large k); for longer vectors k is the block size that runs. This call
+ * times fasth_forward + fasth_backward (`repetitions` >= 1 timed passes after one untimed pass) once for
+ * every different grouping that the candidates lead to and writes the first candidate of the fastest one to *best_k and
+ * its milliseconds per pass to
  * *best_ms (may be NULL); both are HOST pointers. `candidates` is a HOST array of ncandidates block
  * sizes, or NULL for every divisor of n in [2, 128]. Candidates that do not divide n, are out of
  * range, or need more workspace than given are skipped; FASTH_EUNSUPPORTED if none is left.

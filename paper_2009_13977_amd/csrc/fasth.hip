@@ -737,10 +737,16 @@ int fasth_tune_block_size(const fasth_shape* shape, const int* candidates, int n
   if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return FASTH_EHIP; }
   int rc = FASTH_OK, found = 0;
   float best = 0.f;
+  std::vector<Layout> tried;
   for (int k : ks) {
     fasth_shape s = *shape;
     s.k = k;
     if (check_shape(&s) != FASTH_OK || fasth_workspace_bytes(&s) > workspace_bytes) continue;  // not a usable candidate
+    // the library's blocks decide what runs: a candidate that leads to the same ones has been tried (its first stands for all)
+    const Layout L = make_layout(s.d, s.n, s.m, k);
+    if (std::any_of(tried.begin(), tried.end(), [&](const Layout& t) { return t.ki == L.ki && t.np == L.np && t.trio.parts == L.trio.parts; }))
+      continue;
+    tried.push_back(L);
     // one untimed pass, then `repetitions` timed ones
     for (int pass = 0; pass < 2 && rc == FASTH_OK; ++pass) {
       const int reps = pass == 0 ? 1 : repetitions;
