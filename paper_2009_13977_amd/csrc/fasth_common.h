@@ -233,8 +233,12 @@ static bool factor_is_fused(int kp, int d) { return kp <= 32 || (kp == 64 && d <
 // rows: d = n = 128, m = 100: 25, 37, 67; d = n = 512, m = 64: 46, 59, -; m = 300: 72, 88, -; d = n = 1024, m = 32: 72, 73, 86; m = 200:
 // 122, 132, 174; d = n = 2048, m = 64: 184, 185, 208; m = 440 (231 MB of saved inputs per chain): 809, 779, -; d = n = 2560, m = 200
 // (164 MB): 705, 727, -; d = n = 3072, m = 130 (153 MB): 861, 877, -; m = 200 (236 MB): 1064, 923, -.
-// (A longer vector is no reason for blocks of 64: d = n = 2048, m = 32: 157, 161; m = 64: 184, 185, inputs and workspace new to the caches
-// in each pass: 189.5, 190; d = n = 4096, m = 32: 401, 414.)
+// A caller's larger blocks (k > 32) need half the memory for the saved inputs; they become blocks of 64 for vectors of more than 1536
+// elements from 64 columns on, where that costs nothing on the average. us with blocks of 32 and 64, repeated / inputs and workspace
+// new to the caches in each pass: d = n = 2048, m = 64: 184, 185 / 189.5, 190 (three sets in turn, which fit the cache with blocks of
+// 64 only: 189.6, 185.7); d = 2048, n = 1024, m = 64: 106, 105 / 110, 109; d = n = 2048, m = 200: 393, 400 / 446, 409; d = n = 3072, m = 100: 842,
+// 854 / 844, 875; d = 4096, n = 1024, m = 200: 408, 407 / 455, 413; but with fewer columns: d = n = 2048, m = 32: 157, 161 / 163, 167; d = n =
+// 3072, m = 32: 281, 291 / 287, 297; d = n = 4096, m = 8: 392, 417 / 404, 430; and shorter vectors: d = n = 1600, m = 64: 145, 147 / 149, 151.
 // From 897 columns on, where the chains run on the matrix cores and hardly wait, half the saved inputs pay from 25 MB per chain on: blocks
 // of 32 and 64, d = 1024, m = 1000: n = 192 (25 MB): 94, 92; n = 256: 114, 107; d = 512, m = 1500: n = 384 (37 MB): 126, 122; n = 512:
 // 156, 140; d = 2048, m = 1000: n = 128 (33 MB): 142, 132; but m = 800: d = 512, n = 768: 173, 187; d = 640, n = 576: 135, 142.
@@ -245,9 +249,9 @@ static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multip
 static bool fills_64(int d, int n, int m) {
   return n > 320 || padded_rows(n, 64) == padded_rows(n, 32) || (d <= 2048 && (m > 2048 ? n > 128 : m > 896 ? n > 192 : m > 768 && n > 256));
 }
-static int inner_block(int d, int n, int m) {
+static int inner_block(int d, int n, int m, int k) {
   const double saved = 4.0 * ((n + 31) / 32) * m * d;
-  return fills_64(d, n, m) && saved >= (m > 896 ? kManySavedBytesTiles : kManySavedBytes) ? 64 : 32;
+  return fills_64(d, n, m) && ((k > 32 && d > 1536 && m >= 64) || saved >= (m > 896 ? kManySavedBytesTiles : kManySavedBytes)) ? 64 : 32;
 }
 // A caller's larger blocks bound the memory for the saved inputs (n / k of them per chain): smaller ones than the caller's are taken
 // only while the workspace grows by no more than this.
@@ -342,7 +346,7 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
     L.np = padded_rows(n, kMaxBlock);
   } else if (shared && d <= kMaxPaddedD) {
     L.dp = d4;
-    L.ki = fewest ? 8 : k < 32 && few_reflections(d4, n, m) ? kFewRows : inner_block(d4, n, m);
+    L.ki = fewest ? 8 : k < 32 && few_reflections(d4, n, m) ? kFewRows : inner_block(d4, n, m, k);
     // dv_trio_kernel takes 64 rows; blocks of 32 would save twice as many inputs, and the chain kernels for so many columns
     // take 64 rows per step whatever the block
     if (L.ki > kFewRows && fills_64(d4, n, m) && dv_trio_serves(d4, n, m, 64)) L.ki = 64;
