@@ -43,10 +43,15 @@ def f_seq(d, n, m):
     return 16.0 * d * n * m
 
 
+def block_rows(d, k):
+    """Rows of the blocks that run, at least: up to d = 4096 the library regroups the reflections (32 rows, 64 in places)."""
+    return min(k, 32) if d <= 4096 else k
+
+
 def f_exec(d, n, m, k):
     # Gram products 2dnk (upper tiles only: about half of it is issued), two chains 4dnm each,
-    # dV products 4dnm + 2dnk.
-    return 12.0 * d * n * m + 4.0 * d * n * k
+    # dV products 4dnm + 2dnk, k the rows of the blocks that run.
+    return 12.0 * d * n * m + 4.0 * d * n * block_rows(d, k)
 
 
 def kernel_flops(slot, d, n, m, k):
@@ -54,16 +59,17 @@ def kernel_flops(slot, d, n, m, k):
     if slot == "chain_kernel":
         return 4.0 * d * n * m                       # B = V_i a and a -= V_i^T C over all blocks
     if slot == "dv_kernel":
-        return 4.0 * d * n * m + 2.0 * d * n * k     # the three products per block
+        return 4.0 * d * n * m + 2.0 * d * n * block_rows(d, k)  # the three products per block
     if slot in ("factor_fused_kernel", "team_factor_kernel"):
-        return 2.0 * d * n * k                       # Gram products (upper tiles: about half is issued)
+        return 2.0 * d * n * block_rows(d, k)        # Gram products (upper tiles: about half is issued)
     return None
 
 
 def chain_algorithmic_bytes(d, n, m, k):
     """HBM bytes one chain launch must move: V, the factors and the input in; the saved block inputs, the
     coefficients and the output out."""
-    nb = n // k
+    k = block_rows(d, k)
+    nb = -(-n // k)
     return 4.0 * (d * n + nb * k * k + d * m) + 4.0 * (nb * d * m + n * m + d * m)
 
 

@@ -256,7 +256,8 @@ int svd_layer_log_abs_det(int d, const float* sigma, float* log_abs_det, float* 
  * a counter from which every factor launch with a split Gram product draws its number.) */
 enum {
   FASTH_KERNEL_TEAM_FACTOR = 0,
-  FASTH_KERNEL_RESERVED = 1, /* trio_rows_kernel: the rows of V as operands of the chain kernel for wide mini-batches */
+  FASTH_KERNEL_TRIO_ROWS = 1, /* trio_rows_kernel: the rows of V as operands of the chain kernel for wide mini-batches */
+  FASTH_KERNEL_RESERVED = FASTH_KERNEL_TRIO_ROWS, /* its name while no kernel had the slot */
   FASTH_KERNEL_CHAIN = 2,
   FASTH_KERNEL_DV = 3,
   FASTH_KERNEL_SEQ_FORWARD = 4,

@@ -14,9 +14,10 @@
 //   team_factor_kernel   Algorithm 1 Step 1 with a block's Gram product split over workgroups (MFMA); also the products
 //                        V_a V_b^T of consecutive blocks' rows for the chain kernel that joins two blocks per step
 //   chain_*_kernel       Algorithm 1 Step 2 / Algorithm 2 Step 1: the sequential block chain: per column of X
-//                        (pair, pipe, general), a team of workgroups per column (team, team_wide), or 4 / 16 columns per
-//                        workgroup on the matrix cores (quad, tile)
-//   dv_kernel            Algorithm 2 Step 2 as dense products per block (MFMA)
+//                        (pair, pipe, general), a team of workgroups per column (team, team_wide), or 4 / 16 / 32 columns
+//                        per workgroup or team on the matrix cores (quad, tile, team_tile, trio)
+//   trio_rows_kernel     the rows of V as operands of chain_trio_kernel, part of Step 1
+//   dv_*                 Algorithm 2 Step 2 as dense products per block (MFMA)
 //   seq_*                the one-reflection-at-a-time comparison
 //   dsigma_kernel        the diagonal step of the SVD layer
 // The kernels live in fasth_factor.h, fasth_chain.h (+ fasth_chain_team.h, fasth_chain_pair.h, fasth_chain_quad.h,
@@ -157,7 +158,7 @@ static int launch_trio_rows(const Product& P0, const float* V0, const Product* P
   pair.a[1] = P1 ? bind_rows(*P1, V1) : TrioRowsArgs{};
   const int xb = std::max(pair.a[0].xblocks, pair.a[1].xblocks), steps = std::max(pair.a[0].steps, pair.a[1].steps);
   if (xb == 0) return FASTH_OK;
-  prof::Scope ps_(FASTH_KERNEL_RESERVED, stream, "trio_rows_kernel");
+  prof::Scope ps_(FASTH_KERNEL_TRIO_ROWS, stream, "trio_rows_kernel");
   hipLaunchKernelGGL(trio_rows_kernel, dim3(xb, steps, P1 ? 2 : 1), dim3(256), 0, stream, pair);
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;
@@ -538,7 +539,7 @@ int fasth_wait_status(void* stream) {
 const char* fasth_kernel_name(int id) {
   switch (id) {
     case FASTH_KERNEL_TEAM_FACTOR: return "team_factor_kernel";
-    case FASTH_KERNEL_RESERVED: return "trio_rows_kernel";
+    case FASTH_KERNEL_TRIO_ROWS: return "trio_rows_kernel";
     case FASTH_KERNEL_CHAIN: return "chain_kernel";
     case FASTH_KERNEL_DV: return "dv_kernel";
     case FASTH_KERNEL_SEQ_FORWARD: return "seq_forward_kernel";

@@ -480,7 +480,7 @@ static int launch_chain_pipe(const ChainArgs& args, hipStream_t stream) {
 #include "fasth_chain_pair.h"  // chain_pair_kernel: the per-column chain with two waves per SIMD
 #include "fasth_chain_quad.h"  // chain_quad_kernel: four columns per workgroup on the matrix cores, 256 < m <= 1024
 #include "fasth_chain_team.h"  // chain_team_kernel, chain_team_wide_kernel: two to eight workgroups per column, steps of 64 or 128 rows, few columns
-#include "fasth_chain_trio.h"  // chain_trio_kernel: 32 columns per one to eight workgroups on the bf16 matrix cores, some hundred columns and more
+#include "fasth_chain_trio.h"  // chain_trio_kernel: 16 or 32 columns per one to four workgroups on the bf16 matrix cores, more than a thousand columns
 #include "fasth_chain_teamtile.h"  // chain_team_tile_kernel: 16 columns per two to four workgroups on the matrix cores, some hundred columns
 
 namespace fasth {

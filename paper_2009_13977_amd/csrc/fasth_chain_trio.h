@@ -1,4 +1,4 @@
-// Algorithm 1 Step 2 and Algorithm 2 Step 1 for mini-batches of some hundred columns and more on the bf16 matrix cores
+// Algorithm 1 Step 2 and Algorithm 2 Step 1 for mini-batches of more than a thousand columns on the bf16 matrix cores
 // at fp32 precision (chain_trio_kernel), and the kernel that lays the rows of V out for it (trio_rows_kernel).
 // Included by fasth_chain.h after ChainArgs, diag_factor and dsigma_row.
 #pragma once
