@@ -90,7 +90,7 @@ const char* fasth_strerror(int code);
  * on one stream at a time. Two calls that use the same workspace must not overlap on the GPU
  * (this was already so for calls that save for a backward pass; for these shapes it also holds for fasth_apply
  * without saving).
- * Larger mini-batches (1025 columns and more of 513 to 2048 elements, n > 64, while the teams' workgroups fit the GPU at
+ * Larger mini-batches (1025 columns and more of 513 to 2048 elements, while the teams' workgroups fit the GPU at
  * once: up to 4096 columns) are shared by two to four workgroups per tile of columns as well, in every call but
  * fasth_apply without saving. These teams form in the order in which their workgroups start, so they need nothing of
  * what else the GPU runs: such calls may overlap with any others on other streams (a part that has not started is

@@ -218,8 +218,9 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   const Product& F = factors ? *factors : P;
   ChainArgs a;
   a.V = F.rows(V); a.T = F.T(); a.in = in; a.out = out;
-  // wide mini-batches: calls that may overlap on one workspace cannot hand sums over through it
-  a.xch = F.L.trio.parts && !P.exclusive ? nullptr : F.xch();
+  // calls that may overlap on one workspace cannot hand sums over through it
+  const bool no_teams = !P.exclusive && shared_tiles_overlap(P.L.dp, P.m);
+  a.xch = no_teams ? nullptr : F.xch();
   a.wait_limit = wait_limit(); a.parts = 0;
   a.S = reinterpret_cast<const float*>(F.ws + F.L.off_S);
   a.Tt = a.T + (size_t)F.L.nbf * F.L.kpf * F.L.kpf;
@@ -230,8 +231,8 @@ static int run_chain(const Product& P, const float* V, const float* in, float* o
   a.in_rows = in_rows < 0 ? P.d : in_rows;
   a.out_rows = P.d;
   a.d = P.L.dp; a.n = P.L.np; a.m = P.m;
-  // where nothing is saved, the factors' own blocks (chain_trio_kernel's are 64 rows, also of larger blocks)
-  a.k = P.L.trio.parts && !save ? P.L.kf : P.L.ki;
+  // the factors' own blocks for the kernels that stand in where nothing is saved
+  a.k = no_teams || (P.L.trio.parts && !save) ? P.L.kf : P.L.ki;
   a.kp = padded_block(a.k); a.nb = P.L.np / a.k;
   a.transpose = transpose;
   a.sub = 1;

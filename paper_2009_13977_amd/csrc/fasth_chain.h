@@ -55,7 +55,7 @@ struct ChainArgs {
   // the number of polls after which a wait for another workgroup gives up.
   unsigned* xch;
   int wait_limit;
-  int parts;              // chain_team_kernel: workgroups per column (set by its launcher)
+  int parts;              // kernels with teams: workgroups per column or tile (set by their launchers)
   const char* frag;       // chain_trio_kernel: the rows of V as its operands, else null
   const float* S;         // chain_team_wide_kernel: [n / 128][2][64][64], V_a V_b^T of each step's two blocks and its transpose
 };
@@ -472,6 +472,29 @@ static int launch_chain_pipe(const ChainArgs& args, hipStream_t stream) {
   hipLaunchKernelGGL((chain_pipe_kernel<K, VW, NT, RL, SUB, P1, XB>), dim3(a.m + side), dim3(NT), 0, stream, a);
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;
+}
+
+}  // namespace fasth
+
+namespace fasth {
+
+// Workgroups b, b + 8, ... (one XCD) share out the teams of tiles b % 8, b % 8 + 8, ... in the order in which they START: the next
+// ticket is the next part of the next tile. So only the youngest team of an XCD can lack a part, whatever else runs on the GPU: all
+// others are complete, end, and make room for its missing parts. Whoever draws the last ticket puts the counter back for the
+// next launch (one counter per XCD, on a line of its own in the heads of the first eight tiles, which are cleared with the hand-off area).
+// All threads of the workgroup.
+constexpr int kTicketWord = 32;
+constexpr long long kStartPolls = 64;  // times the wait limit: a part that has not started waits for a compute unit, for which kernels of
+                                       // other streams may take their time
+__device__ __forceinline__ int draw_team_ticket(unsigned* xch, unsigned tile_words, int chain_wgs) {
+  __shared__ unsigned ticket;
+  if (threadIdx.x == 0) {
+    unsigned* counter = xch + (size_t)(blockIdx.x & 7u) * tile_words + kTicketWord;
+    ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ticket == (unsigned)chain_wgs / 8u - 1u) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane((int)ticket);
 }
 
 }  // namespace fasth

@@ -43,8 +43,9 @@ static_assert(8 * 32 * 68 == 8 * 64 * 34, "the rows of a step take the same room
 // NT = 2: parts of 256 elements, steps of 64 rows; p.sub = 0: the caller's blocks of 32 rows two per step, else steps per
 // block (1 or 2). NT = 4: parts of 512 elements, steps of 32 rows, p.sub = 1, 2 or 4 steps per block. LDT = 128 / NT: rows
 // of a stored factor, those of a step whatever the caller's block size (the diagonal blocks of a larger block's factor
-// are the factors of its row groups, so only those are built). The number of parts is p.parts.
-template <int NT, int LDT>
+// are the factors of its row groups, so only those are built). The number of parts is p.parts. TICKETS: teams form in the order in
+// which workgroups start (shared_tiles_overlap).
+template <int NT, int LDT, bool TICKETS>
 __global__ void __launch_bounds__(512) chain_team_tile_kernel(ChainArgs p) {
   const int NP = p.parts;  // 2 .. 4
   constexpr int K = 128 / NT, RT = K / 16, LD = NT == 2 ? 34 : 68, XW = 16 * NT, SLICE = 8 * XW, F = 4 * NT;
@@ -60,16 +61,18 @@ __global__ void __launch_bounds__(512) chain_team_tile_kernel(ChainArgs p) {
   float* Cs = Btot + 1024;                   // C in two shares (one per half of the inner index), [2][K][16] (second share at 1024)
   const int m = p.m, d = p.d, n = p.n;
   const int tiles = (m + kTtCols - 1) / kTtCols;
-  // workgroups b, b + 8, ... (one XCD) are the parts of tile 8 (b / (8 NP)) + b % 8
+  // workgroups b, b + 8, ... (one XCD) are the parts of tile 8 (b / (8 NP)) + b % 8, in the order of their indices or in
+  // that in which they start
   const int chain_wgs = 8 * NP * ((tiles + 7) / 8);
   if ((int)blockIdx.x >= chain_wgs) {  // the side product, on compute units the chain leaves idle
     const int row = ((int)blockIdx.x - chain_wgs) * 8 + wave;
     if (row < p.ds_rows) dsigma_row(p.in, p.ds_z1, p.in_scale, p.ds_out, row, m, p.in_scale_mode);
     return;
   }
-  const int part = (int)(blockIdx.x >> 3) % NP;
-  const int tile = (int)(blockIdx.x >> 3) / NP * 8 + (int)(blockIdx.x & 7);
-  if (tile >= tiles) return;
+  const int drawn = TICKETS ? draw_team_ticket(p.xch, team_tile_words(NP), chain_wgs) : (int)(blockIdx.x >> 3);
+  const int part = drawn % NP;
+  const int tile = drawn / NP * 8 + (int)(blockIdx.x & 7);
+  if ((unsigned)tile >= (unsigned)tiles) return;
   const int col = tile * kTtCols + i;
   const bool col_ok = col < m;
   const int x_w = part * SLICE + XW * wave;  // this wave's first element
@@ -192,12 +195,13 @@ __global__ void __launch_bounds__(512) chain_team_tile_kernel(ChainArgs p) {
   {
     unsigned peer_xcc = my_xcc;
     const unsigned hs_from = 32u + (unsigned)(lane < NP ? lane : part) * 8u;
-    int polls = 0;
+    const long long start_limit = (TICKETS ? kStartPolls : 1) * p.wait_limit;
+    long long polls = 0;
     for (;;) {
       const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(hdesc, hs_from, 0, 16);
       peer_xcc = w.x;
       if (__all(w.y == hs_tag)) break;
-      if (polls++ >= p.wait_limit) { gave_up = true; break; }
+      if (polls++ >= start_limit) { gave_up = true; break; }
       asm volatile("" ::: "memory");
     }
     same_xcd = !gave_up && __all(peer_xcc == my_xcc);
@@ -370,6 +374,7 @@ static int launch_chain_team_tile(const ChainArgs& args, hipStream_t stream) {
   ChainArgs a = args;
   a.parts = team_tile_parts(a.d, a.n, a.m, a.k);
   if (a.parts == 0 || !a.xch) return FASTH_EINVAL;
+  const bool tickets = shared_tiles_overlap(a.d, a.m);
   const bool longer = a.d > 1024;  // parts of 512 elements, steps of 32 rows
   // steps per block (0: two of the caller's blocks of 32 per step of 64 rows)
   a.sub = longer ? a.k / 32 : a.k == 32 ? 0 : a.k / 64;
@@ -377,18 +382,20 @@ static int launch_chain_team_tile(const ChainArgs& args, hipStream_t stream) {
   const int side = a.ds_out ? (a.ds_rows + 7) / 8 : 0;
   const int tiles = (a.m + kTtCols - 1) / kTtCols;
   const dim3 grid(8 * a.parts * ((tiles + 7) / 8) + side), block(512);
-#define FASTH_LAUNCH_TT(NT_, LDT_)                                                                                   \
+#define FASTH_LAUNCH_TT(NT_, LDT_, TK_)                                                                                   \
   do {                                                                                                               \
-    int rc_ = allow_lds(chain_team_tile_kernel<NT_, LDT_>, lds);                                                     \
+    int rc_ = allow_lds(chain_team_tile_kernel<NT_, LDT_, TK_>, lds);                                                     \
     if (rc_ != FASTH_OK) return rc_;                                                                                 \
-    static const std::string names_[3] = {variant_name("chain_team_tile_kernel", {NT_, LDT_}) + " (2 parts)",         \
-                                          variant_name("chain_team_tile_kernel", {NT_, LDT_}) + " (3 parts)",         \
-                                          variant_name("chain_team_tile_kernel", {NT_, LDT_}) + " (4 parts)"};        \
+    static const std::string names_[3] = {variant_name("chain_team_tile_kernel", {NT_, LDT_, TK_}) + " (2 parts)",         \
+                                          variant_name("chain_team_tile_kernel", {NT_, LDT_, TK_}) + " (3 parts)",         \
+                                          variant_name("chain_team_tile_kernel", {NT_, LDT_, TK_}) + " (4 parts)"};        \
     prof::Scope ps_(FASTH_KERNEL_CHAIN, stream, names_[a.parts - 2].c_str());                                        \
-    hipLaunchKernelGGL((chain_team_tile_kernel<NT_, LDT_>), grid, block, lds, stream, a);                            \
+    hipLaunchKernelGGL((chain_team_tile_kernel<NT_, LDT_, TK_>), grid, block, lds, stream, a);                            \
   } while (0)
-  if (!longer) FASTH_LAUNCH_TT(2, 64);
-  else FASTH_LAUNCH_TT(4, 32);
+  if (!longer && tickets) FASTH_LAUNCH_TT(2, 64, true);
+  else if (!longer) FASTH_LAUNCH_TT(2, 64, false);
+  else if (tickets) FASTH_LAUNCH_TT(4, 32, true);
+  else FASTH_LAUNCH_TT(4, 32, false);
 #undef FASTH_LAUNCH_TT
   FASTH_HIP(hipGetLastError());
   return FASTH_OK;

@@ -41,7 +41,6 @@ namespace fasth {
 // ------------------------------------------------------------------------------------------
 constexpr int kTrioOperand = 1024;                      // bytes of one operand
 constexpr int kTrioCell = 24 * kTrioOperand;            // bytes per 64 rows x 32 elements
-constexpr int kTrioTicketWord = 32;                     // of a tile's head, on a line of its own: the starting order of an XCD's workgroups
 
 struct TrioRowsArgs {
   const float* V;   // [n][d], the caller's
@@ -111,21 +110,9 @@ __global__ void __launch_bounds__(512) chain_trio_kernel(ChainArgs p) {
   }
   int part = 0, tile = (int)blockIdx.x;
   if constexpr (TEAM) {
-    // Workgroups b, b + 8, ... (one XCD) share out the teams of tiles b % 8, b % 8 + 8, ... in the order in which they START:
-    // the next ticket is the next part of the next tile. So only the youngest team of an XCD can lack a part, whatever else runs
-    // on the GPU: all others are complete, end, and make room for its missing parts. Whoever draws the last ticket puts
-    // the counter back for the next launch (one counter per XCD, in the heads of the first eight tiles).
-    __shared__ unsigned ticket;
-    const unsigned group = blockIdx.x & 7u;
-    if (tid == 0) {
-      unsigned* counter = p.xch + (size_t)group * trio_words(NP, CT) + kTrioTicketWord;
-      ticket = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (ticket == (unsigned)chain_wgs / 8u - 1u) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    const int drawn = __builtin_amdgcn_readfirstlane((int)ticket);
+    const int drawn = draw_team_ticket(p.xch, trio_words(NP, CT), chain_wgs);
     part = drawn % NP;
-    tile = drawn / NP * 8 + (int)group;
+    tile = drawn / NP * 8 + (int)(blockIdx.x & 7u);
     if ((unsigned)tile >= (unsigned)tiles) return;
   }
   const int col0 = tile * COLS + i;  // column tile ct: col0 + 16 ct
@@ -217,8 +204,7 @@ __global__ void __launch_bounds__(512) chain_trio_kernel(ChainArgs p) {
     }
     unsigned peer_xcc = my_xcc;
     const unsigned hs_from = 32u + (unsigned)(lane < NP ? lane : part) * 8u;
-    // a part that has not started waits for a compute unit, for which kernels of other streams may take their time
-    const long long start_limit = 64ll * p.wait_limit;
+    const long long start_limit = kStartPolls * p.wait_limit;
     long long polls = 0;
     for (;;) {
       const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(hdesc, hs_from, 0, 16);

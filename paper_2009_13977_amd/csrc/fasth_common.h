@@ -123,6 +123,10 @@ static int team_parts(int d, int n, int m, int k) {
 #ifndef FASTH_TEAM_TILE_MIN_COLS_SHORT
 #define FASTH_TEAM_TILE_MIN_COLS_SHORT 897  // d <= 512 (two parts)
 #endif
+// Mini-batches for which calls may overlap on the GPU although their tiles are shared by workgroups: beyond 1024 columns of more than
+// 512 elements, where kernels without hand-overs served before. Teams form in the order in which workgroups start there, and calls
+// that may overlap on one workspace take no teams.
+static bool shared_tiles_overlap(int d, int m) { return d > 512 && m > 1024; }
 constexpr unsigned team_tile_words(int np) { return (unsigned)(kTeamHeadBytes + np * 2 * np * 512 * 16) / 4u; }
 static int team_tile_parts(int d, int n, int m, int k) {
   if (m < (d > 1024 ? FASTH_TEAM_TILE_MIN_COLS_LONG : d > 512 ? FASTH_TEAM_TILE_MIN_COLS : FASTH_TEAM_TILE_MIN_COLS_SHORT) ||
@@ -323,9 +327,8 @@ static int steps_rows(int d, int n, int m, int k) {
   return team_parts(d, r64, m, k) || team_wide_parts(d, r64, m, k) ? r64 : own;
 }
 
-// shared = false: the layout without any kernel in which workgroups share columns (no hand-off area) and without the
-// padded copy of V (the caller's own block size), for a caller whose room is limited. Vectors too long for the
-// register-resident kernels keep the caller's block size too.
+// kLayoutPlain: the caller's own blocks, nothing shared and nothing padded: vectors too long for the register-resident kernels, and what
+// fasth_forward_static refuses by. kLayoutShared: without the operands of V for chain_trio_kernel.
 constexpr int kMaxPaddedD = 4096;
 enum LayoutLevel { kLayoutPlain, kLayoutShared, kLayoutTrio };
 static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayoutTrio) {

@@ -1,4 +1,4 @@
-"""Wide mini-batches (chain_trio_kernel) on two streams at a time. Calls on workspaces of their own may overlap although the
+"""Wide mini-batches (chain_trio_kernel, chain_team_tile_kernel beyond 1024 columns) on two streams at a time. Calls on workspaces of their own may overlap although the
 workgroups of a team wait for each other, and so may unsaved applies on one prepared workspace, which run
 without teams: every result is the one of the same call alone, bit for bit."""
 import pytest
@@ -9,8 +9,9 @@ from paper_2009_13977_amd import synthetic
 
 pytestmark = pytest.mark.gpu
 
-# two parts (16 and 32 columns per tile, the launch as large as the GPU or larger), three, two parts of 1024 elements, no team
-SHAPES = [(800, 128, 1040, 32), (1021, 200, 3000, 50), (1500, 130, 1100, 13), (2048, 193, 4096, 1), (512, 128, 2100, 32), (1030, 65, 4200, 13)]
+# two parts (16 and 32 columns per tile, the launch as large as the GPU or larger), three, two parts of 1024 elements, no team, no team;
+# tiles of 16 columns shared by three workgroups
+SHAPES = [(800, 128, 1040, 32), (1021, 200, 3000, 50), (1500, 130, 1100, 13), (2048, 193, 4096, 1), (512, 128, 2100, 32), (1030, 65, 4200, 13), (640, 200, 1280, 50), (1400, 64, 1100, 32)]
 
 
 def _two_streams():
