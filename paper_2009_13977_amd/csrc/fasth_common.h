@@ -147,7 +147,7 @@ static int team_tile_parts(int d, int n, int m, int k) {
 // matrix cores waiting for V: d = 1024, m = 4096: {4, 2} 647, {8, 1} 699, {8, 2} 833; d = 2048, m = 2048: {4, 2} 1242,
 // {8, 1} 1272, {8, 2} 1506.
 // Before (chain_tile_kernel, dv_kernel), us per forward + backward: d = 256, m = 4096: 118 -> 101; d = 512, m = 4096: 311 -> 184;
-// d = 1024, m = 1100: 481 -> 271, 2048: 574 -> 324, 4096: 751 -> 555; d = 2048, m = 1100: 1782 -> 935, 4096: 2651 -> 1995.
+// d = 1024, m = 1100: 481 -> 271, 2048: 574 -> 317, 4096: 751 -> 538; d = 2048, m = 1100: 1782 -> 935, 4096: 2651 -> 1995.
 // Few steps do not pay for the operands of V, and rounding n up to whole steps weighs more: us per forward + backward without and
 // with, d = 256, m = 1500: n = 96: 63, 69; n = 128: 71, 68; d = 640, m = 3000: n = 96: 80, 98; n = 128: 98, 105; n = 192: 136, 132;
 // d = 1024, m = 3000: n = 96: 91, 102; n = 112: 108, 103; d = 1280, m = 1500: n = 80: 89, 89; n = 112: 109, 90; with 1024 elements per
