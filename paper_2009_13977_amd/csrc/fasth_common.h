@@ -247,11 +247,12 @@ static bool factor_is_fused(int kp, int d) { return kp <= 32 || (kp == 64 && d <
 // of 32 and 64, d = 1024, m = 1000: n = 192 (25 MB): 94, 92; n = 256: 114, 107; d = 512, m = 1500: n = 384 (37 MB): 126, 122; n = 512:
 // 156, 140; d = 2048, m = 1000: n = 128 (33 MB): 142, 132; but m = 800: d = 512, n = 768: 173, 187; d = 640, n = 576: 135, 142.
 // Never where rounding n up to 64 adds a step of 32 that matters: d = 2048, m = 4096, n = 32: 114, 140; d = 3072, m = 800, n = 160: 281, 309;
-// n = 288: 416, 437; it matters least on the matrix cores: d = 2048, m = 1000, n = 288: 200, 173; m = 4096, n = 160: 311, 286.
+// n = 288: 416, 437; it matters least on the matrix cores: d = 2048, m = 1000, n = 288: 200, 173; m = 4096, n = 160: 311, 286
+// (d = 640, m = 2100, n = 160: 112, 129).
 constexpr double kManySavedBytes = 2e8, kManySavedBytesTiles = 2.5e7;
 static int padded_rows(int n, int multiple) { return (n + multiple - 1) / multiple * multiple; }
 static bool fills_64(int d, int n, int m) {
-  return n > 320 || padded_rows(n, 64) == padded_rows(n, 32) || (d <= 2048 && (m > 2048 ? n > 128 : m > 896 ? n > 192 : m > 768 && n > 256));
+  return n > 320 || padded_rows(n, 64) == padded_rows(n, 32) || (d <= 2048 && (m > 2048 && d > 1024 ? n > 128 : m > 896 ? n > 192 : m > 768 && n > 256));
 }
 static int inner_block(int d, int n, int m, int k) {
   const double saved = 4.0 * ((n + 31) / 32) * m * d;
@@ -277,7 +278,7 @@ constexpr int kMaxBlocks = 65535, kManyReflections = 64 * (kMaxBlocks / 2);
 // 1024: 32: (128: 29, 31), (192: 35, 37), (224: 38, 37); 300: (128: 51, 58), (320: 79, 82); 600: (80: 62, 67), (112: 69, 67);
 //       1000: (48: 69, 70), (64: 76, 71); 1500: (48: 73, 81), (64: 84, 81)
 // 1280: 64: (160: 38, 43), (192: 44, 43); 100: (192: 48, 51); 1100: (64: 88, 103)
-// 2048: 32: (112: 36, 37), (128: 38, 35); 300: (224: 119, 122), (256: 132, 132); 1000: (32: 115, 131), (48: 129, 132), (64: 145, 131)
+// 2048: 8: (96: 33, 34), (112: 38, 34); 32: (96: 34, 36), (128: 38, 35); 300: (224: 119, 122), (256: 132, 132); 1000: (32: 115, 131), (48: 129, 132), (64: 145, 131)
 // 4096: 32: (16: 32, 35), (24: 41, 38); 128: (256: 128, 131); 300: (192: 201, 203); 600: (128: 237, 239); 1500: (48: 361, 419), (64: 409, 382)
 // Short columns and few of them: a launch each whatever the blocks, and fewer steps with 32 rows (d = 64, m = 32, n = 64: 21.5, 20).
 constexpr int kFewRows = 16;
@@ -289,7 +290,7 @@ static bool few_reflections(int d, int n, int m) {
   if (m > 1024 && d > 2048) return n <= 16 || (n > 32 && n <= 48);
   if (m > 1024) return n <= (m > 1280 || d > 1536 ? 48 : d <= 768 ? 80 : d <= 1024 ? 48 : 64);
   if (d <= 1024) return n <= (m <= 256 ? 192 : m <= 480 ? 576 : m <= 768 ? 96 : d <= 896 ? 80 : 48);
-  if (d <= 2048) return n <= (m <= 64 ? (d <= 1536 ? 160 : 112) : m <= 128 ? (d <= 1536 ? 192 : 128) : m < 640 ? 256 : 48);
+  if (d <= 2048) return n <= (m <= 64 ? (d <= 1536 ? 160 : 96) : m <= 128 ? (d <= 1536 ? 192 : 128) : m < 640 ? 256 : 48);
   if (team_fits(m, (d + kTeamSlice - 1) / kTeamSlice)) return n <= (d <= 3072 ? 32 : 16);
   return n <= (m <= 256 ? 256 : m <= 512 ? 192 : 112);
 }
@@ -299,14 +300,14 @@ static bool few_reflections(int d, int n, int m) {
 // d = 64, m = 1100: n = 64: 35, 46 (tiles); n = 128: 44, 60; d = 256, m = 1100: n = 96: 55, 57.
 static bool fewest_rows(int d, int n, int m) {
   if ((n - 1) % 16 < 8) {
-    if (d > 2048) return n <= (m > 1024 ? 8 : team_fits(m, (d + kTeamSlice - 1) / kTeamSlice) ? 24 : 72);
+    if (d > 2048) return n <= (m > 1024 ? 8 : team_fits(m, (d + kTeamSlice - 1) / kTeamSlice) ? 24 : m <= 300 ? 72 : 40);
     if (n <= 40) return m <= 1024 || (d <= 256 && m <= 1280);
   }
   if (d > 1024 && d <= 2048 && m > 256 && m <= 1024) return n <= (m > 480 ? 48 : d <= 1280 ? 360 : d <= 1536 ? 160 : 120);
   return d <= 256 && m > 1024 && (d <= 128 ? m <= 1536 && n <= 256 : m <= 1280 && n <= 128);
 }
 // Vectors of more than 2048 elements take steps of 8 rows, so blocks of 24 save padding: us with blocks of 24 and of 16 or 32: d = 3072,
-// m = 300: n = 24: 80, 86; n = 72: 102, 116; n = 360: 259, 271.
+// m = 300: n = 24: 80, 86; n = 72: 102, 116; n = 360: 259, 271; but their factors cost more than those of 16: m = 32, n = 20: 40, 33.
 static int least_padding(int d, int n, int rows) {
   return d > 2048 && 25 * padded_rows(n, 24) <= 24 * padded_rows(n, rows) ? 24 : rows;
 }
@@ -356,7 +357,7 @@ static Layout make_layout(int d, int n, int m, int k, LayoutLevel level = kLayou
     L.ki = bounded_block(d4, n, m, k, L.ki);
     L.np = L.ki <= kFewRows ? padded_rows(n, L.ki) : steps_rows(d4, n, m, L.ki);
     // (no kernel with shared columns: those have taken whole steps)
-    if ((L.ki == kFewRows || L.ki == 32) && !team_parts(d4, L.np, m, L.ki) && least_padding(d4, n, L.ki) == 24) {
+    if ((L.ki == 32 || (L.ki == kFewRows && m > 256)) && !team_parts(d4, L.np, m, L.ki) && least_padding(d4, n, L.ki) == 24) {
       L.ki = 24;
       L.np = padded_rows(n, 24);
     }
