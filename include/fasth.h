@@ -54,7 +54,9 @@ enum {
  * reflections), and for d <= 4096 the library regroups them into blocks of its
  * own, 32 or 64 rows (8, 16 or 24 for few reflections in small blocks, k < 32),
  * padding the last one. A larger k still bounds the memory: where blocks of 32 or
- * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. */
+ * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. Wide
+ * mini-batches (more than 1280 columns of vectors of more than 512 elements, 768 of 448 to
+ * 512, with n near d) multiply by the whole H as one matrix, in any k's place. */
 typedef struct fasth_shape {
   int d;          /* length of each Householder vector = rows of X */
   int n;          /* number of reflections = rows of V */
@@ -95,7 +97,7 @@ const char* fasth_strerror(int code);
  * fasth_apply without saving. These teams form in the order in which their workgroups start, so they need nothing of
  * what else the GPU runs: such calls may overlap with any others on other streams (a part that has not started is
  * waited for 64 times as long). fasth_apply without saving runs these shapes without teams, and any number of such calls may
- * overlap on one prepared workspace. */
+ * overlap on one prepared workspace. Where H is one matrix (see fasth_shape) nothing waits inside a kernel, and the same holds. */
 int fasth_wait_status(void* stream);
 int fasth_set_wait_limit(int polls);
 
@@ -106,7 +108,8 @@ int fasth_set_wait_limit(int polls);
  * mini-batch, partial sums of dV; where d is no multiple of 4 or n no multiple
  * of the library's blocks, a padded copy of V; for more than 1024 columns of up to
  * 2048 elements a copy of V as operands of the matrix cores, 12 bytes per
- * element). Returns 0 if the shape is invalid or unsupported. */
+ * element; where H is one matrix, H and some more matrices of its size, and X and
+ * dL/dX as operands, 6 bytes per element, in the place of all saved inputs). Returns 0 if the shape is invalid or unsupported. */
 size_t fasth_workspace_bytes(const fasth_shape* shape);
 
 /* Algorithm 1. A = H X (or H^T X). Step 1 builds, for every block i, the
@@ -122,7 +125,8 @@ int fasth_forward(const fasth_shape* shape, const float* V, const float* X, floa
  * once; fasth_apply runs Step 2 only and may be called any number of times, with any X of the
  * shape's size, while V and the workspace are unchanged. With save_for_backward != 0 it also saves
  * the block inputs, so fasth_prepare + fasth_apply(save) is exactly fasth_forward; with 0 nothing
- * but A is written (inference). */
+ * but A is written (inference). Where H is one matrix (see fasth_shape) fasth_prepare forms it, and an
+ * apply is one product: the former takes longer and the latter less than with block factors. */
 int fasth_prepare(const fasth_shape* shape, const float* V, void* workspace, size_t workspace_bytes,
                   void* stream);
 int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float* A,

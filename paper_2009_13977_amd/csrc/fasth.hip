@@ -18,11 +18,13 @@
 //                        per workgroup or team on the matrix cores (quad, tile, team_tile, trio)
 //   trio_rows_kernel     the rows of V as operands of chain_trio_kernel, part of Step 1
 //   dv_*                 Algorithm 2 Step 2 as dense products per block (MFMA)
+//   gemm_kernel, pack_kernel, block_factor_kernel, block_inverse_kernel, skew_kernel
+//                        wide mini-batches: H as one matrix, and Algorithms 1 and 2 as products with it (MFMA)
 //   seq_*                the one-reflection-at-a-time comparison
 //   dsigma_kernel        the diagonal step of the SVD layer
 // The kernels live in fasth_factor.h, fasth_chain.h (+ fasth_chain_team.h, fasth_chain_pair.h, fasth_chain_quad.h,
-// fasth_chain_tile.h, fasth_chain_trio.h, fasth_chain_teamtile.h), fasth_dv.h and fasth_sequential.h (helpers in fasth_common.h and fasth_device.h); this file holds
-// the host drivers and the C entry points.
+// fasth_chain_tile.h, fasth_chain_trio.h, fasth_chain_teamtile.h), fasth_dv.h, fasth_dense.h (+ fasth_gemm.h) and fasth_sequential.h (helpers in fasth_common.h and
+// fasth_device.h); this file holds the host drivers and the C entry points.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,6 +42,7 @@
 #include "fasth_factor.h"
 #include "fasth_chain.h"
 #include "fasth_dv.h"
+#include "fasth_dense.h"
 #include "fasth_sequential.h"
 #include "fasth_peaks.h"
 
@@ -61,6 +64,8 @@ struct Product {  // one Householder product bound to its slice of a workspace
   // Calls on this workspace never overlap on the GPU: they save into it, or the header says so for the shape. Cleared by
   // fasth_apply without saving, whose calls may overlap except for the header's list of shapes.
   bool exclusive = true;
+  bool dense = false;  // the whole matrix instead of the chain of blocks: the workspace is D's
+  Dense D;
   // the rows the kernels read: the caller's, or the padded copy the factor kernels leave in the workspace
   const float* rows(const float* V) const { return L.copy_v ? reinterpret_cast<const float*>(ws + L.off_V) : V; }
   float* copy() const { return L.copy_v ? reinterpret_cast<float*>(ws + L.off_V) : nullptr; }
@@ -74,13 +79,21 @@ struct Product {  // one Householder product bound to its slice of a workspace
   float* saveCg() const { return reinterpret_cast<float*>(ws + L.off_saveCg); }
 };
 
-static Product bind(int d, int n, int m, int k, void* ws, LayoutLevel level = kLayoutTrio) {
+static Product bind(int d, int n, int m, int k, void* ws, bool dense = false, LayoutLevel level = kLayoutTrio) {
   Product P;
   P.d = d; P.n = n; P.m = m; P.k = k;
-  P.L = make_layout(d, n, m, k, level);
   P.ws = static_cast<char*>(ws);
+  P.dense = dense;
+  if (!dense) {
+    P.L = make_layout(d, n, m, k, level);
+    return P;
+  }
+  P.D.d = d; P.D.n = n; P.D.m = m; P.D.ws = P.ws;
+  P.D.L = make_dense_layout(d, n, m);
   return P;
 }
+static size_t workspace_of(const Product& P) { return P.dense ? P.D.L.total : P.L.total; }
+static size_t workspace_of(int d, int n, int m, int k, bool dense) { return workspace_of(bind(d, n, m, k, nullptr, dense)); }
 
 static int launch_factor_fused(const FactorPair& fp, int count, int kp, bool vec4, hipStream_t stream) {
   static const std::string names[6] = {variant_name("factor_fused_kernel", {1, 4}), variant_name("factor_fused_kernel", {2, 4}),
@@ -366,18 +379,69 @@ static int seq_threads(int d) {
 }
 
 struct SvdLayout {
-  size_t off_U, off_V, off_Z1, off_dZ2, total;
+  bool dense;
+  size_t off_U, off_V, off_Z1, off_dZ2, off_scaled, total;
 };
 
 static SvdLayout make_svd_layout(int d, int n, int m, int k) {
   SvdLayout S;
-  const size_t one = make_layout(d, n, m, k).total;
+  S.dense = dense_serves(d, n, m);
+  const size_t one = workspace_of(d, n, m, k, S.dense);
+  const size_t dm = align_up((size_t)d * m * sizeof(float), 256);
   S.off_U = 0;
   S.off_V = align_up(one, 256);
   S.off_Z1 = S.off_V + align_up(one, 256);
-  S.off_dZ2 = S.off_Z1 + align_up((size_t)d * m * sizeof(float), 256);
-  S.total = S.off_dZ2 + align_up((size_t)d * m * sizeof(float), 256);
+  S.off_dZ2 = S.off_Z1 + dm;
+  S.off_scaled = S.off_dZ2 + dm;  // the second product's inputs, scaled
+  S.total = S.off_scaled + (S.dense ? dm : 0);
   return S;
+}
+
+// The layers on whole matrices: in the notation below, `first` is the factor applied transposed. Z1 = F^T X, Y = S (s Z1).
+static int dense_layer_forward(Dense& F, const float* Vf, Dense& S, const float* Vs, const float* X, float* Z1, float* scaled, const float* sigma,
+                               int mode, int rank, float* Y, hipStream_t st) {
+  F.lower = true;
+  const bool shared = S.owner == &F;  // one set of factors: Y' and H^T, then Y
+  const Dense* D[2] = {&F, &S};
+  const float* V[2] = {Vf, Vs};
+  const PackJob jobs[1] = {F.pack_x(X, F.d)};
+  int rc = dense_factors(D, V, shared ? 1 : 2, jobs, 1, st);
+  if (rc != FASTH_OK || (rc = dense_matrices(D, V, shared ? 1 : 2, true, st)) != FASTH_OK) return rc;
+  if (shared) {
+    Dense plain = F;
+    plain.lower = false;
+    const Dense* one[1] = {&plain};
+    if ((rc = dense_matrices(one, V, 1, false, st)) != FASTH_OK) return rc;
+  }
+  if ((rc = dense_apply(F, true, X, F.d, Z1, sigma, mode, rank, scaled, nullptr, st)) != FASTH_OK) return rc;
+  PackArgs pk{};
+  pk.job[0] = S.pack_x(scaled, rank);
+  if ((rc = launch_pack(pk, 1, FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+  return dense_apply(S, false, scaled, rank, Y, nullptr, 0, 0, nullptr, nullptr, st);
+}
+
+static int dense_layer_backward(Dense& F, const float* Vf, Dense& S, const float* Vs, const float* G, const float* Z1, float* dZ2, float* scaled,
+                                const float* sigma, int mode, int rank, float* dVf, float* dsigma, float* dVs, float* dX, hipStream_t st) {
+  F.lower = true;
+  const bool shared = S.owner == &F;
+  int rc = dense_apply(S, true, G, S.d, dZ2, sigma, mode, rank, scaled, S.at(S.L.dXa), st);
+  if (rc != FASTH_OK) return rc;
+  if ((rc = dense_apply(F, false, scaled, rank, dX, nullptr, 0, 0, nullptr, F.at(F.L.dXa), st)) != FASTH_OK) return rc;
+  {
+    prof::Scope ps_(FASTH_KERNEL_DSIGMA, st, "dsigma_kernel");
+    hipLaunchKernelGGL(dsigma_kernel, dim3((rank + 3) / 4), dim3(256), 0, st, (const float*)dZ2, Z1, sigma, dsigma, rank, S.m, mode);
+    FASTH_HIP(hipGetLastError());
+  }
+  if (!shared) {
+    const Dense* D[2] = {&S, &F};
+    const float* V[2] = {Vs, Vf};
+    float* dV[2] = {dVs, dVf};
+    return dense_dv(D, V, dV, 2, false, st);
+  }
+  const Dense* D[2] = {&S, &F};
+  for (int i = 0; i < 2; ++i)  // both products' gradients are those of the same vectors: the second is added
+    if ((rc = dense_dv(D + i, &Vf, &dVf, 1, i == 1, st)) != FASTH_OK) return rc;
+  return FASTH_OK;
 }
 
 static int check_svd_shape(const fasth_svd_shape* s, fasth_shape* out) {
@@ -401,9 +465,11 @@ static int svd_forward(const fasth_svd_shape* shape, const float* first, const f
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   // "first" is the factor applied transposed (V for W, U for W^-1); it owns slot off_V.
-  const Product Pf = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V);
-  const Product Ps = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U);
+  Product Pf = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V, S.dense);
+  Product Ps = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U, S.dense);
   float* Z1 = reinterpret_cast<float*>(ws + S.off_Z1);
+  if (S.dense)
+    return dense_layer_forward(Pf.D, first, Ps.D, second, X, Z1, reinterpret_cast<float*>(ws + S.off_scaled), sigma, scale_mode, fs.d, Y, st);
   if ((rc = build_factors_pair(Pf, first, Ps, second, st)) != FASTH_OK) return rc;
   if ((rc = run_chain(Pf, first, X, Z1, 1, true, nullptr, 0, st)) != FASTH_OK) return rc;
   return run_chain(Ps, second, Z1, Y, 0, true, sigma, scale_mode, st);
@@ -423,10 +489,13 @@ static int svd_backward(const fasth_svd_shape* shape, const float* first, const 
   if (workspace_bytes < S.total) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  const Product Pf = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V);
-  const Product Ps = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U);
+  Product Pf = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V, S.dense);
+  Product Ps = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U, S.dense);
   const float* Z1 = reinterpret_cast<const float*>(ws + S.off_Z1);
   float* dZ2 = reinterpret_cast<float*>(ws + S.off_dZ2);
+  if (S.dense)
+    return dense_layer_backward(Pf.D, first, Ps.D, second, G, Z1, dZ2, reinterpret_cast<float*>(ws + S.off_scaled), sigma, scale_mode, fs.d,
+                                dfirst, dsigma, dsecond, dX, st);
   // through the second (plain) factor
   if ((rc = run_chain(Ps, second, G, dZ2, 1, false, nullptr, 0, st)) != FASTH_OK) return rc;
   // through the first (transposed) factor; dZ1 = s * dZ2 is fused into the chain's load, and the gradient of
@@ -450,7 +519,8 @@ static int sym_scale_mode(int function) {
 // Rectangular layer (Section 3.3 "Rectangular Matrices"): U is rows x rows, V is cols x cols and
 // Sigma is rows x cols with min(rows, cols) diagonal entries.
 struct RectLayout {
-  size_t off_U, off_V, off_Z1, off_dZ2, total;
+  bool dense;
+  size_t off_U, off_V, off_Z1, off_dZ2, off_scaled, total;
 };
 
 static int check_rect_shape(const fasth_rect_shape* s, fasth_shape* u, fasth_shape* v) {
@@ -463,11 +533,13 @@ static int check_rect_shape(const fasth_rect_shape* s, fasth_shape* u, fasth_sha
 
 static RectLayout make_rect_layout(const fasth_shape& u, const fasth_shape& v) {
   RectLayout S;
+  S.dense = dense_serves(u.d, u.n, u.m) && dense_serves(v.d, v.n, v.m);
   S.off_U = 0;
-  S.off_V = align_up(make_layout(u.d, u.n, u.m, u.k).total, 256);
-  S.off_Z1 = S.off_V + align_up(make_layout(v.d, v.n, v.m, v.k).total, 256);
+  S.off_V = align_up(workspace_of(u.d, u.n, u.m, u.k, S.dense), 256);
+  S.off_Z1 = S.off_V + align_up(workspace_of(v.d, v.n, v.m, v.k, S.dense), 256);
   S.off_dZ2 = S.off_Z1 + align_up((size_t)v.d * v.m * sizeof(float), 256);
-  S.total = S.off_dZ2 + align_up((size_t)u.d * u.m * sizeof(float), 256);
+  S.off_scaled = S.off_dZ2 + align_up((size_t)u.d * u.m * sizeof(float), 256);
+  S.total = S.off_scaled + (S.dense ? align_up((size_t)std::min(u.d, v.d) * u.m * sizeof(float), 256) : 0);
   return S;
 }
 
@@ -624,7 +696,7 @@ int fasth_measure_peaks(void* buffer, size_t buffer_bytes, int repetitions, floa
 
 size_t fasth_workspace_bytes(const fasth_shape* shape) {
   if (check_shape(shape) != FASTH_OK) return 0;
-  return make_layout(shape->d, shape->n, shape->m, shape->k).total;
+  return workspace_of(shape->d, shape->n, shape->m, shape->k, dense_serves(shape->d, shape->n, shape->m));
 }
 
 int fasth_forward(const fasth_shape* shape, const float* V, const float* X, float* A, void* workspace,
@@ -633,9 +705,17 @@ int fasth_forward(const fasth_shape* shape, const float* V, const float* X, floa
   if (rc != FASTH_OK) return rc;
   if (!V || !X || !A || !workspace) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(X) || !aligned16(A) || !aligned16(workspace)) return FASTH_EALIGN;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
-  if (workspace_bytes < P.L.total) return FASTH_EWORKSPACE;
+  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace, dense_serves(shape->d, shape->n, shape->m));
+  if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (P.dense) {
+    Dense D = P.D;
+    D.lower = shape->transpose != 0;
+    const Dense* list[1] = {&D};
+    const PackJob jobs[1] = {D.pack_x(X, P.d)};
+    if ((rc = dense_factors(list, &V, 1, jobs, 1, st)) != FASTH_OK || (rc = dense_matrices(list, &V, 1, true, st)) != FASTH_OK) return rc;
+    return dense_apply(D, shape->transpose != 0, X, P.d, A, nullptr, 0, 0, nullptr, nullptr, st);
+  }
   if ((rc = build_factors(P, V, st)) != FASTH_OK) return rc;
   return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st);
 }
@@ -671,7 +751,7 @@ int fasth_forward_static(const fasth_shape* shape, const float* V, const float* 
   const int segments = (n + rows - 1) / rows;
   for (int i = 0; i < segments; ++i) {
     const int first = (shape->transpose ? i : segments - 1 - i) * rows;
-    const Product P = bind(d, std::min(rows, n - first), m, k, ws, level);
+    const Product P = bind(d, std::min(rows, n - first), m, k, ws, false, level);
     const float* Vs = V + (size_t)first * d;
     if ((rc = build_factors(P, Vs, st)) != FASTH_OK) return rc;
     if ((rc = run_chain(P, Vs, i == 0 ? X : A, A, shape->transpose, true, nullptr, 0, st, false)) != FASTH_OK) return rc;
@@ -684,9 +764,15 @@ int fasth_prepare(const fasth_shape* shape, const float* V, void* workspace, siz
   if (rc != FASTH_OK) return rc;
   if (!V || !workspace) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(workspace)) return FASTH_EALIGN;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
-  if (workspace_bytes < P.L.total) return FASTH_EWORKSPACE;
-  return build_factors(P, V, static_cast<hipStream_t>(stream));
+  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace, dense_serves(shape->d, shape->n, shape->m));
+  if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (P.dense) {
+    const Dense* D[1] = {&P.D};
+    if ((rc = dense_factors(D, &V, 1, nullptr, 0, st)) != FASTH_OK) return rc;
+    return dense_matrices(D, &V, 1, true, st);
+  }
+  return build_factors(P, V, st);
 }
 
 int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float* A, void* workspace,
@@ -695,11 +781,23 @@ int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float*
   if (rc != FASTH_OK) return rc;
   if (!V || !X || !A || !workspace) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(X) || !aligned16(A) || !aligned16(workspace)) return FASTH_EALIGN;
-  Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
-  if (workspace_bytes < P.L.total) return FASTH_EWORKSPACE;
+  Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace, dense_serves(shape->d, shape->n, shape->m));
+  if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (P.dense && save_for_backward) {
+    PackArgs pk{};
+    pk.job[0] = P.D.pack_x(X, P.d);
+    if ((rc = launch_pack(pk, 1, FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+    if (shape->transpose) {  // fasth_prepare leaves Y; the gradients of this product need Y'
+      Dense D = P.D;
+      D.lower = true;
+      const Dense* list[1] = {&D};
+      if ((rc = dense_matrices(list, &V, 1, false, st)) != FASTH_OK) return rc;
+    }
+  }
+  if (P.dense) return dense_apply(P.D, shape->transpose != 0, X, P.d, A, nullptr, 0, 0, nullptr, nullptr, st);
   P.exclusive = save_for_backward != 0;
-  return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, static_cast<hipStream_t>(stream),
-                   save_for_backward != 0);
+  return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st, save_for_backward != 0);
 }
 
 int fasth_backward(const fasth_shape* shape, const float* V, const float* G, float* dV, float* dX, void* workspace,
@@ -708,9 +806,16 @@ int fasth_backward(const fasth_shape* shape, const float* V, const float* G, flo
   if (rc != FASTH_OK) return rc;
   if (!V || !G || !dV || !dX || !workspace) return FASTH_EINVAL;
   if (!aligned16(V) || !aligned16(G) || !aligned16(dV) || !aligned16(dX) || !aligned16(workspace)) return FASTH_EALIGN;
-  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace);
-  if (workspace_bytes < P.L.total) return FASTH_EWORKSPACE;
+  const Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace, dense_serves(shape->d, shape->n, shape->m));
+  if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (P.dense) {
+    Dense D = P.D;
+    D.lower = shape->transpose != 0;
+    const Dense* list[1] = {&D};
+    if ((rc = dense_apply(D, !shape->transpose, G, P.d, dX, nullptr, 0, 0, nullptr, D.at(D.L.dXa), st)) != FASTH_OK) return rc;
+    return dense_dv(list, &V, &dV, 1, false, st);
+  }
   if ((rc = run_chain(P, V, G, dX, !shape->transpose, false, nullptr, 0, st)) != FASTH_OK) return rc;
   return run_dv(P, V, dV, shape->transpose, st);
 }
@@ -745,6 +850,7 @@ int fasth_tune_block_size(const fasth_shape* shape, const int* candidates, int n
     s.k = k;
     if (check_shape(&s) != FASTH_OK || fasth_workspace_bytes(&s) > workspace_bytes) continue;  // not a usable candidate
     // the library's blocks decide what runs: a candidate that leads to the same ones has been tried (its first stands for all)
+    if (dense_serves(s.d, s.n, s.m) && found) break;  // no blocks
     const Layout L = make_layout(s.d, s.n, s.m, k);
     if (std::any_of(tried.begin(), tried.end(), [&](const Layout& t) { return t.ki == L.ki && t.np == L.np && t.trio.parts == L.trio.parts; }))
       continue;
@@ -863,9 +969,13 @@ int svd_sym_apply(const fasth_svd_shape* shape, int function, const float* Uv, c
   if (workspace_bytes < S.total) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  const Product Pin = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V);   // U^T X; owns the factors
-  const Product Pout = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U);  // U (s * Z1); saves only
+  Product Pin = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V, S.dense);   // U^T X; owns the factors
+  Product Pout = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U, S.dense);  // U (s * Z1); saves only
   float* Z1 = reinterpret_cast<float*>(ws + S.off_Z1);
+  if (S.dense) {
+    Pout.D.owner = &Pin.D;
+    return dense_layer_forward(Pin.D, Uv, Pout.D, Uv, X, Z1, reinterpret_cast<float*>(ws + S.off_scaled), sigma, mode, fs.d, Y, st);
+  }
   if ((rc = build_factors(Pin, Uv, st)) != FASTH_OK) return rc;
   if ((rc = run_chain(Pin, Uv, X, Z1, 1, true, nullptr, 0, st)) != FASTH_OK) return rc;
   return run_chain(Pout, Uv, Z1, Y, 0, true, sigma, mode, st, true, &Pin);
@@ -886,10 +996,15 @@ int svd_sym_apply_backward(const fasth_svd_shape* shape, int function, const flo
   if (workspace_bytes < S.total) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  const Product Pin = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V);
-  const Product Pout = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U);
+  Product Pin = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_V, S.dense);
+  Product Pout = bind(fs.d, fs.n, fs.m, fs.k, ws + S.off_U, S.dense);
   const float* Z1 = reinterpret_cast<const float*>(ws + S.off_Z1);
   float* dZ2 = reinterpret_cast<float*>(ws + S.off_dZ2);
+  if (S.dense) {
+    Pout.D.owner = &Pin.D;
+    return dense_layer_backward(Pin.D, Uv, Pout.D, Uv, G, Z1, dZ2, reinterpret_cast<float*>(ws + S.off_scaled), sigma, mode, fs.d, dUv, dsigma,
+                                dUv, dX, st);
+  }
   if ((rc = run_chain(Pout, Uv, G, dZ2, 1, false, nullptr, 0, st, true, &Pin)) != FASTH_OK) return rc;
   if ((rc = run_dv(Pout, Uv, dUv, 0, st, false, &Pin)) != FASTH_OK) return rc;
   if ((rc = run_chain(Pin, Uv, dZ2, dX, 0, false, sigma, mode, st, true, nullptr, -1, Z1, dsigma, fs.d)) != FASTH_OK)
@@ -946,10 +1061,11 @@ int svd_rect_apply(const fasth_rect_shape* shape, const float* Uv, const float* 
   if (workspace_bytes < S.total) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  const Product Pu = bind(fu.d, fu.n, fu.m, fu.k, ws + S.off_U);
-  const Product Pv = bind(fv.d, fv.n, fv.m, fv.k, ws + S.off_V);
+  Product Pu = bind(fu.d, fu.n, fu.m, fu.k, ws + S.off_U, S.dense);
+  Product Pv = bind(fv.d, fv.n, fv.m, fv.k, ws + S.off_V, S.dense);
   float* Z1 = reinterpret_cast<float*>(ws + S.off_Z1);
   const int r = fu.d < fv.d ? fu.d : fv.d;
+  if (S.dense) return dense_layer_forward(Pv.D, Vv, Pu.D, Uv, X, Z1, reinterpret_cast<float*>(ws + S.off_scaled), sigma, 1, r, Y, st);
   if ((rc = build_factors_pair(Pv, Vv, Pu, Uv, st)) != FASTH_OK) return rc;
   if ((rc = run_chain(Pv, Vv, X, Z1, 1, true, nullptr, 0, st)) != FASTH_OK) return rc;
   // Sigma Z1: the first r rows of Z1 scaled by sigma, rows r..rows-1 zero; fused into the chain's load
@@ -970,11 +1086,13 @@ int svd_rect_apply_backward(const fasth_rect_shape* shape, const float* Uv, cons
   if (workspace_bytes < S.total) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  const Product Pu = bind(fu.d, fu.n, fu.m, fu.k, ws + S.off_U);
-  const Product Pv = bind(fv.d, fv.n, fv.m, fv.k, ws + S.off_V);
+  Product Pu = bind(fu.d, fu.n, fu.m, fu.k, ws + S.off_U, S.dense);
+  Product Pv = bind(fv.d, fv.n, fv.m, fv.k, ws + S.off_V, S.dense);
   const float* Z1 = reinterpret_cast<const float*>(ws + S.off_Z1);
   float* dZ2 = reinterpret_cast<float*>(ws + S.off_dZ2);
   const int r = fu.d < fv.d ? fu.d : fv.d;
+  if (S.dense)
+    return dense_layer_backward(Pv.D, Vv, Pu.D, Uv, G, Z1, dZ2, reinterpret_cast<float*>(ws + S.off_scaled), sigma, 1, r, dVv, dsigma, dUv, dX, st);
   if ((rc = run_chain(Pu, Uv, G, dZ2, 1, false, nullptr, 0, st)) != FASTH_OK) return rc;
   // Sigma^T dZ2: first r rows scaled, rows r..cols-1 zero
   if ((rc = run_chain(Pv, Vv, dZ2, dX, 0, false, sigma, 1, st, true, nullptr, r, Z1, dsigma, r)) != FASTH_OK) return rc;

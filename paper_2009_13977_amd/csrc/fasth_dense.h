@@ -1,0 +1,541 @@
+// The product of all reflections as one matrix, for wide mini-batches.
+// Included by fasth.hip after the chain and dV kernels.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "fasth_common.h"
+#include "fasth_gemm.h"
+
+namespace fasth {
+
+// ------------------------------------------------------------------------------------------
+// All n reflections are one WY block (Lemma 1 with k = n): with S = V V^T and T = (diag(S) / 2 + striu(S))^-1,
+//   H = I - V^T T V = I - V^T Y,   Y = T V,     H^T = I - V^T T^T V.
+// T is formed for groups of 256 reflections only. With P = H_(g+1) ... H_G the product of the groups applied before group g, the rows
+// of Y that belong to it are Y_g = T_g V_g P, and P - V_g^T Y_g is the product with it: from P = I to P = H. (All of T, by doubling
+// blocks, is as much work, and H is less exact: at n = d = 1024 its error is 4.2e-7, 2.0e-7 of it from the rounding of S beyond the groups
+// and 2.7e-7 from that of T.) Errors of A, dV and dX, n = d = 1024, normal V: 2.7e-7, 4.2e-7, 2.7e-7 (chain of blocks of 64: 4.5e-7, 5.1e-7, 4.1e-7);
+// with rows that are far from orthogonal the size of the group counts: one direction plus 0.3 times normal rows: 3.1e-6, 8.3e-6, 3.1e-6 (3.4e-6,
+// 6.3e-6, 3.0e-6), at d = 512 3.4e-6, 9.0e-6, 3.4e-6 (blocks of 32: 2.0e-6, 4.1e-6, 2.0e-6).
+// The chain of blocks costs 12 d n m operations per gradient step, one block after the other. As matrices a step costs 6 d^2 m and a
+// part that does not depend on m:
+//   forward   A = H X
+//   backward  dX = H^T G,   Q = dX X^T,   K = (Q - Q^T) / 2,   W = Y K,   dV = 2 (W - striu(W Y^T) V)
+// The gradient with respect to H is D = G X^T, and dL = <D, dH> = <H^T D, H^T dH> = <Q, H^T dH>. H stays orthogonal, so H^T dH is
+// skew-symmetric and only the skew part K of Q counts: D may be replaced by H K. Differentiating H = I - V^T T V gives
+//   dV = -(Y D^T + Y' D) + E V,   Y' = T^T V,   E = U + U^T + diag(Z),   Z = Y' D Y^T,   U = striu(Z),
+// and V H = -T^-T Y, i.e. Y = -Y' H and Y' = -Y H^T, turns it for D = H K into Z = -W Y^T with W = Y K (skew, as K is), Y' D = -W and
+// Y D^T = -W H^T = -W + W V^T T^T V = -W - Z V, so that dV = 2 W + (E + Z) V = 2 W + 2 U V.
+// For A = H^T X the same holds with T^T in the place of T (lower triangular: stril in the place of striu).
+// All products are three-piece bf16 products (fasth_gemm.h): fp32 in, fp32 out, fp32 accumulators.
+// ------------------------------------------------------------------------------------------
+
+constexpr int kGroup = 256;  // reflections that share a T
+
+// The factors of 64 rows, (diag(S_bb) / 2 + striu(S_bb))^-1; a row that does not exist has a one on the diagonal. Bound by the steps of the
+// inversion, one after the other: 5 us for any number of blocks up to one per compute unit.
+struct FactorArgs64 {
+  const float* S;  // [np][256]
+  float* factor;   // [np / 64][64][64]
+  int n, np;
+};
+struct FactorPair64 {
+  FactorArgs64 a[2];  // blockIdx.y
+};
+__global__ void __launch_bounds__(512) block_factor_kernel(FactorPair64 pair) {
+  constexpr int LD = 68;
+  __shared__ __align__(16) float M[64 * LD + invert_scratch_floats(64)];
+  const FactorArgs64& p = pair.a[blockIdx.y];
+  const int r0 = (int)blockIdx.x * 64, tid = threadIdx.x;
+  if (r0 >= p.np) return;  // whole workgroup
+  float* Xs = M + 64 * LD;
+  float s[8];
+#pragma unroll
+  for (int it = 0; it < 8; ++it) s[it] = p.S[(size_t)(r0 + (tid >> 6) + 8 * it) * kGroup + r0 % kGroup + (tid & 63)];
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int r = (tid >> 6) + 8 * it, c = tid & 63;
+    const float v = r0 + r >= p.n || r0 + c >= p.n ? (r == c ? 1.f : 0.f) : r < c ? s[it] : r == c ? 0.5f * s[it] : 0.f;
+    M[r * LD + c] = v;
+    diag_scratch_store(Xs, 64, r, c, v);
+  }
+  __syncthreads();
+  invert_upper_lds<true>(M, Xs, 64, LD);
+#pragma unroll
+  for (int it = 0; it < 8; ++it) p.factor[(size_t)r0 * 64 + tid + 512 * it] = M[((tid >> 6) + 8 * it) * LD + (tid & 63)];
+}
+
+// T of 256 rows from the factors of its blocks of 64 rows, as operands: block back substitution on 16 columns per workgroup,
+//   X_c = T_cc E,   X_b = -T_bb (sum over b < j <= c of S_bj X_j),
+// with fp64 matrix instructions (in fp32, 6 us less, its sums cost as much accuracy as all the other products of H together); wave w takes rows
+// 16 w ... of every block. All of S and T that a wave reads is fetched before the first product, one trip to memory. The blocks below the
+// diagonal are written as zeros. Bound by the chain of six products of the last block column, 13 us for any number of groups up to 16.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+struct InverseArgs {
+  const float* S;       // [np][256]: a group's rows against its rows, the blocks of 64 x 64 on and above the diagonal
+  const float* factor;  // [np / 64][64][64]
+  char* T;              // the groups' T as operands, rows stay rows (np x 256)
+  char* Tt;             // their transposes
+  int np;
+};
+struct InversePair {
+  InverseArgs a[2];     // blockIdx.y
+};
+
+template <int C>
+__device__ __forceinline__ void inverse_panel(const InverseArgs& p, int b0, int sub, double (*X)[64][17], double (*R)[17]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, i = lane & 15;
+  f32x4 s[(C * (C + 1) / 2) * 4 + 1], t[C * 4 + 1];  // lane (q, i): four consecutive inner indices 16 g + 4 q of row i, g = 0 .. 3
+  int at = 0;
+#pragma unroll
+  for (int b = C - 1; b >= 0; --b) {
+    const size_t row = (size_t)(b0 + b) * 64 + 16 * wave + i;
+#pragma unroll
+    for (int j = C; j > b; --j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) s[at++] = *reinterpret_cast<const f32x4*>(p.S + row * kGroup + j * 64 + 16 * g + 4 * q);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) t[(C - 1 - b) * 4 + g] = *reinterpret_cast<const f32x4*>(p.factor + row * 64 + 16 * g + 4 * q);
+  }
+  {
+    const int r = tid >> 2, c = (tid & 3) * 4;
+    const f32x4 x = *reinterpret_cast<const f32x4*>(p.factor + ((size_t)(b0 + C) * 64 + r) * 64 + 16 * sub + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) X[C][r][c + e] = x[e];
+  }
+  __syncthreads();
+  auto product = [&](const f32x4* a, const double (*B)[17], f64x4 (&acc)[4]) {  // 64 inner indices, four chains of instructions
+    double b[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[4 * g + e] = B[16 * g + 4 * q + e][i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[g][e], b[4 * g + e], acc[g], 0, 0, 0);
+  };
+  at = 0;
+#pragma unroll
+  for (int b = C - 1; b >= 0; --b) {
+    f64x4 acc[4] = {};
+#pragma unroll
+    for (int j = C; j > b; --j) product(s + at + 4 * (C - j), X[j], acc);
+    at += 4 * (C - b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) R[16 * wave + q + 4 * e][i] = (acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e]);
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = f64x4{0., 0., 0., 0.};
+    product(t + (C - 1 - b) * 4, R, acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) X[b][16 * wave + q + 4 * e][i] = -((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e]));
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(256) block_inverse_kernel(InversePair pair) {
+  __shared__ double X[4][64][17];
+  __shared__ double R[64][17];
+  const InverseArgs& p = pair.a[blockIdx.y];
+  const int b0 = (int)blockIdx.x / 16 * 4, c = (int)blockIdx.x % 16 / 4, sub = (int)blockIdx.x % 4;
+  const int blocks = min(4, p.np / 64 - b0);
+  if (c >= blocks) return;
+  switch (c) {
+    case 0: inverse_panel<0>(p, b0, sub, X, R); break;
+    case 1: inverse_panel<1>(p, b0, sub, X, R); break;
+    case 2: inverse_panel<2>(p, b0, sub, X, R); break;
+    default: inverse_panel<3>(p, b0, sub, X, R); break;
+  }
+  constexpr int kt = kGroup / 32;
+  const int col0 = c * 64 + 16 * sub;  // in the group
+  const double* flat = &X[0][0][0];
+  for (int u = threadIdx.x; u < blocks * 128; u += 256) {  // eight columns of a row: the low bits of the row fastest
+    const int row = u / 32 * 16 + (u & 15), k8 = u >> 4 & 1;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = row / 64 <= c ? (float)flat[row * 17 + 8 * k8 + e] : 0.f;
+    store_unit(p.T, kt, b0 * 64 + row, col0 / 8 + k8, v);
+  }
+  for (int u = threadIdx.x; u < blocks * 128; u += 256) {  // eight rows of a column
+    const int col = u & 15, r8 = u >> 4;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = r8 / 8 <= c ? (float)flat[(8 * r8 + e) * 17 + col] : 0.f;
+    store_unit(p.Tt, kt, b0 * 64 + col0 + col, r8, v);
+  }
+}
+
+// K = (Q - Q^T) / 2, Q the sum of `parts` matrices of d x d: d = 1024, one part: 12 MB in 5 us, mostly launch and one trip to memory.
+struct SkewArgs {
+  const float* Q;
+  float* K;
+  int d, parts;
+};
+struct SkewPair {
+  SkewArgs a[2];  // blockIdx.z
+};
+__global__ void __launch_bounds__(256) skew_kernel(SkewPair pair) {
+  __shared__ float tile[32][33];
+  const SkewArgs& p = pair.a[blockIdx.z];
+  const int r0 = (int)blockIdx.y * 32, c0 = (int)blockIdx.x * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5, d = p.d;
+  if (r0 >= d || c0 >= d) return;  // whole workgroup
+  // (entries that do not exist: the first one instead; the fetches of up to eight parts are in flight together)
+  float own[4], other[4];
+  unsigned at[4], to[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = r0 + y + 8 * it, c = c0 + x, rt = c0 + y + 8 * it, ct = r0 + x;
+    at[it] = r < d && c < d ? (unsigned)(r * d + c) : 0u;
+    to[it] = rt < d && ct < d ? (unsigned)(rt * d + ct) : 0u;
+    own[it] = other[it] = 0.f;
+  }
+#pragma unroll 8
+  for (int s = 0; s < p.parts; ++s) {
+    const float* Q = p.Q + (size_t)s * d * d;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      own[it] += Q[at[it]];
+      other[it] += Q[to[it]];
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < 4; ++it) tile[y + 8 * it][x] = other[it];
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int r = r0 + y + 8 * it, c = c0 + x;
+    if (r < d && c < d) p.K[(size_t)r * d + c] = 0.5f * (own[it] - tile[x][y + 8 * it]);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Workspace
+// ------------------------------------------------------------------------------------------
+struct DenseLayout {
+  size_t Va, Vt;          // V as operands: rows stay rows; its transpose
+  size_t S, factor;       // the groups' Gram matrices, the factors of 64 rows
+  size_t T, Tt;           // the groups' T and T^T as operands
+  size_t TV;              // T_g V_g as operands
+  size_t P;               // the product of the groups so far
+  size_t Y, Ya;           // Y fp32 and as operands
+  size_t Yt;              // Y' = T^T V as operands
+  size_t H, Ht;           // H and H^T as operands
+  // saved by the forward pass / used by the backward pass
+  size_t Xa, dXa, Q, K, W, Wa, U;
+  int q_split;
+  size_t total;
+};
+
+// Parts of the mini-batch for Q = dX X^T: enough workgroups for the GPU, 256 columns each at least.
+static int dense_q_split(int d, int m) {
+  const int t = pad64(d) / 64, tiles = t * t;
+  int split = tiles >= 192 ? 1 : (256 + tiles - 1) / tiles;
+  return std::max(1, std::min(split, m / 256));
+}
+
+static DenseLayout make_dense_layout(int d, int n, int m) {
+  DenseLayout L{};
+  size_t off = 256;  // header, reserved
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off = align_up(off + bytes, 256);
+    return o;
+  };
+  const size_t np = pad64(n);
+  L.Va = take(packed_bytes(n, d));
+  L.Vt = take(packed_bytes(d, n));
+  L.S = take(np * kGroup * 4);
+  L.factor = take(np * 64 * 4);
+  L.T = take(np * kGroup * 6);
+  L.Tt = take(np * kGroup * 6);
+  L.TV = take(packed_bytes(n, d));
+  L.P = take((size_t)d * d * 4);
+  L.Y = take((size_t)n * d * 4);
+  L.Ya = take(packed_bytes(n, d));
+  L.H = take(packed_bytes(d, d));
+  L.Ht = take(packed_bytes(d, d));
+  L.q_split = dense_q_split(d, m);
+  L.Xa = take(packed_bytes(d, m));
+  L.dXa = take(packed_bytes(d, m));
+  L.Q = take((size_t)L.q_split * d * d * 4);
+  L.K = take((size_t)d * d * 4);
+  L.W = take((size_t)n * d * 4);
+  L.Wa = take(packed_bytes(n, d));
+  L.U = take(packed_bytes(n, n));
+  L.Yt = take(packed_bytes(n, d));
+  L.total = off;
+  return L;
+}
+
+// ------------------------------------------------------------------------------------------
+// Launches
+// ------------------------------------------------------------------------------------------
+struct GemmList {
+  GemmArgs args;
+  int count = 0;
+  GemmProblem& add() { return args.p[count++] = GemmProblem{}; }
+};
+
+template <int RT, int CT, int WM, int WN, int KS, bool BF, bool EXACT>
+static int launch_gemm_as(GemmList& list, hipStream_t stream) {
+  constexpr int BM = 16 * RT * WM, BN = 16 * CT * WN;
+  int width = 0;
+  for (int i = 0; i < list.count; ++i) {
+    GemmProblem& p = list.args.p[i];
+    const int rt = (pad64(p.rows) + BM - 1) / BM, ct = (pad64(p.cols) + BN - 1) / BN;
+    p.tiles = p.flags & kUpper ? rt * (rt + 1) / 2 : rt * ct * std::max(p.split, 1);
+    // (rows of a triangular operand take different times: every XCD takes all of them)
+    if (!(p.flags & kUpper) && p.split <= 1)
+      p.xcd_rows = (p.term.part & (kFromRow | kToRow)) ? (ct % 8 == 0 ? 1 : 0) : xcd_cut(rt, ct, 6. * BM, (BF ? 4. : 6.) * BN);
+    width = std::max(width, (p.tiles + 7) / 8 * 8);
+  }
+  constexpr size_t lds = gemm_lds<BM, BN, KS>();
+  auto kernel = gemm_kernel<RT, CT, WM, WN, KS, BF, EXACT>;
+  const int rc = allow_lds(kernel, lds);
+  if (rc != FASTH_OK) return rc;
+  hipLaunchKernelGGL(kernel, dim3(width, list.count), dim3(64 * WM * WN * KS), lds, stream, list.args);
+  FASTH_HIP(hipGetLastError());
+  list.count = 0;
+  return FASTH_OK;
+}
+
+// Which tiles: the largest that give every compute unit a workgroup; a launch of short rounds of small tiles is over sooner than
+// one of few large ones. us, k = 1024, packed operands, {128 x 128, 64 x 64, 32 x 32}: 1024 x 4096: 54, 71, -; 1024 x 1024: 35, 18.7, 38;
+// 1024 x 256: -, 15.5, 7.9; 1024 x 100: -, -, 7.0; k = 512: 512 x 512: -, 10.3, 6.5.
+template <bool BF, bool EXACT = false>
+static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_tile = 32, int max_tile = 128) {
+  if (list.count == 0) return FASTH_OK;
+  long t128 = 0, t32 = 0;
+  for (int i = 0; i < list.count; ++i) {
+    const GemmProblem& p = list.args.p[i];
+    const long half = p.flags & kUpper ? 2 : 1, split = std::max(p.split, 1);
+    t128 += (long)((p.rows + 127) / 128) * ((p.cols + 127) / 128) * split / half;
+    t32 += (long)(pad64(p.rows) / 32) * (pad64(p.cols) / 32) * split / half;
+  }
+  int tile = t128 >= 192 ? 128 : t32 > 512 ? 64 : 32;
+  tile = std::min(std::max(tile, min_tile), max_tile);
+  static const std::string flags = std::string(BF ? ", true" : ", false") + (EXACT ? ", true>" : ", false>");
+  static const std::string names[3] = {"gemm_kernel<4, 4, 2, 2, 2" + flags, (EXACT ? "gemm_kernel<4, 2, 1, 2, 4" : "gemm_kernel<4, 4, 1, 1, 8") + flags,
+                                       "gemm_kernel<2, 2, 1, 1, 8" + flags};
+  prof::Scope ps_(slot, stream, names[tile == 128 ? 0 : tile == 64 ? 1 : 2].c_str());
+  if constexpr (EXACT) {  // (its second set of sums leaves no room for 64 x 64 outputs per wave)
+    if (tile >= 64) return launch_gemm_as<4, 2, 1, 2, 4, BF, EXACT>(list, stream);
+  } else {
+    if (tile == 128) return launch_gemm_as<4, 4, 2, 2, 2, BF, EXACT>(list, stream);
+    if (tile == 64) return launch_gemm_as<4, 4, 1, 1, 8, BF, EXACT>(list, stream);
+  }
+  return launch_gemm_as<2, 2, 1, 1, 8, BF, EXACT>(list, stream);
+}
+
+static int launch_pack(PackArgs& args, int count, int slot, hipStream_t stream) {
+  int width = 0;
+  for (int i = 0; i < count; ++i) width = std::max(width, args.job[i].blocks);
+  if (width == 0) return FASTH_OK;
+  prof::Scope ps_(slot, stream, "pack_kernel");
+  hipLaunchKernelGGL(pack_kernel, dim3(width, count), dim3(256), 0, stream, args);
+  FASTH_HIP(hipGetLastError());
+  return FASTH_OK;
+}
+
+// One product on its slice of a workspace.
+struct Dense {
+  int d = 0, n = 0, m = 0;
+  bool lower = false;            // the product is H^T X: T^T in the place of T
+  const Dense* owner = nullptr;  // whose workspace has T, Y and H, if not this one's
+  DenseLayout L;
+  char* ws = nullptr;
+  const Dense& factors() const { return owner ? *owner : *this; }
+  char* at(size_t off) const { return ws + off; }
+  float* f(size_t off) const { return reinterpret_cast<float*>(ws + off); }
+  int kt(int x) const { return pad64(x) / 32; }
+  PackJob pack_v(const float* V) const { return PackJob{V, at(L.Va), at(L.Vt), n, d, pad64(n) / 64 * (pad64(d) / 64)}; }
+  // the inputs of the saved product ([rows][m], rows beyond are zero) as operands for the backward pass
+  PackJob pack_x(const float* X, int rows) const { return PackJob{X, at(L.Xa), nullptr, rows, m, pad64(d) / 64 * (pad64(m) / 64)}; }
+  // H or H^T as operands, Y (or, of a lower product, Y' = T^T V) as operands
+  char* matrix(bool transpose) const { const Dense& F = factors(); return F.at(transpose ? F.L.Ht : F.L.H); }
+  char* y() const { const Dense& F = factors(); return F.at(lower ? F.L.Yt : F.L.Ya); }
+};
+
+static int group_rows(const Dense& P, int g) { return std::min(kGroup, P.n - g * kGroup); }
+// (row, k) of operands with kt tiles of k
+static char* operand_cell(char* base, int kt, int row, int k) { return base + ((size_t)(row / 16) * kt + k / 32) * kTileBytes; }
+
+// The groups' T of up to two products; `jobs`: what else is to be packed in the first launch.
+static int dense_factors(const Dense* const* D, const float* const* V, int count, const PackJob* jobs, int njobs, hipStream_t stream) {
+  const int slot = FASTH_KERNEL_FACTOR;
+  PackArgs pk{};
+  for (int i = 0; i < count; ++i) pk.job[i] = D[i]->pack_v(V[i]);
+  for (int i = 0; i < njobs; ++i) pk.job[count + i] = jobs[i];
+  int rc = launch_pack(pk, count + njobs, slot, stream);
+  if (rc != FASTH_OK) return rc;
+  InversePair inv{};
+  FactorPair64 fac{};
+  int width = 0;
+  GemmList gram;
+  for (int i = 0; i < count; ++i) {
+    const Dense& P = *D[i];
+    const int groups = (P.n + kGroup - 1) / kGroup;
+    fac.a[i] = FactorArgs64{P.f(P.L.S), P.f(P.L.factor), P.n, pad64(P.n)};
+    inv.a[i] = InverseArgs{P.f(P.L.S), P.f(P.L.factor), P.at(P.L.T), P.at(P.L.Tt), pad64(P.n)};
+    width = std::max(width, groups);
+    for (int g = 0; g < groups; ++g) {
+      if (gram.count == kGemmProblems && (rc = launch_gemm<false, true>(gram, slot, stream)) != FASTH_OK) return rc;
+      GemmProblem& p = gram.add();
+      char* rows = operand_cell(P.at(P.L.Va), P.kt(P.d), g * kGroup, 0);
+      p.term = GemmTerm{rows, rows, P.kt(P.d), P.kt(P.d), P.d, 0};
+      p.rows = p.cols = pad64(group_rows(P, g)); p.ldo = kGroup; p.flags = kUpper; p.alpha = 1.f;
+      p.out = P.f(P.L.S) + (size_t)g * kGroup * kGroup;
+    }
+  }
+  if ((rc = launch_gemm<false, true>(gram, slot, stream)) != FASTH_OK) return rc;
+  {
+    prof::Scope ps_(slot, stream, "block_factor_kernel");
+    hipLaunchKernelGGL(block_factor_kernel, dim3(width * (kGroup / 64), count), dim3(512), 0, stream, fac);
+    FASTH_HIP(hipGetLastError());
+  }
+  prof::Scope ps_(slot, stream, "block_inverse_kernel");
+  hipLaunchKernelGGL(block_inverse_kernel, dim3(width * 16, count), dim3(256), 0, stream, inv);
+  FASTH_HIP(hipGetLastError());
+  return FASTH_OK;
+}
+
+// Y and H of up to two products, or, of lower ones, Y' and H^T (which leaves H too); without `matrix` Y or Y' alone.
+static int dense_matrices(const Dense* const* D, const float* const* V, int count, bool matrix, hipStream_t stream) {
+  const int slot = FASTH_KERNEL_FACTOR;
+  int rc, steps = 0, groups[2] = {0, 0};
+  for (int i = 0; i < count; ++i) {
+    groups[i] = (D[i]->n + kGroup - 1) / kGroup;
+    steps = std::max(steps, groups[i]);
+  }
+  auto group_at = [&](int i, int step) { return D[i]->lower ? step : groups[i] - 1 - step; };
+  auto y_of = [](GemmProblem& p, const Dense& P, int g) {
+    p.rows = group_rows(P, g); p.cols = p.ldo = P.d; p.alpha = 1.f;
+    p.out = P.f(P.L.Y) + (size_t)g * kGroup * P.d;
+    p.along = operand_cell(P.y(), P.kt(P.d), g * kGroup, 0); p.along_kt = P.kt(P.d);
+  };
+  // T_g V_g: Y_g of the group that is applied first, operands for the others'
+  GemmList tv;
+  for (int i = 0; i < count; ++i) {
+    const Dense& P = *D[i];
+    for (int step = 0; step < groups[i]; ++step) {
+      const int g = group_at(i, step);
+      if (tv.count == kGemmProblems && (rc = launch_gemm<true>(tv, slot, stream)) != FASTH_OK) return rc;
+      GemmProblem& p = tv.add();
+      y_of(p, P, g);
+      p.term = GemmTerm{operand_cell(P.at(P.lower ? P.L.Tt : P.L.T), kGroup / 32, g * kGroup, 0), reinterpret_cast<const char*>(V[i] + (size_t)g * kGroup * P.d),
+                        kGroup / 32, P.d, group_rows(P, g), P.lower ? kToRow : kFromRow};
+      if (step > 0) {
+        p.out = nullptr;
+        p.along = operand_cell(P.at(P.L.TV), P.kt(P.d), g * kGroup, 0);
+      }
+    }
+  }
+  if ((rc = launch_gemm<true>(tv, slot, stream)) != FASTH_OK) return rc;
+  // P <- P - V_g^T Y_g, Y_g = (T_g V_g) P
+  for (int step = 0; step < steps; ++step) {
+    GemmList y, h;
+    for (int i = 0; i < count; ++i) {
+      if (step >= groups[i]) continue;
+      const Dense& P = *D[i];
+      const int g = group_at(i, step);
+      if (step > 0) {
+        GemmProblem& p = y.add();
+        y_of(p, P, g);
+        p.term = GemmTerm{operand_cell(P.at(P.L.TV), P.kt(P.d), g * kGroup, 0), P.at(P.L.P), P.kt(P.d), P.d, P.d, 0};
+      }
+      const bool last = step + 1 == groups[i];
+      if (last && !matrix) continue;
+      GemmProblem& p = h.add();
+      p.term = GemmTerm{operand_cell(P.at(P.L.Vt), P.kt(P.n), 0, g * kGroup), reinterpret_cast<const char*>(P.f(P.L.Y) + (size_t)g * kGroup * P.d), P.kt(P.n), P.d, group_rows(P, g), 0};
+      p.rows = p.cols = p.ldo = P.d; p.alpha = -1.f;
+      if (step == 0) p.diag = 1.f;
+      else { p.add = P.f(P.L.P); p.beta = 1.f; }
+      if (!last) {
+        p.out = P.f(P.L.P);
+      } else {
+        p.along = P.matrix(P.lower); p.along_kt = P.kt(P.d);
+        p.across = P.matrix(!P.lower); p.across_kt = P.kt(P.d);
+      }
+    }
+    if ((rc = launch_gemm<true>(y, slot, stream)) != FASTH_OK || (rc = launch_gemm<true>(h, slot, stream)) != FASTH_OK) return rc;
+  }
+  return FASTH_OK;
+}
+
+// out = H in, or H^T in; `in` has in_rows rows, the others are zero. Optionally the scaled rows for the next product
+// and the result as operands.
+static int dense_apply(const Dense& P, bool transpose, const float* in, int in_rows, float* out, const float* scale, int scale_mode, int scaled_rows,
+                       float* scaled, char* along, hipStream_t stream) {
+  GemmList list;
+  GemmProblem& g = list.add();
+  g.term = GemmTerm{P.matrix(transpose), reinterpret_cast<const char*>(in), P.kt(P.d), P.m, in_rows, 0};
+  g.rows = P.d; g.cols = g.ldo = P.m; g.alpha = 1.f;
+  g.out = out;
+  g.scaled = scaled; g.scale = scale; g.scale_mode = scale_mode; g.scaled_rows = scaled_rows;
+  g.along = along; g.along_kt = P.kt(P.m);
+  return launch_gemm<true>(list, FASTH_KERNEL_CHAIN, stream);
+}
+
+// dV of up to two products from X and dX as operands (pack_x, dense_apply).
+static int dense_dv(const Dense* const* D, const float* const* V, float* const* dV, int count, bool accumulate, hipStream_t stream) {
+  const int slot = FASTH_KERNEL_DV;
+  GemmList q, w, z, v;
+  SkewPair sk{};
+  int dmax = 0;
+  for (int i = 0; i < count; ++i) {
+    const Dense& P = *D[i];
+    GemmProblem& a = q.add();
+    a.term = GemmTerm{P.at(P.L.dXa), P.at(P.L.Xa), P.kt(P.m), P.kt(P.m), P.m, 0};
+    a.rows = a.cols = a.ldo = P.d; a.alpha = 1.f; a.out = P.f(P.L.Q); a.split = P.L.q_split;
+    sk.a[i] = SkewArgs{P.f(P.L.Q), P.f(P.L.K), P.d, P.L.q_split};
+    dmax = std::max(dmax, P.d);
+    GemmProblem& b = w.add();
+    b.term = GemmTerm{P.y(), P.at(P.L.K), P.kt(P.d), P.d, P.d, 0};
+    b.rows = P.n; b.cols = b.ldo = P.d; b.alpha = 1.f; b.out = P.f(P.L.W);
+    b.along = P.at(P.L.Wa); b.along_kt = P.kt(P.d);
+    GemmProblem& c = z.add();
+    // striu(W Y^T), or the transpose of stril(W Y^T), striu(Y W^T)
+    c.term = GemmTerm{P.lower ? P.y() : P.at(P.L.Wa), P.lower ? P.at(P.L.Wa) : P.y(), P.kt(P.d), P.kt(P.d), P.d, 0};
+    c.rows = c.cols = c.ldo = P.n; c.alpha = 1.f; c.flags = kUpper | kStrict;
+    if (P.lower) { c.across = P.at(P.L.U); c.across_kt = P.kt(P.n); }
+    else { c.along = P.at(P.L.U); c.along_kt = P.kt(P.n); }
+    GemmProblem& e = v.add();
+    e.term = GemmTerm{P.at(P.L.U), reinterpret_cast<const char*>(V[i]), P.kt(P.n), P.d, P.n, P.lower ? kToRow : kFromRow};
+    e.rows = P.n; e.cols = e.ldo = P.d; e.alpha = -2.f; e.beta = 2.f; e.add = P.f(P.L.W); e.out = dV[i];
+    e.flags = accumulate ? kAccumulate : 0;
+  }
+  int rc = launch_gemm<false>(q, slot, stream);
+  if (rc != FASTH_OK) return rc;
+  {
+    prof::Scope ps_(slot, stream, "skew_kernel");
+    const int t = (dmax + 31) / 32;
+    hipLaunchKernelGGL(skew_kernel, dim3(t, t, count), dim3(256), 0, stream, sk);
+    FASTH_HIP(hipGetLastError());
+  }
+  if ((rc = launch_gemm<true>(w, slot, stream)) != FASTH_OK) return rc;
+  // the tiles of U beyond its diagonal tiles are not written: both products in tiles of one size
+  const int tile = (long)(pad64(D[0]->n) / 32) * (pad64(D[0]->d) / 32) * count <= 512 ? 32 : 64;
+  if ((rc = launch_gemm<false>(z, slot, stream, tile, tile)) != FASTH_OK) return rc;
+  return launch_gemm<true>(v, slot, stream, tile, tile);
+}
+
+// 32-bit byte offsets into the fp32 operands; reflections far beyond the vector length would share a T of more rounding
+static bool dense_fits(int d, int n, int m) {
+  return d <= 4096 && 2 * n <= 3 * d && (size_t)d * m * sizeof(float) < 0x80000000u;
+}
+// Whether gradient steps (and what is prepared) run on the whole matrix: the m-dependent part of a step is 6 d^2 m operations instead of
+// 12 d n m, the rest is as much as a mini-batch of some 1.2 d columns; where teams of workgroups serve up to 1280 columns they keep them. us
+// per forward + backward, chain of blocks and this, n = d and (n = 3/4 d): d = 512: m = 512: 86, 97; m = 768: 118, 105 (101, 105);
+// m = 4096: 183, 147 (151, 145); d = 640: m = 1024: 149, 145; m = 1300: 187, 152; m = 4096: 286, 213 (242, 200); d = 768: m = 1300: 216, 194 (177, 172);
+// m = 1700: 225, 222 (185, 200); m = 2300: 287, 227 (233, 205); d = 1024: m = 1024: 236, 232; m = 1300: 284, 266 (228, 237); m = 2300: 411, 313 (311, 283);
+// m = 4096: 564, 334 (425, 306), n = 1/2 d: 298, 265; d = 1280: m = 1300: 481, 440; m = 1700: 533, 485 (398, 436); m = 3000: (725, 460); d = 1536: m = 1300:
+// 640, 629; m = 1700: 720, 686 (521, 567); m = 2300: (626, 589); d = 2048: m = 1024: 760, 906; shorter vectors: d = 384: m = 1300: 111, 102; m = 4096: 142, 150;
+// d = 256: m = 1700: 82, 85; m = 4096: 101, 128.
+static bool dense_serves(int d, int n, int m) {
+  if (!dense_fits(d, n, m)) return false;
+  if (d <= 512) return d >= 448 && 10 * n >= 9 * d && m >= 768;
+  return m > 1280 && (double)m * n * n >= 1.25 * std::max(d, 1024) * d * d;
+}
+
+}  // namespace fasth
