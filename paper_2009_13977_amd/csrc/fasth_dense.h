@@ -277,7 +277,7 @@ struct GemmList {
   GemmProblem& add() { return args.p[count++] = GemmProblem{}; }
 };
 
-template <int RT, int CT, int WM, int WN, int KS, bool BF, bool EXACT>
+template <int RT, int CT, int WM, int WN, int KS, int BF, bool EXACT>
 static int launch_gemm_as(GemmList& list, hipStream_t stream) {
   constexpr int BM = 16 * RT * WM, BN = 16 * CT * WN;
   int width = 0;
@@ -303,9 +303,8 @@ static int launch_gemm_as(GemmList& list, hipStream_t stream) {
 // Which tiles: the largest that give every compute unit a workgroup; a launch of short rounds of small tiles is over sooner than
 // one of few large ones. us, k = 1024, packed operands, {128 x 128, 64 x 64, 32 x 32}: 1024 x 4096: 54, 71, -; 1024 x 1024: 35, 18.7, 38;
 // 1024 x 256: -, 15.5, 7.9; 1024 x 100: -, -, 7.0; k = 512: 512 x 512: -, 10.3, 6.5.
-template <bool BF, bool EXACT = false>
-static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_tile = 32, int max_tile = 128) {
-  if (list.count == 0) return FASTH_OK;
+template <int BF, bool EXACT = false>
+static int launch_gemm_tiles(GemmList& list, int slot, hipStream_t stream, int min_tile, int max_tile) {
   long t128 = 0, t32 = 0;
   for (int i = 0; i < list.count; ++i) {
     const GemmProblem& p = list.args.p[i];
@@ -315,7 +314,7 @@ static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_til
   }
   int tile = t128 >= 192 ? 128 : t32 > 512 ? 64 : 32;
   tile = std::min(std::max(tile, min_tile), max_tile);
-  static const std::string flags = std::string(BF ? ", true" : ", false") + (EXACT ? ", true>" : ", false>");
+  static const std::string flags = ", " + std::to_string(BF) + (EXACT ? ", true>" : ", false>");
   static const std::string names[3] = {"gemm_kernel<4, 4, 2, 2, 2" + flags, (EXACT ? "gemm_kernel<4, 2, 1, 2, 4" : "gemm_kernel<4, 4, 1, 1, 8") + flags,
                                        "gemm_kernel<2, 2, 1, 1, 8" + flags};
   prof::Scope ps_(slot, stream, names[tile == 128 ? 0 : tile == 64 ? 1 : 2].c_str());
@@ -326,6 +325,22 @@ static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_til
     if (tile == 64) return launch_gemm_as<4, 4, 1, 1, 8, BF, EXACT>(list, stream);
   }
   return launch_gemm_as<2, 2, 1, 1, 8, BF, EXACT>(list, stream);
+}
+
+// BF: B is fp32 [k][cols]; where its rows are made of 16-byte groups a lane loads neighbouring columns at once. us per forward + backward, a load per
+// column and this: d = n = 1024, m = 4096: 334, 330; m = 1400: 259, 252; d = 512, m = 2048: 114, 113; d = 1536, m = 2048: 665, 658.
+template <bool BF, bool EXACT = false>
+static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_tile = 32, int max_tile = 128) {
+  if (list.count == 0) return FASTH_OK;
+  if constexpr (BF) {
+    bool wide = true;
+    for (int i = 0; i < list.count; ++i) {
+      const GemmProblem& p = list.args.p[i];
+      wide = wide && p.cols % 4 == 0 && p.term.ldb % 4 == 0 && reinterpret_cast<uintptr_t>(p.term.B) % 16 == 0;
+    }
+    if (wide) return launch_gemm_tiles<2, EXACT>(list, slot, stream, min_tile, max_tile);
+  }
+  return launch_gemm_tiles<BF ? 1 : 0, EXACT>(list, slot, stream, min_tile, max_tile);
 }
 
 static int launch_pack(PackArgs& args, int count, int slot, hipStream_t stream) {

@@ -24,7 +24,7 @@ __device__ __forceinline__ BufferDesc make_buffer(const float* base, size_t byte
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)bytes, 0x00020000);
 }
 
-// VEC consecutive floats (1 or 4) at byte offset lane_bytes + uniform_bytes of the buffer.
+// VEC consecutive floats (1, 2 or 4) at byte offset lane_bytes + uniform_bytes of the buffer.
 template <int VEC>
 struct BufVec {
   float e[VEC];
@@ -35,8 +35,11 @@ __device__ __forceinline__ BufVec<VEC> buffer_load(BufferDesc desc, unsigned lan
   if constexpr (VEC == 4) {
     const float4 v = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(desc, lane_bytes, uniform_bytes, 0));
     r.e[0] = v.x; r.e[1] = v.y; r.e[2] = v.z; r.e[3] = v.w;
+  } else if constexpr (VEC == 2) {
+    const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(desc, lane_bytes, uniform_bytes, 0));
+    r.e[0] = v.x; r.e[1] = v.y;
   } else {
-    static_assert(VEC == 1, "1 or 4 floats");
+    static_assert(VEC == 1, "1, 2 or 4 floats");
     r.e[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(desc, lane_bytes, uniform_bytes, 0));
   }
   return r;

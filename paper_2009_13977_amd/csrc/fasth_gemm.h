@@ -231,12 +231,14 @@ __device__ __forceinline__ void gemm_range(const GemmTerm& g, int r0, int c0, in
 
 // A wave forms 16 RT x 16 CT outputs and fetches its operands straight into registers, a tile of k ahead; WM x WN waves make up a
 // workgroup's tile and KS such groups share the inner index. No LDS and no barrier before the sums meet: waves that share an operand find it in
-// the compute unit's cache. BF: B is fp32 [k][cols], split in registers.
-// Bound by the loads of the vector-memory path (36 .. 41 bytes per clock and compute unit; a tile of 64 x 64 x 32 of a wave needs 24 KiB or, BF,
-// 20 KiB, for 96 instructions of the matrix cores). 1024 x 4096 x 1024: 54 .. 62 us, 139 .. 159 TF/s of fp32 products, which are six bf16
-// products each (the matrix cores' limit: 335); 1024 x 1024 x 1024: 17 us; 1024 x 256 x 1024: 7.2 us; the smallest: 4.9 us, launch and code
-// fetch. The same products with both operands staged in LDS took 57 us at 1024 x 4096 x 1024 (packed) and 67 us (split on the way).
-template <int RT, int CT, int WM, int WN, int KS, bool BF, bool EXACT>
+// the compute unit's cache. BF: B is fp32 [k][cols], split in registers: 1, a load per column; 2, where its rows are made of groups of four, a
+// load per lane takes the columns of all column tiles, so that lane i's are CT i, CT i + 1, ... of the wave's.
+// 1024 x 4096 x 1024: 54 us packed; BF 58 .. 60 us (62 with loads of one column each), 143 TF/s of fp32 products, which are six bf16 products each
+// (the matrix cores' limit: 335, 25 us). Bound by what the waves issue: without the split 47 us, without the loads 45, with every load from the
+// same addresses 57, so neither memory nor the L2s; some 8 are launch, first fetch and the way out. 1024 x 1024 x 1024: 17 us; 1024 x 256 x 1024: 7.2;
+// the smallest: 4.9, launch and code fetch. The same products with both operands staged in LDS took 57 us at 1024 x 4096 x 1024 (packed) and 67 us
+// (split on the way); a barrier per tile of k, for waves that share an operand to fetch it together: 63.
+template <int RT, int CT, int WM, int WN, int KS, int BF, bool EXACT>
 __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) {
   constexpr int BM = 16 * RT * WM, BN = 16 * CT * WN, LD = BN + 4;
   extern __shared__ __align__(16) float tile[];
@@ -291,12 +293,13 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
   if (k < end) {
     const char* A[RT];
     const char* B[CT];
-    unsigned uoff[CT];
+    unsigned uoff[BF == 1 ? CT : 1];
 #pragma unroll
     for (int r = 0; r < RT; ++r) A[r] = g.A + ((size_t)min(ra + r, last_r) * g.lda + k) * kTileBytes;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-      if constexpr (BF) uoff[c] = ((unsigned)(8 * q) * (unsigned)g.ldb + (unsigned)min((cb + c) * 16 + i, p.cols - 1)) * 4u;
+      if constexpr (BF == 1) uoff[c] = ((unsigned)(8 * q) * (unsigned)g.ldb + (unsigned)min((cb + c) * 16 + i, p.cols - 1)) * 4u;
+      else if constexpr (BF == 2) uoff[0] = ((unsigned)(8 * q) * (unsigned)g.ldb + (unsigned)min(cb * 16 + CT * i, p.cols - CT)) * 4u;
       else B[c] = g.B + ((size_t)min(cb + c, last_c) * g.ldb + k) * kTileBytes;
     }
     // An operand of the next tile of k is fetched as soon as its registers have been read: one tile of k ahead. Beyond its last tile
@@ -312,12 +315,14 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
         // rows of B that do not exist lie beyond the buffer and read as zero
         const BufferDesc desc = make_buffer(reinterpret_cast<const float*>(g.B) + (size_t)k * 32 * g.ldb, (size_t)max(g.K - 32 * k, 0) * g.ldb * sizeof(float));
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
+        for (int c = 0; c < (BF == 2 ? 1 : CT); ++c) {
           unsigned off = uoff[c];
           asm("" : "+v"(off));  // (the eight offsets formed here again: kept over the loop, they would take registers)
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            v[c][e] = buffer_load<1>(desc, off, 0).e[0];
+            const auto got = buffer_load<(BF == 2 ? CT : 1)>(desc, off, 0);
+#pragma unroll
+            for (int x = 0; x < (BF == 2 ? CT : 1); ++x) v[c + x][e] = got.e[x];
             off += (unsigned)g.ldb * 4u;
           }
         }
@@ -366,7 +371,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
   constexpr int NT = 64 * WM * WN * KS, UNITS = BM * BN / 4, PER = (UNITS + NT - 1) / NT;
   f32x4* parts = reinterpret_cast<f32x4*>(tile);  // [group][row tile][column tile][lane]
   auto to_rows = [&](int unit, f32x4 v) {
-    const int l = unit & 63, t = unit >> 6, row = t / (BN / 16) * 16 + 4 * (l >> 4), col = t % (BN / 16) * 16 + (l & 15);
+    const int l = unit & 63, t = unit >> 6, row = t / (BN / 16) * 16 + 4 * (l >> 4), ct = t % (BN / 16);
+    const int col = BF == 2 ? ct / CT * (16 * CT) + CT * (l & 15) + ct % CT : ct * 16 + (l & 15);
 #pragma unroll
     for (int j = 0; j < 4; ++j) tile[(row + j) * LD + col] = v[j];
   };

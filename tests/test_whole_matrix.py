@@ -7,8 +7,9 @@ from helpers import assert_close, gpu_fasth, gpu_svd_layer, gpu_svd_rect, gpu_sv
 from oracle import householder as orc
 from paper_2009_13977_amd import synthetic
 
-# groups of 256 rows with a last one of 148, 194, 256, 1, 88 and 65 rows; vectors of whole tiles of 64, one more, four less; columns likewise
-SHAPES = [(448, 404, 768, 4), (500, 450, 769, 50), (512, 768, 770, 64), (513, 513, 1281, 1), (577, 600, 1344, 24), (640, 577, 1601, 1)]
+# groups of 256 rows with a last one of 148, 194, 256, 1, 88, 65 and 88 rows; vectors of whole tiles of 64, one more, four less; columns likewise;
+# rows of whole 16-byte groups and not, in V and in X; the last has enough columns for the largest tiles of a product
+SHAPES = [(448, 404, 768, 4), (500, 450, 769, 50), (512, 768, 770, 64), (513, 513, 1281, 1), (577, 600, 1344, 24), (640, 577, 1601, 1), (640, 600, 4993, 24)]
 
 
 def test_the_rule_by_the_workspace():
