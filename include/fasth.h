@@ -55,8 +55,9 @@ enum {
  * own, 32 or 64 rows (8, 16 or 24 for few reflections in small blocks, k < 32),
  * padding the last one. A larger k still bounds the memory: where blocks of 32 or
  * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. Wide
- * mini-batches (more than 1280 columns of vectors of more than 512 elements, 768 of 448 to
- * 512, with n near d) multiply by the whole H as one matrix, in any k's place. */
+ * mini-batches (some 640 columns and more of vectors of 448 to 640 elements, 1000 of 864
+ * to 1024, 1280 to 2048 of other lengths up to 4096, with n not far below d) multiply
+ * by the whole H as one matrix, in any k's place. */
 typedef struct fasth_shape {
   int d;          /* length of each Householder vector = rows of X */
   int n;          /* number of reflections = rows of V */

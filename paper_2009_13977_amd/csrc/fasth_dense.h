@@ -540,16 +540,25 @@ static bool dense_fits(int d, int n, int m) {
   return d <= 4096 && 2 * n <= 3 * d && (size_t)d * m * sizeof(float) < 0x80000000u;
 }
 // Whether gradient steps (and what is prepared) run on the whole matrix: the m-dependent part of a step is 6 d^2 m operations instead of
-// 12 d n m, the rest is as much as a mini-batch of some 1.2 d columns; where teams of workgroups serve up to 1280 columns they keep them. us
-// per forward + backward, chain of blocks and this, n = d and (n = 3/4 d): d = 512: m = 512: 86, 97; m = 768: 118, 105 (101, 105);
-// m = 4096: 183, 147 (151, 145); d = 640: m = 1024: 149, 145; m = 1300: 187, 152; m = 4096: 286, 213 (242, 200); d = 768: m = 1300: 216, 194 (177, 172);
-// m = 1700: 225, 222 (185, 200); m = 2300: 287, 227 (233, 205); d = 1024: m = 1024: 236, 232; m = 1300: 284, 266 (228, 237); m = 2300: 411, 313 (311, 283);
-// m = 4096: 564, 334 (425, 306), n = 1/2 d: 298, 265; d = 1280: m = 1300: 481, 440; m = 1700: 533, 485 (398, 436); m = 3000: (725, 460); d = 1536: m = 1300:
-// 640, 629; m = 1700: 720, 686 (521, 567); m = 2300: (626, 589); d = 2048: m = 1024: 760, 906; shorter vectors: d = 384: m = 1300: 111, 102; m = 4096: 142, 150;
-// d = 256: m = 1700: 82, 85; m = 4096: 101, 128.
+// 12 d n m, the rest is as much as a mini-batch of some 1.2 d columns. Where the lines lie depends on the chain that would run: teams of workgroups
+// serve up to 1280 columns (d <= 640, and 768), 1024 (d > 768) or 2048 (d <= 512), and are slower per column beyond. us per forward + backward, chain of blocks and
+// this, n / d in brackets:
+// d = 448: m = 640: 97, 99 (1); m = 1300: 107, 110 (0.7); m = 4096: 135, 147 (0.7). d = 464: m = 640: 106, 101 (1); 100, 101 (0.9); m = 1024: 112, 103 (0.7).
+// d = 512: m = 512: 85, 96 (1); m = 640: 113, 100 (1); 108, 100 (0.9); 98, 100 (0.8); m = 1024: 129, 104 (0.9); 110, 103 (0.7); m = 1500: 123, 110 (0.7).
+// d = 544: m = 704: 131, 126 (1); 121, 114 (0.85); 101, 106 (0.7); m = 1280: 119, 121 (0.7); m = 1500: 141, 123 (0.6). d = 640: m = 704: 139, 131 (1);
+// m = 768: 135, 137 (0.85); m = 1500: 143, 130 (0.6). d = 704: m = 768: 151, 152 (1); m = 1500: 167, 167 (0.7); m = 2200: 210, 174 (0.7); 195, 171 (0.6).
+// d = 768: m = 1280: 174, 186 (1); m = 2300: 287, 222 (1); 233, 203 (0.75). d = 864: m = 1024: 206, 202 (1); m = 1100: 241, 209 (1); 229, 207 (0.9).
+// d = 928: m = 1100: 243, 245 (0.9); 231, 243 (0.85). d = 960: m = 960: 231, 219 (1); 226, 218 (0.95); 207, 215 (0.9). d = 1001: m = 1100: 256, 263 (0.95).
+// d = 1024: m = 960: 227, 226 (1); m = 1024: 234, 226 (1); 226, 225 (0.9); m = 1280: 281, 256 (1); 264, 252 (0.9); 251, 247 (0.85); m = 4096: 552, 333 (1);
+// 425, 303 (0.75). d = 1152: m = 1280: 355, 384 (1). d = 1280: m = 1280: 390, 417 (1); m = 1500: 503, 429 (1). d = 1536: m = 1280: 536, 620 (1); m = 1500: 689, 665 (1); 493, 551
+// (0.75). d = 2048: m = 1024: 760, 906 (1); shorter vectors: d = 384: m = 1300: 112, 103 (1); m = 3000: 135, 148 (1).
 static bool dense_serves(int d, int n, int m) {
   if (!dense_fits(d, n, m)) return false;
-  if (d <= 512) return d >= 448 && 10 * n >= 9 * d && m >= 768;
+  const auto at_least = [&](int twentieths) { return 20ll * n >= (long long)twentieths * d; };  // n / d
+  if (d <= 512) return d >= 448 && ((at_least(18) && m >= (d >= 464 ? 640 : 768)) || (d >= 464 && at_least(14) && m >= 1024 && m <= 2560));
+  if (d <= 640 && m >= 704 && at_least(d <= 560 ? 17 : 19)) return true;
+  if (d <= 704 && at_least(12) && m >= (d <= 640 ? 1281 : 2048)) return true;
+  if (d >= 864 && d <= 1024 && d % 4 == 0 && (m > 1024 ? at_least(18) : d >= 960 && m >= 1000 && at_least(19))) return true;
   return m > 1280 && (double)m * n * n >= 1.25 * std::max(d, 1024) * d * d;
 }
 

@@ -7,17 +7,21 @@ from helpers import assert_close, gpu_fasth, gpu_svd_layer, gpu_svd_rect, gpu_sv
 from oracle import householder as orc
 from paper_2009_13977_amd import synthetic
 
-# groups of 256 rows with a last one of 148, 194, 256, 1, 88, 65 and 88 rows; vectors of whole tiles of 64, one more, four less; columns likewise;
-# rows of whole 16-byte groups and not, in V and in X; the last has enough columns for the largest tiles of a product
-SHAPES = [(448, 404, 768, 4), (500, 450, 769, 50), (512, 768, 770, 64), (513, 513, 1281, 1), (577, 600, 1344, 24), (640, 577, 1601, 1), (640, 600, 4993, 24)]
+# groups of 256 rows with a last one of 148, 194, 256, 1, 88, 65, 88, 69, 220, 144 and 167 rows; vectors of whole tiles of 64, one more, four less; columns likewise;
+# rows of whole 16-byte groups and not, in V and in X; the seventh has enough columns for the largest tiles of a product
+SHAPES = [(448, 404, 768, 4), (500, 450, 769, 50), (512, 768, 770, 64), (513, 513, 1281, 1), (577, 600, 1344, 24), (640, 577, 1601, 1), (640, 600, 4993, 24),
+          (464, 325, 1024, 25), (560, 476, 704, 28), (960, 912, 1000, 24), (704, 423, 2048, 47)]
 
 
 def test_the_rule_by_the_workspace():
     """No saved inputs per block: the workspace on the two sides of the rule's lines, whatever the block size."""
     from paper_2009_13977_amd import binding as B
     size = B.fasth_workspace_bytes
-    for (d, n, m), (d2, n2, m2) in (((1024, 1024, 1281), (1024, 1024, 1280)), ((512, 512, 768), (512, 512, 767)), ((448, 448, 900), (444, 444, 900)),
-                                    ((1024, 768, 2276), (1024, 768, 2275)), ((600, 900, 1300), (600, 904, 1300)), ((512, 461, 2000), (512, 460, 2000))):
+    for (d, n, m), (d2, n2, m2) in (((1024, 1024, 1000), (1024, 1024, 999)), ((1000, 900, 1025), (1000, 900, 1024)), ((1024, 1024, 1025), (1025, 1025, 1025)),
+                                    ((512, 512, 640), (512, 512, 639)), ((448, 448, 900), (444, 444, 900)), ((464, 325, 1024), (464, 325, 1023)),
+                                    ((512, 461, 3000), (512, 460, 3000)), ((560, 476, 704), (560, 475, 704)), ((640, 608, 704), (640, 607, 704)),
+                                    ((640, 384, 1281), (640, 384, 1280)), ((704, 423, 2048), (704, 423, 2047)), ((1024, 768, 2276), (1024, 768, 2275)),
+                                    ((600, 900, 1300), (600, 904, 1300))):
         for k in (1, 2, 4):
             if n % k == 0 and n2 % k == 0:
                 assert size(d, n, m, k) == size(d, n, m, 1)
