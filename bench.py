@@ -54,8 +54,10 @@ def f_exec(d, n, m, k):
     return 12.0 * d * n * m + 4.0 * d * n * block_rows(d, k)
 
 
-def kernel_flops(slot, d, n, m, k):
+def kernel_flops(slot, launched, d, n, m, k):
     """Algorithmic FLOP of one launch of the kernel in a profiler slot."""
+    if (launched or "").startswith(("gemm_kernel", "pack_kernel", "block_", "skew_kernel")):  # H as one matrix
+        return 2.0 * d * d * m if slot == "chain_kernel" else None  # H X; the other slots' launches are of many sizes
     if slot == "chain_kernel":
         return 4.0 * d * n * m                       # B = V_i a and a -= V_i^T C over all blocks
     if slot == "dv_kernel":
@@ -219,7 +221,7 @@ def measure_product(torch, B, synthetic, name, steps, warmup, sequential=True):
     ms = _timed(torch, step, steps)
     kernels = _profiled(torch, B, step, min(steps, 50))
     dom = _dominant(kernels)
-    flops = kernel_flops(dom, d, n, m, k)
+    flops = kernel_flops(dom, kernels[dom]["launched"], d, n, m, k)
     tflops = flops / (kernels[dom]["ms_avg"] * 1e-3) / 1e12 if flops else None
     out = {
         "workload": name, "d": d, "n": n, "m": m, "k": k, "steps": steps,
@@ -278,7 +280,7 @@ def measure_svd_layer(torch, B, synthetic, name, steps, warmup):
         ms = _timed(torch, fn, steps)
         kernels = _profiled(torch, B, fn, min(steps, 50))
         dom = _dominant(kernels)
-        kf = kernel_flops(dom, d, n, m, k)
+        kf = kernel_flops(dom, kernels[dom]["launched"], d, n, m, k)
         tflops = kf / (kernels[dom]["ms_avg"] * 1e-3) / 1e12 if kf else None
         res.append({
             "workload": name, "direction": label, "d": d, "n": n, "m": m, "k": k, "steps": steps,
@@ -375,9 +377,9 @@ def main() -> int:
     launched = kernels[dom]["launched"] or dom
     dom_ms = kernels[dom]["ms_avg"]
     dom_tflops = head["dominant_kernel_tflops"]
-    on_matrix_cores = launched.startswith(("chain_tile_kernel", "chain_quad_kernel", "dv_kernel", "factor_fused_kernel", "team_factor_kernel"))
+    on_matrix_cores = launched.startswith(("chain_tile_kernel", "chain_quad_kernel", "gemm_kernel", "dv_kernel", "factor_fused_kernel", "team_factor_kernel"))
     traffic, traffic_source = traffic_from_profiles(name, launched)
-    alg_bytes = chain_algorithmic_bytes(d, n, m, k) if dom == "chain_kernel" else None
+    alg_bytes = chain_algorithmic_bytes(d, n, m, k) if dom == "chain_kernel" and not launched.startswith("gemm_kernel") else None
     roofline = {
         "kernel": launched,                      # the instantiation that ran, as the launcher picked it
         "slot": dom,
