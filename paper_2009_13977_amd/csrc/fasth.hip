@@ -398,47 +398,35 @@ static SvdLayout make_svd_layout(int d, int n, int m, int k) {
 }
 
 // The layers on whole matrices: in the notation below, `first` is the factor applied transposed. Z1 = F^T X, Y = S (s Z1).
-static int dense_layer_forward(Dense& F, const float* Vf, Dense& S, const float* Vs, const float* X, float* Z1, float* scaled, const float* sigma,
-                               int mode, int rank, float* Y, hipStream_t st) {
-  F.lower = true;
-  const bool shared = S.owner == &F;  // one set of factors: Y' and H^T, then Y
+static int dense_layer_forward(const Dense& F, const float* Vf, const Dense& S, const float* Vs, const float* X, float* Z1, float* scaled,
+                               const float* sigma, int mode, int rank, float* Y, hipStream_t st) {
   const Dense* D[2] = {&F, &S};
   const float* V[2] = {Vf, Vs};
-  const PackJob jobs[1] = {F.pack_x(X, F.d)};
-  int rc = dense_factors(D, V, shared ? 1 : 2, jobs, 1, st);
-  if (rc != FASTH_OK || (rc = dense_matrices(D, V, shared ? 1 : 2, true, st)) != FASTH_OK) return rc;
-  if (shared) {
-    Dense plain = F;
-    plain.lower = false;
-    const Dense* one[1] = {&plain};
-    if ((rc = dense_matrices(one, V, 1, false, st)) != FASTH_OK) return rc;
-  }
-  if ((rc = dense_apply(F, true, X, F.d, Z1, sigma, mode, rank, scaled, nullptr, st)) != FASTH_OK) return rc;
-  PackArgs pk{};
-  pk.job[0] = S.pack_x(scaled, rank);
-  if ((rc = launch_pack(pk, 1, FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+  const int count = S.owner == &F ? 1 : 2;  // one set of factors?
+  int rc = dense_factors(D, V, count, nullptr, 0, st);
+  if (rc != FASTH_OK || (rc = dense_matrices(D, V, count, st)) != FASTH_OK) return rc;
+  if ((rc = dense_apply(F, true, X, F.d, Z1, sigma, mode, rank, scaled, F.left(), st)) != FASTH_OK) return rc;
+  if ((rc = dense_pack(S.pack_right(scaled, rank), FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
   return dense_apply(S, false, scaled, rank, Y, nullptr, 0, 0, nullptr, nullptr, st);
 }
 
-static int dense_layer_backward(Dense& F, const float* Vf, Dense& S, const float* Vs, const float* G, const float* Z1, float* dZ2, float* scaled,
-                                const float* sigma, int mode, int rank, float* dVf, float* dsigma, float* dVs, float* dX, hipStream_t st) {
-  F.lower = true;
-  const bool shared = S.owner == &F;
-  int rc = dense_apply(S, true, G, S.d, dZ2, sigma, mode, rank, scaled, S.at(S.L.dXa), st);
+static int dense_layer_backward(const Dense& F, const float* Vf, const Dense& S, const float* Vs, const float* G, const float* Z1, float* dZ2,
+                                float* scaled, const float* sigma, int mode, int rank, float* dVf, float* dsigma, float* dVs, float* dX, hipStream_t st) {
+  int rc = dense_apply(S, true, G, S.d, dZ2, sigma, mode, rank, scaled, S.left(), st);
   if (rc != FASTH_OK) return rc;
-  if ((rc = dense_apply(F, false, scaled, rank, dX, nullptr, 0, 0, nullptr, F.at(F.L.dXa), st)) != FASTH_OK) return rc;
+  if ((rc = dense_pack(F.pack_right(scaled, rank), FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+  if ((rc = dense_apply(F, false, scaled, rank, dX, nullptr, 0, 0, nullptr, nullptr, st)) != FASTH_OK) return rc;
   {
     prof::Scope ps_(FASTH_KERNEL_DSIGMA, st, "dsigma_kernel");
     hipLaunchKernelGGL(dsigma_kernel, dim3((rank + 3) / 4), dim3(256), 0, st, (const float*)dZ2, Z1, sigma, dsigma, rank, S.m, mode);
     FASTH_HIP(hipGetLastError());
   }
-  if (!shared) {
-    const Dense* D[2] = {&S, &F};
+  const Dense* D[2] = {&S, &F};
+  if (S.owner != &F) {
     const float* V[2] = {Vs, Vf};
     float* dV[2] = {dVs, dVf};
     return dense_dv(D, V, dV, 2, false, st);
   }
-  const Dense* D[2] = {&S, &F};
   for (int i = 0; i < 2; ++i)  // both products' gradients are those of the same vectors: the second is added
     if ((rc = dense_dv(D + i, &Vf, &dVf, 1, i == 1, st)) != FASTH_OK) return rc;
   return FASTH_OK;
@@ -709,12 +697,11 @@ int fasth_forward(const fasth_shape* shape, const float* V, const float* X, floa
   if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (P.dense) {
-    Dense D = P.D;
-    D.lower = shape->transpose != 0;
-    const Dense* list[1] = {&D};
-    const PackJob jobs[1] = {D.pack_x(X, P.d)};
-    if ((rc = dense_factors(list, &V, 1, jobs, 1, st)) != FASTH_OK || (rc = dense_matrices(list, &V, 1, true, st)) != FASTH_OK) return rc;
-    return dense_apply(D, shape->transpose != 0, X, P.d, A, nullptr, 0, 0, nullptr, nullptr, st);
+    const bool t = shape->transpose != 0;
+    const Dense* list[1] = {&P.D};
+    const PackJob jobs[1] = {P.D.pack_right(X, P.d)};
+    if ((rc = dense_factors(list, &V, 1, jobs, t ? 0 : 1, st)) != FASTH_OK || (rc = dense_matrices(list, &V, 1, st)) != FASTH_OK) return rc;
+    return dense_apply(P.D, t, X, P.d, A, nullptr, 0, 0, nullptr, t ? P.D.left() : nullptr, st);
   }
   if ((rc = build_factors(P, V, st)) != FASTH_OK) return rc;
   return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st);
@@ -770,7 +757,7 @@ int fasth_prepare(const fasth_shape* shape, const float* V, void* workspace, siz
   if (P.dense) {
     const Dense* D[1] = {&P.D};
     if ((rc = dense_factors(D, &V, 1, nullptr, 0, st)) != FASTH_OK) return rc;
-    return dense_matrices(D, &V, 1, true, st);
+    return dense_matrices(D, &V, 1, st);
   }
   return build_factors(P, V, st);
 }
@@ -784,18 +771,11 @@ int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float*
   Product P = bind(shape->d, shape->n, shape->m, shape->k, workspace, dense_serves(shape->d, shape->n, shape->m));
   if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (P.dense && save_for_backward) {
-    PackArgs pk{};
-    pk.job[0] = P.D.pack_x(X, P.d);
-    if ((rc = launch_pack(pk, 1, FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
-    if (shape->transpose) {  // fasth_prepare leaves Y; the gradients of this product need Y'
-      Dense D = P.D;
-      D.lower = true;
-      const Dense* list[1] = {&D};
-      if ((rc = dense_matrices(list, &V, 1, false, st)) != FASTH_OK) return rc;
-    }
+  if (P.dense) {
+    const bool t = shape->transpose != 0, save = save_for_backward != 0;
+    if (save && !t && (rc = dense_pack(P.D.pack_right(X, P.d), FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+    return dense_apply(P.D, t, X, P.d, A, nullptr, 0, 0, nullptr, save && t ? P.D.left() : nullptr, st);
   }
-  if (P.dense) return dense_apply(P.D, shape->transpose != 0, X, P.d, A, nullptr, 0, 0, nullptr, nullptr, st);
   P.exclusive = save_for_backward != 0;
   return run_chain(P, V, X, A, shape->transpose, true, nullptr, 0, st, save_for_backward != 0);
 }
@@ -810,10 +790,10 @@ int fasth_backward(const fasth_shape* shape, const float* V, const float* G, flo
   if (workspace_bytes < workspace_of(P)) return FASTH_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (P.dense) {
-    Dense D = P.D;
-    D.lower = shape->transpose != 0;
-    const Dense* list[1] = {&D};
-    if ((rc = dense_apply(D, !shape->transpose, G, P.d, dX, nullptr, 0, 0, nullptr, D.at(D.L.dXa), st)) != FASTH_OK) return rc;
+    const bool t = shape->transpose != 0;
+    const Dense* list[1] = {&P.D};
+    if (t && (rc = dense_pack(P.D.pack_right(G, P.d), FASTH_KERNEL_CHAIN, st)) != FASTH_OK) return rc;
+    if ((rc = dense_apply(P.D, !t, G, P.d, dX, nullptr, 0, 0, nullptr, t ? nullptr : P.D.left(), st)) != FASTH_OK) return rc;
     return dense_dv(list, &V, &dV, 1, false, st);
   }
   if ((rc = run_chain(P, V, G, dX, !shape->transpose, false, nullptr, 0, st)) != FASTH_OK) return rc;

@@ -26,7 +26,8 @@ namespace fasth {
 //   dV = -(Y D^T + Y' D) + E V,   Y' = T^T V,   E = U + U^T + diag(Z),   Z = Y' D Y^T,   U = striu(Z),
 // and V H = -T^-T Y, i.e. Y = -Y' H and Y' = -Y H^T, turns it for D = H K into Z = -W Y^T with W = Y K (skew, as K is), Y' D = -W and
 // Y D^T = -W H^T = -W + W V^T T^T V = -W - Z V, so that dV = 2 W + (E + Z) V = 2 W + 2 U V.
-// For A = H^T X the same holds with T^T in the place of T (lower triangular: stril in the place of striu).
+// For A = H^T X with G = dL/dA the gradient with respect to H is D = X G^T and Q = H^T D = A G^T; the rest is the same, from the same Y. So one
+// preparation serves products in both directions, saved or not.
 // All products are three-piece bf16 products (fasth_gemm.h): fp32 in, fp32 out, fp32 accumulators.
 // ------------------------------------------------------------------------------------------
 
@@ -75,7 +76,6 @@ struct InverseArgs {
   const float* S;       // [np][256]: a group's rows against its rows, the blocks of 64 x 64 on and above the diagonal
   const float* factor;  // [np / 64][64][64]
   char* T;              // the groups' T as operands, rows stay rows (np x 256)
-  char* Tt;             // their transposes
   int np;
 };
 struct InversePair {
@@ -157,13 +157,6 @@ __global__ void __launch_bounds__(256) block_inverse_kernel(InversePair pair) {
     for (int e = 0; e < 8; ++e) v[e] = row / 64 <= c ? (float)flat[row * 17 + 8 * k8 + e] : 0.f;
     store_unit(p.T, kt, b0 * 64 + row, col0 / 8 + k8, v);
   }
-  for (int u = threadIdx.x; u < blocks * 128; u += 256) {  // eight rows of a column
-    const int col = u & 15, r8 = u >> 4;
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = r8 / 8 <= c ? (float)flat[(8 * r8 + e) * 17 + col] : 0.f;
-    store_unit(p.Tt, kt, b0 * 64 + col0 + col, r8, v);
-  }
 }
 
 // K = (Q - Q^T) / 2, Q the sum of `parts` matrices of d x d: d = 1024, one part: 12 MB in 5 us, mostly launch and one trip to memory.
@@ -215,14 +208,14 @@ __global__ void __launch_bounds__(256) skew_kernel(SkewPair pair) {
 struct DenseLayout {
   size_t Va, Vt;          // V as operands: rows stay rows; its transpose
   size_t S, factor;       // the groups' Gram matrices, the factors of 64 rows
-  size_t T, Tt;           // the groups' T and T^T as operands
+  size_t T;               // the groups' T as operands
   size_t TV;              // T_g V_g as operands
   size_t P;               // the product of the groups so far
   size_t Y, Ya;           // Y fp32 and as operands
-  size_t Yt;              // Y' = T^T V as operands
   size_t H, Ht;           // H and H^T as operands
   // saved by the forward pass / used by the backward pass
-  size_t Xa, dXa, Q, K, W, Wa, U;
+  size_t left, right;     // operands of Q = left right^T: dX and X or, of a product H^T X, A and G
+  size_t Q, K, W, Wa, U;
   int q_split;
   size_t total;
 };
@@ -248,7 +241,6 @@ static DenseLayout make_dense_layout(int d, int n, int m) {
   L.S = take(np * kGroup * 4);
   L.factor = take(np * 64 * 4);
   L.T = take(np * kGroup * 6);
-  L.Tt = take(np * kGroup * 6);
   L.TV = take(packed_bytes(n, d));
   L.P = take((size_t)d * d * 4);
   L.Y = take((size_t)n * d * 4);
@@ -256,14 +248,13 @@ static DenseLayout make_dense_layout(int d, int n, int m) {
   L.H = take(packed_bytes(d, d));
   L.Ht = take(packed_bytes(d, d));
   L.q_split = dense_q_split(d, m);
-  L.Xa = take(packed_bytes(d, m));
-  L.dXa = take(packed_bytes(d, m));
+  L.left = take(packed_bytes(d, m));
+  L.right = take(packed_bytes(d, m));
   L.Q = take((size_t)L.q_split * d * d * 4);
   L.K = take((size_t)d * d * 4);
   L.W = take((size_t)n * d * 4);
   L.Wa = take(packed_bytes(n, d));
   L.U = take(packed_bytes(n, n));
-  L.Yt = take(packed_bytes(n, d));
   L.total = off;
   return L;
 }
@@ -287,7 +278,7 @@ static int launch_gemm_as(GemmList& list, hipStream_t stream) {
     p.tiles = p.flags & kUpper ? rt * (rt + 1) / 2 : rt * ct * std::max(p.split, 1);
     // (rows of a triangular operand take different times: every XCD takes all of them)
     if (!(p.flags & kUpper) && p.split <= 1)
-      p.xcd_rows = (p.term.part & (kFromRow | kToRow)) ? (ct % 8 == 0 ? 1 : 0) : xcd_cut(rt, ct, 6. * BM, (BF ? 4. : 6.) * BN);
+      p.xcd_rows = p.term.upper ? (ct % 8 == 0 ? 1 : 0) : xcd_cut(rt, ct, 6. * BM, (BF ? 4. : 6.) * BN);
     width = std::max(width, (p.tiles + 7) / 8 * 8);
   }
   constexpr size_t lds = gemm_lds<BM, BN, KS>();
@@ -356,7 +347,6 @@ static int launch_pack(PackArgs& args, int count, int slot, hipStream_t stream) 
 // One product on its slice of a workspace.
 struct Dense {
   int d = 0, n = 0, m = 0;
-  bool lower = false;            // the product is H^T X: T^T in the place of T
   const Dense* owner = nullptr;  // whose workspace has T, Y and H, if not this one's
   DenseLayout L;
   char* ws = nullptr;
@@ -365,16 +355,23 @@ struct Dense {
   float* f(size_t off) const { return reinterpret_cast<float*>(ws + off); }
   int kt(int x) const { return pad64(x) / 32; }
   PackJob pack_v(const float* V) const { return PackJob{V, at(L.Va), at(L.Vt), n, d, pad64(n) / 64 * (pad64(d) / 64)}; }
-  // the inputs of the saved product ([rows][m], rows beyond are zero) as operands for the backward pass
-  PackJob pack_x(const float* X, int rows) const { return PackJob{X, at(L.Xa), nullptr, rows, m, pad64(d) / 64 * (pad64(m) / 64)}; }
-  // H or H^T as operands, Y (or, of a lower product, Y' = T^T V) as operands
+  // X of a product H X, or G of a product H^T X ([rows][m], rows beyond are zero), for dV
+  PackJob pack_right(const float* X, int rows) const { return PackJob{X, at(L.right), nullptr, rows, m, pad64(d) / 64 * (pad64(m) / 64)}; }
+  char* left() const { return at(L.left); }
+  // H or H^T, and Y, as operands
   char* matrix(bool transpose) const { const Dense& F = factors(); return F.at(transpose ? F.L.Ht : F.L.H); }
-  char* y() const { const Dense& F = factors(); return F.at(lower ? F.L.Yt : F.L.Ya); }
+  char* y() const { const Dense& F = factors(); return F.at(F.L.Ya); }
 };
 
 static int group_rows(const Dense& P, int g) { return std::min(kGroup, P.n - g * kGroup); }
 // (row, k) of operands with kt tiles of k
 static char* operand_cell(char* base, int kt, int row, int k) { return base + ((size_t)(row / 16) * kt + k / 32) * kTileBytes; }
+
+static int dense_pack(const PackJob& job, int slot, hipStream_t stream) {
+  PackArgs args{};
+  args.job[0] = job;
+  return launch_pack(args, 1, slot, stream);
+}
 
 // The groups' T of up to two products; `jobs`: what else is to be packed in the first launch.
 static int dense_factors(const Dense* const* D, const float* const* V, int count, const PackJob* jobs, int njobs, hipStream_t stream) {
@@ -392,13 +389,13 @@ static int dense_factors(const Dense* const* D, const float* const* V, int count
     const Dense& P = *D[i];
     const int groups = (P.n + kGroup - 1) / kGroup;
     fac.a[i] = FactorArgs64{P.f(P.L.S), P.f(P.L.factor), P.n, pad64(P.n)};
-    inv.a[i] = InverseArgs{P.f(P.L.S), P.f(P.L.factor), P.at(P.L.T), P.at(P.L.Tt), pad64(P.n)};
+    inv.a[i] = InverseArgs{P.f(P.L.S), P.f(P.L.factor), P.at(P.L.T), pad64(P.n)};
     width = std::max(width, groups);
     for (int g = 0; g < groups; ++g) {
       if (gram.count == kGemmProblems && (rc = launch_gemm<false, true>(gram, slot, stream)) != FASTH_OK) return rc;
       GemmProblem& p = gram.add();
       char* rows = operand_cell(P.at(P.L.Va), P.kt(P.d), g * kGroup, 0);
-      p.term = GemmTerm{rows, rows, P.kt(P.d), P.kt(P.d), P.d, 0};
+      p.term = GemmTerm{rows, rows, P.kt(P.d), P.kt(P.d), P.d, false};
       p.rows = p.cols = pad64(group_rows(P, g)); p.ldo = kGroup; p.flags = kUpper; p.alpha = 1.f;
       p.out = P.f(P.L.S) + (size_t)g * kGroup * kGroup;
     }
@@ -415,15 +412,15 @@ static int dense_factors(const Dense* const* D, const float* const* V, int count
   return FASTH_OK;
 }
 
-// Y and H of up to two products, or, of lower ones, Y' and H^T (which leaves H too); without `matrix` Y or Y' alone.
-static int dense_matrices(const Dense* const* D, const float* const* V, int count, bool matrix, hipStream_t stream) {
+// Y, H and H^T of up to two products.
+static int dense_matrices(const Dense* const* D, const float* const* V, int count, hipStream_t stream) {
   const int slot = FASTH_KERNEL_FACTOR;
   int rc, steps = 0, groups[2] = {0, 0};
   for (int i = 0; i < count; ++i) {
     groups[i] = (D[i]->n + kGroup - 1) / kGroup;
     steps = std::max(steps, groups[i]);
   }
-  auto group_at = [&](int i, int step) { return D[i]->lower ? step : groups[i] - 1 - step; };
+  auto group_at = [&](int i, int step) { return groups[i] - 1 - step; };
   auto y_of = [](GemmProblem& p, const Dense& P, int g) {
     p.rows = group_rows(P, g); p.cols = p.ldo = P.d; p.alpha = 1.f;
     p.out = P.f(P.L.Y) + (size_t)g * kGroup * P.d;
@@ -438,8 +435,8 @@ static int dense_matrices(const Dense* const* D, const float* const* V, int coun
       if (tv.count == kGemmProblems && (rc = launch_gemm<true>(tv, slot, stream)) != FASTH_OK) return rc;
       GemmProblem& p = tv.add();
       y_of(p, P, g);
-      p.term = GemmTerm{operand_cell(P.at(P.lower ? P.L.Tt : P.L.T), kGroup / 32, g * kGroup, 0), reinterpret_cast<const char*>(V[i] + (size_t)g * kGroup * P.d),
-                        kGroup / 32, P.d, group_rows(P, g), P.lower ? kToRow : kFromRow};
+      p.term = GemmTerm{operand_cell(P.at(P.L.T), kGroup / 32, g * kGroup, 0), reinterpret_cast<const char*>(V[i] + (size_t)g * kGroup * P.d),
+                        kGroup / 32, P.d, group_rows(P, g), true};
       if (step > 0) {
         p.out = nullptr;
         p.along = operand_cell(P.at(P.L.TV), P.kt(P.d), g * kGroup, 0);
@@ -457,20 +454,19 @@ static int dense_matrices(const Dense* const* D, const float* const* V, int coun
       if (step > 0) {
         GemmProblem& p = y.add();
         y_of(p, P, g);
-        p.term = GemmTerm{operand_cell(P.at(P.L.TV), P.kt(P.d), g * kGroup, 0), P.at(P.L.P), P.kt(P.d), P.d, P.d, 0};
+        p.term = GemmTerm{operand_cell(P.at(P.L.TV), P.kt(P.d), g * kGroup, 0), P.at(P.L.P), P.kt(P.d), P.d, P.d, false};
       }
       const bool last = step + 1 == groups[i];
-      if (last && !matrix) continue;
       GemmProblem& p = h.add();
-      p.term = GemmTerm{operand_cell(P.at(P.L.Vt), P.kt(P.n), 0, g * kGroup), reinterpret_cast<const char*>(P.f(P.L.Y) + (size_t)g * kGroup * P.d), P.kt(P.n), P.d, group_rows(P, g), 0};
+      p.term = GemmTerm{operand_cell(P.at(P.L.Vt), P.kt(P.n), 0, g * kGroup), reinterpret_cast<const char*>(P.f(P.L.Y) + (size_t)g * kGroup * P.d), P.kt(P.n), P.d, group_rows(P, g), false};
       p.rows = p.cols = p.ldo = P.d; p.alpha = -1.f;
       if (step == 0) p.diag = 1.f;
       else { p.add = P.f(P.L.P); p.beta = 1.f; }
       if (!last) {
         p.out = P.f(P.L.P);
       } else {
-        p.along = P.matrix(P.lower); p.along_kt = P.kt(P.d);
-        p.across = P.matrix(!P.lower); p.across_kt = P.kt(P.d);
+        p.along = P.matrix(false); p.along_kt = P.kt(P.d);
+        p.across = P.matrix(true); p.across_kt = P.kt(P.d);
       }
     }
     if ((rc = launch_gemm<true>(y, slot, stream)) != FASTH_OK || (rc = launch_gemm<true>(h, slot, stream)) != FASTH_OK) return rc;
@@ -484,7 +480,7 @@ static int dense_apply(const Dense& P, bool transpose, const float* in, int in_r
                        float* scaled, char* along, hipStream_t stream) {
   GemmList list;
   GemmProblem& g = list.add();
-  g.term = GemmTerm{P.matrix(transpose), reinterpret_cast<const char*>(in), P.kt(P.d), P.m, in_rows, 0};
+  g.term = GemmTerm{P.matrix(transpose), reinterpret_cast<const char*>(in), P.kt(P.d), P.m, in_rows, false};
   g.rows = P.d; g.cols = g.ldo = P.m; g.alpha = 1.f;
   g.out = out;
   g.scaled = scaled; g.scale = scale; g.scale_mode = scale_mode; g.scaled_rows = scaled_rows;
@@ -492,7 +488,7 @@ static int dense_apply(const Dense& P, bool transpose, const float* in, int in_r
   return launch_gemm<true>(list, FASTH_KERNEL_CHAIN, stream);
 }
 
-// dV of up to two products from X and dX as operands (pack_x, dense_apply).
+// dV of up to two products from their `left` and `right` operands (dense_apply, pack_right).
 static int dense_dv(const Dense* const* D, const float* const* V, float* const* dV, int count, bool accumulate, hipStream_t stream) {
   const int slot = FASTH_KERNEL_DV;
   GemmList q, w, z, v;
@@ -501,22 +497,21 @@ static int dense_dv(const Dense* const* D, const float* const* V, float* const* 
   for (int i = 0; i < count; ++i) {
     const Dense& P = *D[i];
     GemmProblem& a = q.add();
-    a.term = GemmTerm{P.at(P.L.dXa), P.at(P.L.Xa), P.kt(P.m), P.kt(P.m), P.m, 0};
+    a.term = GemmTerm{P.left(), P.at(P.L.right), P.kt(P.m), P.kt(P.m), P.m, false};
     a.rows = a.cols = a.ldo = P.d; a.alpha = 1.f; a.out = P.f(P.L.Q); a.split = P.L.q_split;
     sk.a[i] = SkewArgs{P.f(P.L.Q), P.f(P.L.K), P.d, P.L.q_split};
     dmax = std::max(dmax, P.d);
     GemmProblem& b = w.add();
-    b.term = GemmTerm{P.y(), P.at(P.L.K), P.kt(P.d), P.d, P.d, 0};
+    b.term = GemmTerm{P.y(), P.at(P.L.K), P.kt(P.d), P.d, P.d, false};
     b.rows = P.n; b.cols = b.ldo = P.d; b.alpha = 1.f; b.out = P.f(P.L.W);
     b.along = P.at(P.L.Wa); b.along_kt = P.kt(P.d);
     GemmProblem& c = z.add();
-    // striu(W Y^T), or the transpose of stril(W Y^T), striu(Y W^T)
-    c.term = GemmTerm{P.lower ? P.y() : P.at(P.L.Wa), P.lower ? P.at(P.L.Wa) : P.y(), P.kt(P.d), P.kt(P.d), P.d, 0};
+    // striu(W Y^T)
+    c.term = GemmTerm{P.at(P.L.Wa), P.y(), P.kt(P.d), P.kt(P.d), P.d, false};
     c.rows = c.cols = c.ldo = P.n; c.alpha = 1.f; c.flags = kUpper | kStrict;
-    if (P.lower) { c.across = P.at(P.L.U); c.across_kt = P.kt(P.n); }
-    else { c.along = P.at(P.L.U); c.along_kt = P.kt(P.n); }
+    c.along = P.at(P.L.U); c.along_kt = P.kt(P.n);
     GemmProblem& e = v.add();
-    e.term = GemmTerm{P.at(P.L.U), reinterpret_cast<const char*>(V[i]), P.kt(P.n), P.d, P.n, P.lower ? kToRow : kFromRow};
+    e.term = GemmTerm{P.at(P.L.U), reinterpret_cast<const char*>(V[i]), P.kt(P.n), P.d, P.n, true};
     e.rows = P.n; e.cols = e.ldo = P.d; e.alpha = -2.f; e.beta = 2.f; e.add = P.f(P.L.W); e.out = dV[i];
     e.flags = accumulate ? kAccumulate : 0;
   }

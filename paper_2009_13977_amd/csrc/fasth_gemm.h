@@ -77,14 +77,12 @@ __global__ void __launch_bounds__(256) pack_kernel(PackArgs args) {
 // ------------------------------------------------------------------------------------------
 // Products
 // ------------------------------------------------------------------------------------------
-// Which k a tile of rows [r0, r0 + BM) and columns [c0, c0 + BN) needs, for triangular operands.
-enum { kFromRow = 1, kToRow = 2, kToCol = 4 };
-
 struct GemmTerm {
   const char* A;     // operands; lda tiles of k per row of tiles
   const char* B;     // operands, or fp32 [k][cols] (the kernels' BF)
   int lda, ldb;      // tiles of k per row of tiles (fp32 B: its row length)
-  int K, part;       // inner indices (fp32 B: its rows)
+  int K;             // inner indices (fp32 B: its rows)
+  bool upper;        // A is upper triangular: a tile of rows from r0 on needs k from r0 on
 };
 enum { kUpper = 1, kStrict = 2, kAccumulate = 4 };
 // out = alpha sum + beta add, + 1 on the diagonal with diag = 1. Every output is optional.
@@ -216,12 +214,9 @@ __device__ __forceinline__ bool gemm_tile(const GemmProblem& p, int& r0, int& c0
 }
 
 // First and last tile of k.
-__device__ __forceinline__ void gemm_range(const GemmTerm& g, int r0, int c0, int BM, int BN, int split, int part, int& beg, int& end) {
-  beg = 0;
+__device__ __forceinline__ void gemm_range(const GemmTerm& g, int r0, int split, int part, int& beg, int& end) {
+  beg = g.upper ? r0 / 32 : 0;
   end = pad64(g.K) / 32;
-  if (g.part & kFromRow) beg = r0 / 32;
-  if (g.part & kToRow) end = min(end, (r0 + BM) / 32);
-  if (g.part & kToCol) end = min(end, (c0 + BN) / 32);
   if (split > 0) {
     const int each = ((end - beg) / 2 + split - 1) / split * 2;
     beg += part * each;
@@ -288,7 +283,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
   const int ra = r0 / 16 + wm * RT, cb = c0 / 16 + wn * CT, last_r = pad64(p.rows) / 16 - 1, last_c = pad64(p.cols) / 16 - 1;
   const GemmTerm g = p.term;
   int beg, end;
-  gemm_range(g, r0, c0, BM, BN, p.split, part, beg, end);
+  gemm_range(g, r0, p.split, part, beg, end);
   int k = beg + ks;
   if (k < end) {
     const char* A[RT];

@@ -104,6 +104,60 @@ def test_prepared_products():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("first", [False, True])
+@pytest.mark.parametrize("transpose", [False, True])
+def test_saved_applies_after_a_forward_call(first, transpose):
+    """A forward call leaves what fasth_prepare leaves: saved applies in either direction and their gradients, on a workspace that no
+    other call has seen."""
+    import torch
+    from paper_2009_13977_amd import binding as B
+    d, n, m, k = 500, 520, 800, 20
+    print(f"matrix forward then apply d={d} n={n} m={m} {first} {transpose}", flush=True)
+    p = synthetic.householder_problem(d, n, m, seed=107000)
+    V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
+    A, dX, dV = torch.empty_like(X), torch.empty_like(X), torch.empty_like(V)
+    ws = B.new_workspace(B.fasth_workspace_bytes(d, n, m, k))
+    ws.fill_(0xff)
+    B.fasth_forward(V, G, A, ws, k, first)
+    B.fasth_apply(V, X, A, ws, k, transpose, True)
+    B.fasth_backward(V, G, dV, dX, ws, k, transpose)
+    torch.cuda.synchronize()
+    for name, g, r in zip(("A", "dV", "dX"), (A, dV, dX), orc.product_gradients(p["V"], p["X"], p["G"], transpose=transpose)):
+        assert_close(g.cpu().numpy(), r, name, rows=name == "dV")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transpose", [False, True])
+def test_saved_applies_form_nothing_again(transpose):
+    """Prepared once, a saved apply is one product (and its operand), in either direction, and the two calls are exactly fasth_forward."""
+    import torch
+    from paper_2009_13977_amd import binding as B
+    d, n, m, k = 500, 520, 800, 20
+    print(f"matrix saved applies d={d} n={n} m={m} {transpose}", flush=True)
+    p = synthetic.householder_problem(d, n, m, seed=108000)
+    V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
+    out = []
+    for split in (False, True):
+        A, dX, dV = torch.empty_like(X), torch.empty_like(X), torch.empty_like(V)
+        ws = B.new_workspace(B.fasth_workspace_bytes(d, n, m, k))
+        if split:
+            B.fasth_prepare(V, m, ws, k)
+            torch.cuda.synchronize()
+            B.fasth_profile_enable(True)
+            B.fasth_apply(V, X, A, ws, k, transpose, True)
+            launches = {name: count for name, (_, count) in B.fasth_profile_collect().items()}
+            B.fasth_profile_enable(False)
+            assert 1 <= launches.pop("chain_kernel") <= 2 and not any(launches.values()), launches
+        else:
+            B.fasth_forward(V, X, A, ws, k, transpose)
+        B.fasth_backward(V, G, dV, dX, ws, k, transpose)
+        torch.cuda.synchronize()
+        out.append((A, dV, dX))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
 def test_captured_and_replayed():
     import torch
     from paper_2009_13977_amd import binding as B
