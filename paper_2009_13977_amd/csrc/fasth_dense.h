@@ -13,10 +13,11 @@ namespace fasth {
 //   H = I - V^T T V = I - V^T Y,   Y = T V,     H^T = I - V^T T^T V.
 // T is formed for groups of 256 reflections only. With P = H_(g+1) ... H_G the product of the groups applied before group g, the rows
 // of Y that belong to it are Y_g = T_g V_g P, and P - V_g^T Y_g is the product with it: from P = I to P = H. (All of T, by doubling
-// blocks, is as much work, and H is less exact: at n = d = 1024 its error is 4.2e-7, 2.0e-7 of it from the rounding of S beyond the groups
-// and 2.7e-7 from that of T.) Errors of A, dV and dX, n = d = 1024, normal V: 2.7e-7, 4.2e-7, 2.7e-7 (chain of blocks of 64: 4.5e-7, 5.1e-7, 4.1e-7);
-// with rows that are far from orthogonal the size of the group counts: one direction plus 0.3 times normal rows: 3.1e-6, 8.3e-6, 3.1e-6 (3.4e-6,
-// 6.3e-6, 3.0e-6), at d = 512 3.4e-6, 9.0e-6, 3.4e-6 (blocks of 32: 2.0e-6, 4.1e-6, 2.0e-6).
+// blocks, is as much work, and H is less exact.) Errors of A, dV and dX against fp64, n = d = 1024 and in brackets the chain of blocks of 64: normal V
+// 2.1e-7, 3.2e-7, 2.0e-7 (4.5e-7, 4.8e-7, 4.1e-7). Rows far from orthogonal, A and dV: positive 2.7e-7, 1.1e-6 (1.4e-6, 1.8e-6); one direction
+// plus 0.3 times normal 2.9e-7, 1.4e-6 (3.4e-6, 6.3e-6); four directions plus 0.01 times normal 5.4e-7, 7.8e-6 (2.8e-6, 2.9e-5). At d = 512, where the chain has
+// blocks of 32: 1.9e-7, 2.9e-7 (5.1e-7, 7.4e-7); 2.3e-7, 6.1e-7 (9.4e-7, 1.3e-6); 3.3e-7, 9.2e-7 (2.0e-6, 4.1e-6); 6.8e-7, 5.1e-6 (1.1e-6, 8.6e-6). That takes S and the
+// inverse in fp64 up to T: with S from three-piece products and fp32 factors of 64 rows the last were 2.3e-6, 2.3e-5.
 // The chain of blocks costs 12 d n m operations per gradient step, one block after the other. As matrices a step costs 6 d^2 m and a
 // part that does not depend on m:
 //   forward   A = H X
@@ -33,49 +34,179 @@ namespace fasth {
 
 constexpr int kGroup = 256;  // reflections that share a T
 
-// The factors of 64 rows, (diag(S_bb) / 2 + striu(S_bb))^-1; a row that does not exist has a one on the diagonal. Bound by the steps of the
-// inversion, one after the other: 5 us for any number of blocks up to one per compute unit.
+// S: the groups' V_g V_g^T, its tiles of 16 x 16 on and above the diagonal, with fp64 matrix instructions from the fp32 rows as they are. With rows far from
+// orthogonal the rounding of S decides the error of H (T amplifies it). One tile per workgroup, its waves share the elements of the rows. Bound by the matrix
+// instructions, 109 cycles each: d = n = 1024: 544 workgroups, up to three per compute unit, 14.3 us (with fp32 instructions and a sum in fp64 every 16
+// elements some 8, but T is then off by 9e-8 of its size where the rows are normal and by 8e-7 where they are near one direction; here by 1e-14 and 1e-11).
+// What else the step needs of V and X as operands is packed in the same launch, by workgroups behind these.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kGroupTiles = (kGroup / 16) * (kGroup / 16 + 1) / 2;
+struct GramArgs {
+  const float* V;  // [n][d]
+  double* S;       // [np][256]
+  int n, d, tiles; // tiles: kGroupTiles per group (0: no product)
+};
+struct GramPair {
+  GramArgs a[2];   // blockIdx.y
+  int width;       // workgroups with a larger blockIdx.x pack
+};
+template <int VEC>  // floats per load: 4 where d is a multiple of it, else 1
+__global__ void __launch_bounds__(256) gram_kernel(GramPair pair, PackArgs pack) {
+  typedef double Part[4][16][17];
+  __shared__ __align__(16) char lds[std::max(sizeof(Part), sizeof(PackTile))];
+  if ((int)blockIdx.x >= pair.width) {
+    const PackJob& job = pack.job[blockIdx.y];
+    const int block = (int)blockIdx.x - pair.width;
+    if (block < job.blocks) pack_block(job, block, *reinterpret_cast<PackTile*>(lds));
+    return;
+  }
+  if (blockIdx.y >= 2) return;
+  Part& part = *reinterpret_cast<Part*>(lds);
+  const GramArgs& p = pair.a[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, i = lane & 15;
+  const int per = p.tiles / 8, index = (int)blockIdx.x >> 3;  // workgroups of one XCD take consecutive tiles, which share rows
+  if (index >= per) return;
+  const int tile = ((int)blockIdx.x & 7) * per + index, g = tile / kGroupTiles, t = tile % kGroupTiles;
+  int tj = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);  // tile columns of 1, 2, ... tiles
+  while ((tj + 1) * (tj + 2) / 2 <= t) ++tj;
+  while (tj * (tj + 1) / 2 > t) --tj;
+  const int ti = t - tj * (tj + 1) / 2, rows = min(kGroup, p.n - g * kGroup);
+  if (16 * tj >= pad64(rows)) return;
+  const BufferDesc desc = make_buffer(p.V + (size_t)g * kGroup * p.d, (size_t)rows * p.d * sizeof(float));  // rows that do not exist read as zero
+  // lane (q, i): of each 16 elements the four from 4 q on of rows i (the sum may run in any order); 64 elements are a step, a step ahead is fetched
+  const unsigned left = (unsigned)(16 * ti + i) * (unsigned)p.d, right = (unsigned)(16 * tj + i) * (unsigned)p.d;
+  BufVec<4> a[2][4], b[2][4];
+  auto fetch = [&](int s, int k0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int k = k0 + 16 * c + 4 * q;
+#pragma unroll
+      for (int e = 0; e < 4; e += VEC) {
+        const bool in = k + e < p.d;
+        const BufVec<VEC> x = buffer_load<VEC>(desc, in ? (left + k + e) * 4u : kOob, 0), y = buffer_load<VEC>(desc, in ? (right + k + e) * 4u : kOob, 0);
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) { a[s][c].e[e + u] = x.e[u]; b[s][c].e[e + u] = y.e[u]; }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);  // (else the loads wait until they are needed)
+  };
+  f64x4 acc[2] = {};
+  auto multiply = [&](int s) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s][c].e[e], (double)b[s][c].e[e], acc[e & 1], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int k = 64 * wave;
+  fetch(0, k);
+  for (; k < p.d; k += 512) {
+    fetch(1, k + 256);
+    multiply(0);
+    fetch(0, k + 512);
+    multiply(1);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[wave][q + 4 * e][i] = acc[0][e] + acc[1][e];
+  __syncthreads();
+  const int r = tid >> 4, c = tid & 15;
+  p.S[(size_t)(g * kGroup + 16 * ti + r) * kGroup + 16 * tj + c] = (part[0][r][c] + part[1][r][c]) + (part[2][r][c] + part[3][r][c]);
+}
+
+// The factors of 64 rows, (diag(S_bb) / 2 + striu(S_bb))^-1 = M^-1; a row that does not exist has a one on the diagonal. The inverse in fp32, F, and one step
+// of refinement in fp64, F + F (I - M F). Bound by the steps of the inversion and the two products, one after the other: 7.2 us for any number of blocks up to one
+// per compute unit (4.8 without the refinement).
 struct FactorArgs64 {
-  const float* S;  // [np][256]
-  float* factor;   // [np / 64][64][64]
+  const double* S;  // [np][256]
+  double* factor;   // [np / 64][64][64]
   int n, np;
 };
 struct FactorPair64 {
   FactorArgs64 a[2];  // blockIdx.y
 };
 __global__ void __launch_bounds__(512) block_factor_kernel(FactorPair64 pair) {
-  constexpr int LD = 68;
-  __shared__ __align__(16) float M[64 * LD + invert_scratch_floats(64)];
+  constexpr int LD = 68, LDD = 66;
+  __shared__ __align__(16) float F[64 * LD + invert_scratch_floats(64)];
+  __shared__ double M[64 * LDD];
   const FactorArgs64& p = pair.a[blockIdx.y];
   const int r0 = (int)blockIdx.x * 64, tid = threadIdx.x;
   if (r0 >= p.np) return;  // whole workgroup
-  float* Xs = M + 64 * LD;
-  float s[8];
+  float* Xs = F + 64 * LD;
+  double s[8];
 #pragma unroll
   for (int it = 0; it < 8; ++it) s[it] = p.S[(size_t)(r0 + (tid >> 6) + 8 * it) * kGroup + r0 % kGroup + (tid & 63)];
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int r = (tid >> 6) + 8 * it, c = tid & 63;
-    const float v = r0 + r >= p.n || r0 + c >= p.n ? (r == c ? 1.f : 0.f) : r < c ? s[it] : r == c ? 0.5f * s[it] : 0.f;
-    M[r * LD + c] = v;
-    diag_scratch_store(Xs, 64, r, c, v);
+    const double v = r0 + r >= p.n || r0 + c >= p.n ? (r == c ? 1. : 0.) : r < c ? s[it] : r == c ? 0.5 * s[it] : 0.;
+    M[r * LDD + c] = v;
+    F[r * LD + c] = (float)v;
+    diag_scratch_store(Xs, 64, r, c, (float)v);
   }
   __syncthreads();
-  invert_upper_lds<true>(M, Xs, 64, LD);
+  invert_upper_lds<true>(F, Xs, 64, LD);
+  // tiles of 16 x 16 on and above the diagonal, the longest sums first: a wave's one, and a second for two waves
+  const int lane = tid & 63, wave = tid >> 6, q = lane >> 4, i = lane & 15;
+  const int tiles = wave < 6 ? 1 : 2;
+  auto row_of = [&](int u) { return u > 0 ? wave - 4 : (0x10210100 >> (4 * wave)) & 15; };
+  auto column_of = [&](int u) { return u > 0 ? wave - 4 : (0x10321323 >> (4 * wave)) & 15; };
+  f64x4 acc[2] = {};
 #pragma unroll
-  for (int it = 0; it < 8; ++it) p.factor[(size_t)r0 * 64 + tid + 512 * it] = M[((tid >> 6) + 8 * it) * LD + (tid & 63)];
+  for (int u = 0; u < 2; ++u) {  // I - M F
+    if (u >= tiles) break;
+    const int ti = row_of(u), tj = column_of(u);
+    for (int k0 = ti; k0 <= tj; ++k0) {  // lane (q, i) takes inner indices 16 k0 + 4 q ...: every read is issued before the first product
+      double m[4], f[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        m[e] = M[(16 * ti + i) * LDD + 16 * k0 + 4 * q + e];
+        f[e] = -(double)F[(16 * k0 + 4 * q + e) * LD + 16 * tj + i];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[e], f[e], acc[u], 0, 0, 0);
+    }
+    if (ti == tj)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u][e] += q + 4 * e == i ? 1. : 0.;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (u < tiles)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) M[(16 * row_of(u) + q + 4 * e) * LDD + 16 * column_of(u) + i] = acc[u][e];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    if (u >= tiles) break;
+    const int ti = row_of(u), tj = column_of(u);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[u][e] = F[(16 * ti + q + 4 * e) * LD + 16 * tj + i];
+    for (int k0 = ti; k0 <= tj; ++k0) {
+      double f[4], m[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        f[e] = (double)F[(16 * ti + i) * LD + 16 * k0 + 4 * q + e];
+        m[e] = M[(16 * k0 + 4 * q + e) * LDD + 16 * tj + i];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[e], m[e], acc[u], 0, 0, 0);
+    }
+    // (the tiles below the diagonal are nowhere read)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p.factor[(size_t)(r0 + 16 * ti + q + 4 * e) * 64 + 16 * tj + i] = acc[u][e];
+  }
 }
 
 // T of 256 rows from the factors of its blocks of 64 rows, as operands: block back substitution on 16 columns per workgroup,
 //   X_c = T_cc E,   X_b = -T_bb (sum over b < j <= c of S_bj X_j),
 // with fp64 matrix instructions (in fp32, 6 us less, its sums cost as much accuracy as all the other products of H together); wave w takes rows
-// 16 w ... of every block. All of S and T that a wave reads is fetched before the first product, one trip to memory. The blocks below the
-// diagonal are written as zeros. Bound by the chain of six products of the last block column, 13 us for any number of groups up to 16.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
+// 16 w ... of every block. What a wave reads of S and T for a block is fetched under the products of the block before. The blocks below the
+// diagonal are written as zeros. Bound by the chain of six products of the last block column.
 struct InverseArgs {
-  const float* S;       // [np][256]: a group's rows against its rows, the blocks of 64 x 64 on and above the diagonal
-  const float* factor;  // [np / 64][64][64]
-  char* T;              // the groups' T as operands, rows stay rows (np x 256)
+  const double* S;       // [np][256]: a group's rows against its rows, the blocks of 64 x 64 on and above the diagonal
+  const double* factor;  // [np / 64][64][64], tiles on and above the diagonal
+  char* T;               // the groups' T as operands, rows stay rows (np x 256)
   int np;
 };
 struct InversePair {
@@ -85,26 +216,26 @@ struct InversePair {
 template <int C>
 __device__ __forceinline__ void inverse_panel(const InverseArgs& p, int b0, int sub, double (*X)[64][17], double (*R)[17]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, i = lane & 15;
-  f32x4 s[(C * (C + 1) / 2) * 4 + 1], t[C * 4 + 1];  // lane (q, i): four consecutive inner indices 16 g + 4 q of row i, g = 0 .. 3
-  int at = 0;
-#pragma unroll
-  for (int b = C - 1; b >= 0; --b) {
+  f64x4 s[2][4 * (C > 0 ? C : 1)], t[2][4];  // lane (q, i): four consecutive inner indices 16 g + 4 q of row i, g = 0 .. 3
+  auto fetch = [&](int b, f64x4 (&to_s)[4 * (C > 0 ? C : 1)], f64x4 (&to_t)[4]) {
     const size_t row = (size_t)(b0 + b) * 64 + 16 * wave + i;
 #pragma unroll
     for (int j = C; j > b; --j)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) s[at++] = *reinterpret_cast<const f32x4*>(p.S + row * kGroup + j * 64 + 16 * g + 4 * q);
+      for (int g = 0; g < 4; ++g) to_s[4 * (C - j) + g] = *reinterpret_cast<const f64x4*>(p.S + row * kGroup + j * 64 + 16 * g + 4 * q);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) t[(C - 1 - b) * 4 + g] = *reinterpret_cast<const f32x4*>(p.factor + row * 64 + 16 * g + 4 * q);
-  }
+    for (int g = 0; g < 4; ++g)
+      to_t[g] = g >= wave ? *reinterpret_cast<const f64x4*>(p.factor + row * 64 + 16 * g + 4 * q) : f64x4{0., 0., 0., 0.};
+  };
+  if constexpr (C > 0) fetch(C - 1, s[0], t[0]);
   {
     const int r = tid >> 2, c = (tid & 3) * 4;
-    const f32x4 x = *reinterpret_cast<const f32x4*>(p.factor + ((size_t)(b0 + C) * 64 + r) * 64 + 16 * sub + c);
+    const f64x4 x = r / 16 <= sub ? *reinterpret_cast<const f64x4*>(p.factor + ((size_t)(b0 + C) * 64 + r) * 64 + 16 * sub + c) : f64x4{0., 0., 0., 0.};
 #pragma unroll
     for (int e = 0; e < 4; ++e) X[C][r][c + e] = x[e];
   }
   __syncthreads();
-  auto product = [&](const f32x4* a, const double (*B)[17], f64x4 (&acc)[4]) {  // 64 inner indices, four chains of instructions
+  auto product = [&](const f64x4* a, const double (*B)[17], f64x4 (&acc)[4]) {  // 64 inner indices, four chains of instructions
     double b[16];
 #pragma unroll
     for (int g = 0; g < 4; ++g)
@@ -113,21 +244,21 @@ __device__ __forceinline__ void inverse_panel(const InverseArgs& p, int b0, int 
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[g][e], b[4 * g + e], acc[g], 0, 0, 0);
+      for (int g = 0; g < 4; ++g) acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g][e], b[4 * g + e], acc[g], 0, 0, 0);
   };
-  at = 0;
 #pragma unroll
   for (int b = C - 1; b >= 0; --b) {
+    const int at = (C - 1 - b) & 1;
+    if (b > 0) fetch(b - 1, s[at ^ 1], t[at ^ 1]);
     f64x4 acc[4] = {};
 #pragma unroll
-    for (int j = C; j > b; --j) product(s + at + 4 * (C - j), X[j], acc);
-    at += 4 * (C - b);
+    for (int j = C; j > b; --j) product(s[at] + 4 * (C - j), X[j], acc);
 #pragma unroll
     for (int e = 0; e < 4; ++e) R[16 * wave + q + 4 * e][i] = (acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e]);
     __syncthreads();
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = f64x4{0., 0., 0., 0.};
-    product(t + (C - 1 - b) * 4, R, acc);
+    product(t[at], R, acc);
 #pragma unroll
     for (int e = 0; e < 4; ++e) X[b][16 * wave + q + 4 * e][i] = -((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e]));
     __syncthreads();
@@ -206,8 +337,8 @@ __global__ void __launch_bounds__(256) skew_kernel(SkewPair pair) {
 // Workspace
 // ------------------------------------------------------------------------------------------
 struct DenseLayout {
-  size_t Va, Vt;          // V as operands: rows stay rows; its transpose
-  size_t S, factor;       // the groups' Gram matrices, the factors of 64 rows
+  size_t Vt;              // V^T as operands
+  size_t S, factor;       // the groups' Gram matrices, the factors of 64 rows (fp64)
   size_t T;               // the groups' T as operands
   size_t TV;              // T_g V_g as operands
   size_t P;               // the product of the groups so far
@@ -236,10 +367,9 @@ static DenseLayout make_dense_layout(int d, int n, int m) {
     return o;
   };
   const size_t np = pad64(n);
-  L.Va = take(packed_bytes(n, d));
   L.Vt = take(packed_bytes(d, n));
-  L.S = take(np * kGroup * 4);
-  L.factor = take(np * 64 * 4);
+  L.S = take(np * kGroup * 8);
+  L.factor = take(np * 64 * 8);
   L.T = take(np * kGroup * 6);
   L.TV = take(packed_bytes(n, d));
   L.P = take((size_t)d * d * 4);
@@ -268,7 +398,7 @@ struct GemmList {
   GemmProblem& add() { return args.p[count++] = GemmProblem{}; }
 };
 
-template <int RT, int CT, int WM, int WN, int KS, int BF, bool EXACT>
+template <int RT, int CT, int WM, int WN, int KS, int BF>
 static int launch_gemm_as(GemmList& list, hipStream_t stream) {
   constexpr int BM = 16 * RT * WM, BN = 16 * CT * WN;
   int width = 0;
@@ -282,7 +412,7 @@ static int launch_gemm_as(GemmList& list, hipStream_t stream) {
     width = std::max(width, (p.tiles + 7) / 8 * 8);
   }
   constexpr size_t lds = gemm_lds<BM, BN, KS>();
-  auto kernel = gemm_kernel<RT, CT, WM, WN, KS, BF, EXACT>;
+  auto kernel = gemm_kernel<RT, CT, WM, WN, KS, BF>;
   const int rc = allow_lds(kernel, lds);
   if (rc != FASTH_OK) return rc;
   hipLaunchKernelGGL(kernel, dim3(width, list.count), dim3(64 * WM * WN * KS), lds, stream, list.args);
@@ -294,7 +424,7 @@ static int launch_gemm_as(GemmList& list, hipStream_t stream) {
 // Which tiles: the largest that give every compute unit a workgroup; a launch of short rounds of small tiles is over sooner than
 // one of few large ones. us, k = 1024, packed operands, {128 x 128, 64 x 64, 32 x 32}: 1024 x 4096: 54, 71, -; 1024 x 1024: 35, 18.7, 38;
 // 1024 x 256: -, 15.5, 7.9; 1024 x 100: -, -, 7.0; k = 512: 512 x 512: -, 10.3, 6.5.
-template <int BF, bool EXACT = false>
+template <int BF>
 static int launch_gemm_tiles(GemmList& list, int slot, hipStream_t stream, int min_tile, int max_tile) {
   long t128 = 0, t32 = 0;
   for (int i = 0; i < list.count; ++i) {
@@ -305,22 +435,17 @@ static int launch_gemm_tiles(GemmList& list, int slot, hipStream_t stream, int m
   }
   int tile = t128 >= 192 ? 128 : t32 > 512 ? 64 : 32;
   tile = std::min(std::max(tile, min_tile), max_tile);
-  static const std::string flags = ", " + std::to_string(BF) + (EXACT ? ", true>" : ", false>");
-  static const std::string names[3] = {"gemm_kernel<4, 4, 2, 2, 2" + flags, (EXACT ? "gemm_kernel<4, 2, 1, 2, 4" : "gemm_kernel<4, 4, 1, 1, 8") + flags,
-                                       "gemm_kernel<2, 2, 1, 1, 8" + flags};
+  static const std::string names[3] = {variant_name("gemm_kernel", {4, 4, 2, 2, 2, BF}), variant_name("gemm_kernel", {4, 4, 1, 1, 8, BF}),
+                                       variant_name("gemm_kernel", {2, 2, 1, 1, 8, BF})};
   prof::Scope ps_(slot, stream, names[tile == 128 ? 0 : tile == 64 ? 1 : 2].c_str());
-  if constexpr (EXACT) {  // (its second set of sums leaves no room for 64 x 64 outputs per wave)
-    if (tile >= 64) return launch_gemm_as<4, 2, 1, 2, 4, BF, EXACT>(list, stream);
-  } else {
-    if (tile == 128) return launch_gemm_as<4, 4, 2, 2, 2, BF, EXACT>(list, stream);
-    if (tile == 64) return launch_gemm_as<4, 4, 1, 1, 8, BF, EXACT>(list, stream);
-  }
-  return launch_gemm_as<2, 2, 1, 1, 8, BF, EXACT>(list, stream);
+  if (tile == 128) return launch_gemm_as<4, 4, 2, 2, 2, BF>(list, stream);
+  if (tile == 64) return launch_gemm_as<4, 4, 1, 1, 8, BF>(list, stream);
+  return launch_gemm_as<2, 2, 1, 1, 8, BF>(list, stream);
 }
 
 // BF: B is fp32 [k][cols]; where its rows are made of 16-byte groups a lane loads neighbouring columns at once. us per forward + backward, a load per
 // column and this: d = n = 1024, m = 4096: 334, 330; m = 1400: 259, 252; d = 512, m = 2048: 114, 113; d = 1536, m = 2048: 665, 658.
-template <bool BF, bool EXACT = false>
+template <bool BF>
 static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_tile = 32, int max_tile = 128) {
   if (list.count == 0) return FASTH_OK;
   if constexpr (BF) {
@@ -329,9 +454,9 @@ static int launch_gemm(GemmList& list, int slot, hipStream_t stream, int min_til
       const GemmProblem& p = list.args.p[i];
       wide = wide && p.cols % 4 == 0 && p.term.ldb % 4 == 0 && reinterpret_cast<uintptr_t>(p.term.B) % 16 == 0;
     }
-    if (wide) return launch_gemm_tiles<2, EXACT>(list, slot, stream, min_tile, max_tile);
+    if (wide) return launch_gemm_tiles<2>(list, slot, stream, min_tile, max_tile);
   }
-  return launch_gemm_tiles<BF ? 1 : 0, EXACT>(list, slot, stream, min_tile, max_tile);
+  return launch_gemm_tiles<BF ? 1 : 0>(list, slot, stream, min_tile, max_tile);
 }
 
 static int launch_pack(PackArgs& args, int count, int slot, hipStream_t stream) {
@@ -353,8 +478,9 @@ struct Dense {
   const Dense& factors() const { return owner ? *owner : *this; }
   char* at(size_t off) const { return ws + off; }
   float* f(size_t off) const { return reinterpret_cast<float*>(ws + off); }
+  double* f64(size_t off) const { return reinterpret_cast<double*>(ws + off); }
   int kt(int x) const { return pad64(x) / 32; }
-  PackJob pack_v(const float* V) const { return PackJob{V, at(L.Va), at(L.Vt), n, d, pad64(n) / 64 * (pad64(d) / 64)}; }
+  PackJob pack_v(const float* V) const { return PackJob{V, nullptr, at(L.Vt), n, d, pad64(n) / 64 * (pad64(d) / 64)}; }
   // X of a product H X, or G of a product H^T X ([rows][m], rows beyond are zero), for dV
   PackJob pack_right(const float* X, int rows) const { return PackJob{X, at(L.right), nullptr, rows, m, pad64(d) / 64 * (pad64(m) / 64)}; }
   char* left() const { return at(L.left); }
@@ -377,30 +503,32 @@ static int dense_pack(const PackJob& job, int slot, hipStream_t stream) {
 static int dense_factors(const Dense* const* D, const float* const* V, int count, const PackJob* jobs, int njobs, hipStream_t stream) {
   const int slot = FASTH_KERNEL_FACTOR;
   PackArgs pk{};
-  for (int i = 0; i < count; ++i) pk.job[i] = D[i]->pack_v(V[i]);
-  for (int i = 0; i < njobs; ++i) pk.job[count + i] = jobs[i];
-  int rc = launch_pack(pk, count + njobs, slot, stream);
-  if (rc != FASTH_OK) return rc;
+  int pack = 0;  // blocks of the largest job
+  for (int i = 0; i < count + njobs; ++i) {
+    pk.job[i] = i < count ? D[i]->pack_v(V[i]) : jobs[i - count];
+    pack = std::max(pack, pk.job[i].blocks);
+  }
   InversePair inv{};
   FactorPair64 fac{};
+  GramPair gram{};
   int width = 0;
-  GemmList gram;
+  bool vec4 = true;
   for (int i = 0; i < count; ++i) {
     const Dense& P = *D[i];
     const int groups = (P.n + kGroup - 1) / kGroup;
-    fac.a[i] = FactorArgs64{P.f(P.L.S), P.f(P.L.factor), P.n, pad64(P.n)};
-    inv.a[i] = InverseArgs{P.f(P.L.S), P.f(P.L.factor), P.at(P.L.T), pad64(P.n)};
+    gram.a[i] = GramArgs{V[i], P.f64(P.L.S), P.n, P.d, groups * kGroupTiles};
+    fac.a[i] = FactorArgs64{P.f64(P.L.S), P.f64(P.L.factor), P.n, pad64(P.n)};
+    inv.a[i] = InverseArgs{P.f64(P.L.S), P.f64(P.L.factor), P.at(P.L.T), pad64(P.n)};
     width = std::max(width, groups);
-    for (int g = 0; g < groups; ++g) {
-      if (gram.count == kGemmProblems && (rc = launch_gemm<false, true>(gram, slot, stream)) != FASTH_OK) return rc;
-      GemmProblem& p = gram.add();
-      char* rows = operand_cell(P.at(P.L.Va), P.kt(P.d), g * kGroup, 0);
-      p.term = GemmTerm{rows, rows, P.kt(P.d), P.kt(P.d), P.d, false};
-      p.rows = p.cols = pad64(group_rows(P, g)); p.ldo = kGroup; p.flags = kUpper; p.alpha = 1.f;
-      p.out = P.f(P.L.S) + (size_t)g * kGroup * kGroup;
-    }
+    vec4 = vec4 && P.d % 4 == 0;
   }
-  if ((rc = launch_gemm<false, true>(gram, slot, stream)) != FASTH_OK) return rc;
+  gram.width = width * kGroupTiles;
+  {
+    static_assert(kGroupTiles % 8 == 0, "every XCD takes as many tiles");
+    prof::Scope ps_(slot, stream, vec4 ? "gram_kernel<4>" : "gram_kernel<1>");
+    hipLaunchKernelGGL(vec4 ? gram_kernel<4> : gram_kernel<1>, dim3(gram.width + pack, count + njobs), dim3(256), 0, stream, gram, pk);
+    FASTH_HIP(hipGetLastError());
+  }
   {
     prof::Scope ps_(slot, stream, "block_factor_kernel");
     hipLaunchKernelGGL(block_factor_kernel, dim3(width * (kGroup / 64), count), dim3(512), 0, stream, fac);

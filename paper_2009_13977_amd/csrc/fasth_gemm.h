@@ -14,7 +14,10 @@ namespace fasth {
 // Operands. A matrix whose rows are an operand's rows (of A) or columns (of B) and whose columns are the inner index k is stored as tiles of 16 rows
 // x 32 k: three pieces of 1 KiB, slot 16 kq + row of a piece holding k = 8 kq .. 8 kq + 7 of that row, which is what lane 16 kq + row of
 // v_mfma_f32_16x16x32_bf16 reads. Tiles of a row of tiles follow one another; rows and k are padded with zeros to multiples of 64,
-// so that no product has an edge. 6 bytes per element.
+// so that no product has an edge. 6 bytes per element. The odd tiles of k are stored with the opposite sign: where an addend is much smaller than
+// another, v_mfma_f32_16x16x32_bf16 cuts it off downwards, whatever its sign (mean error -6e-9 of the sum's size per instruction, rms 3.7e-8, with an
+// accumulator 2^-8 of the products). Added over all tiles of k that leaves errors of one direction, which a product with rows of one sign adds up; so half of
+// a sum is formed as -(-a) b. Where both operands are stored this way the signs cancel.
 // ------------------------------------------------------------------------------------------
 constexpr int kTileBytes = 3 * 1024;
 static __host__ __device__ __forceinline__ int pad64(int x) { return (x + 63) & ~63; }
@@ -22,7 +25,11 @@ static __host__ __device__ __forceinline__ size_t packed_bytes(int rows, int k) 
 
 // Eight consecutive k of a row: slot kq of (row, k / 32).
 __device__ __forceinline__ void store_unit(char* pack, int kt, int row, int k8, const float (&v)[8]) {
-  const Trio t = split8(v);
+  const unsigned sign = (unsigned)(k8 & 4) << 29;
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(__float_as_uint(v[e]) ^ sign);
+  const Trio t = split8(x);
   u32x4* dst = reinterpret_cast<u32x4*>(pack + ((size_t)(row >> 4) * kt + (k8 >> 2)) * kTileBytes) + (k8 & 3) * 16 + (row & 15);
 #pragma unroll
   for (int pc = 0; pc < 3; ++pc) dst[pc * 64] = __builtin_bit_cast(u32x4, t.p[pc]);
@@ -41,13 +48,10 @@ struct PackArgs {
   PackJob job[kPackJobs];  // blockIdx.y
 };
 
-// One 64 x 64 block per workgroup, through LDS: reads 4 bytes per element and writes 6 per kind, and is bound by that: V of 1024 x 1024
-// both ways and X of 1024 x 4096 along its rows, 60 MB, take 10 us (6.0 TB/s).
-__global__ void __launch_bounds__(256) pack_kernel(PackArgs args) {
-  __shared__ float tile[64][65];
-  const PackJob& p = args.job[blockIdx.y];
-  if ((int)blockIdx.x >= p.blocks) return;
-  const int bc = pad64(p.cols) / 64, r0 = (int)blockIdx.x / bc * 64, c0 = (int)blockIdx.x % bc * 64;
+// One 64 x 64 block per workgroup of 256 threads, through LDS: reads 4 bytes per element and writes 6 per kind.
+typedef float PackTile[64][65];
+__device__ __forceinline__ void pack_block(const PackJob& p, int block, PackTile& tile) {
+  const int bc = pad64(p.cols) / 64, r0 = block / bc * 64, c0 = block % bc * 64;
   const int tid = threadIdx.x, c = tid & 63;
   const BufferDesc desc = make_buffer(p.src + (size_t)r0 * p.cols, (size_t)max(0, min(64, p.rows - r0)) * p.cols * sizeof(float));
   float x[16];
@@ -72,6 +76,12 @@ __global__ void __launch_bounds__(256) pack_kernel(PackArgs args) {
       store_unit(p.across, p.blocks / bc * 2, c0 + row, r0 / 8 + k8, v);
     }
   }
+}
+
+__global__ void __launch_bounds__(256) pack_kernel(PackArgs args) {
+  __shared__ PackTile tile;
+  const PackJob& p = args.job[blockIdx.y];
+  if ((int)blockIdx.x < p.blocks) pack_block(p, (int)blockIdx.x, tile);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -233,7 +243,7 @@ __device__ __forceinline__ void gemm_range(const GemmTerm& g, int r0, int split,
 // same addresses 57, so neither memory nor the L2s; some 8 are launch, first fetch and the way out. 1024 x 1024 x 1024: 17 us; 1024 x 256 x 1024: 7.2;
 // the smallest: 4.9, launch and code fetch. The same products with both operands staged in LDS took 57 us at 1024 x 4096 x 1024 (packed) and 67 us
 // (split on the way); a barrier per tile of k, for waves that share an operand to fetch it together: 63.
-template <int RT, int CT, int WM, int WN, int KS, int BF, bool EXACT>
+template <int RT, int CT, int WM, int WN, int KS, int BF>
 __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) {
   constexpr int BM = 16 * RT * WM, BN = 16 * CT * WN, LD = BN + 4;
   extern __shared__ __align__(16) float tile[];
@@ -245,15 +255,12 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
   if (!gemm_tile<BM, BN>(p, r0, c0, part)) return;
 
   // A tile of k is summed by itself, the small products first and the leading one last, and added to what is there: one rounding of full size
-  // per 32 terms, and another in the sum. EXACT: what the sum rounds away is kept.
-  f32x4 sum[RT][CT], rest[EXACT ? RT : 1][EXACT ? CT : 1];
+  // per 32 terms, and another in the sum.
+  f32x4 sum[RT][CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      sum[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (EXACT) rest[r][c] = sum[r][c];
-    }
+    for (int c = 0; c < CT; ++c) sum[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   const unsigned lane_off = (unsigned)lane * 16u;
   auto multiply_row = [&](int r, const Trio& a, const Trio (&b)[CT]) {
     f32x4 part[CT];
@@ -265,18 +272,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
         part[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[kLeft[u]], b[c].p[kRight[u]], u == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[c], 0, 0, 0);
     }
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      if constexpr (EXACT) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = sum[r][c][e], y = part[c][e], both = x + y, from_y = both - x;
-          rest[r][c][e] += (x - (both - from_y)) + (y - from_y);
-          sum[r][c][e] = both;
-        }
-      } else {
-        sum[r][c] += part[c];
-      }
-    }
+    for (int c = 0; c < CT; ++c) sum[r][c] += part[c];
     __builtin_amdgcn_sched_barrier(0);  // (else the sums of all rows wait for the last product, in registers that are not there)
   };
   // the wave's first tiles (panels that lie beyond the last are the last one: what they give is not stored)
@@ -356,11 +352,14 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
       }
     }
   }
-  if constexpr (EXACT) {
+  if constexpr (BF) {  // A's odd tiles of k have the other sign; a wave's are all odd or all even
+    static_assert(KS % 2 == 0, "groups of waves take every KS-th tile of k");
+    if ((beg + ks) & 1) {
 #pragma unroll
-    for (int r = 0; r < RT; ++r)
+      for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int c = 0; c < CT; ++c) sum[r][c] += rest[r][c];
+        for (int c = 0; c < CT; ++c) sum[r][c] = -sum[r][c];
+    }
   }
   // The groups' sums meet in LDS, 16 bytes per lane and tile, and all threads add them (in fp64: KS - 1 roundings of full size less); then the tile goes into rows.
   constexpr int NT = 64 * WM * WN * KS, UNITS = BM * BN / 4, PER = (UNITS + NT - 1) / NT;
@@ -371,39 +370,32 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) gemm_kernel(GemmArgs args) 
 #pragma unroll
     for (int j = 0; j < 4; ++j) tile[(row + j) * LD + col] = v[j];
   };
-  if constexpr (KS > 1) {
 #pragma unroll
-    for (int r = 0; r < RT; ++r)
+  for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int c = 0; c < CT; ++c) parts[ks * UNITS + ((wm * RT + r) * (BN / 16) + wn * CT + c) * 64 + lane] = sum[r][c];
-    __syncthreads();
-    f32x4 v[PER];
+    for (int c = 0; c < CT; ++c) parts[ks * UNITS + ((wm * RT + r) * (BN / 16) + wn * CT + c) * 64 + lane] = sum[r][c];
+  __syncthreads();
+  f32x4 v[PER];
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int unit = tid + it * NT;
-      if (UNITS % NT == 0 || unit < UNITS) {
-        double x[4] = {0., 0., 0., 0.};
+  for (int it = 0; it < PER; ++it) {
+    const int unit = tid + it * NT;
+    if (UNITS % NT == 0 || unit < UNITS) {
+      double x[4] = {0., 0., 0., 0.};
 #pragma unroll
-        for (int g = 0; g < KS; ++g) {
-          const f32x4 part = parts[g * UNITS + unit];
+      for (int g = 0; g < KS; ++g) {
+        const f32x4 part = parts[g * UNITS + unit];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) x[j] += (double)part[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[it][j] = (float)x[j];
+        for (int j = 0; j < 4; ++j) x[j] += (double)part[j];
       }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[it][j] = (float)x[j];
     }
-    __syncthreads();
+  }
+  __syncthreads();
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int unit = tid + it * NT;
-      if (UNITS % NT == 0 || unit < UNITS) to_rows(unit, v[it]);
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-      for (int c = 0; c < CT; ++c) to_rows(((wm * RT + r) * (BN / 16) + wn * CT + c) * 64 + lane, sum[r][c]);
+  for (int it = 0; it < PER; ++it) {
+    const int unit = tid + it * NT;
+    if (UNITS % NT == 0 || unit < UNITS) to_rows(unit, v[it]);
   }
   __syncthreads();
   gemm_epilogue<BM, BN, 64 * WM * WN * KS>(p, tile, r0, c0, part);

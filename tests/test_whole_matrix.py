@@ -40,6 +40,89 @@ def test_gradient_steps(d, n, m, k, transpose):
         assert np.linalg.norm(g - r) <= 1e-6 * np.linalg.norm(r), name
 
 
+def _far_from_orthogonal(kind, d, n):
+    r = np.random.default_rng(d + n)
+    V = r.standard_normal((n, d))
+    return {"positive": lambda: np.abs(V), "one direction": lambda: r.standard_normal((1, d)) + 0.3 * V,
+            "rank 4": lambda: r.standard_normal((n, 4)) @ r.standard_normal((4, d)) + 1e-2 * V,
+            "rank 32": lambda: r.standard_normal((n, 32)) @ r.standard_normal((32, d)) + 0.1 * V}[kind]().astype(np.float32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n,m,transpose,kind", [(512, 512, 800, False, "positive"), (512, 512, 800, True, "one direction"), (512, 512, 800, False, "rank 4"),
+                                                  (512, 461, 700, True, "rank 32"), (1024, 973, 1004, False, "positive")])
+def test_rows_far_from_orthogonal(d, n, m, transpose, kind):
+    """T grows with the angles between the rows that share it: the larger groups must not be less exact than the chain of blocks, which serves the
+    two halves of the columns."""
+    print(f"matrix rows far from orthogonal d={d} n={n} m={m} transpose={transpose} {kind}", flush=True)
+    V = _far_from_orthogonal(kind, d, n)
+    p = synthetic.householder_problem(d, n, m, seed=109000)
+    X, G = p["X"], p["G"]
+    ref = orc.product_gradients(V, X, G, transpose=transpose)
+    got = gpu_fasth(V, X, G, 1, transpose)
+    halves = [gpu_fasth(V, np.ascontiguousarray(X[:, s]), np.ascontiguousarray(G[:, s]), 1, transpose) for s in (slice(0, m // 2), slice(m // 2, m))]
+    chain = (np.concatenate([h[0] for h in halves], 1), halves[0][1].astype(np.float64) + halves[1][1], np.concatenate([h[2] for h in halves], 1))
+    for name, g, c, r in zip(("A", "dV", "dX"), got, chain, ref):
+        ours, theirs = (np.linalg.norm(x - r) / np.linalg.norm(r) for x in (g, c))
+        print(f"  {name} {ours:.2e} chain {theirs:.2e}", flush=True)
+        assert ours <= theirs, (name, ours, theirs)
+
+
+@pytest.mark.gpu
+def test_sums_of_one_term():
+    """Rows with a single non-zero v: H turns the sign of n entries, through T = 2 / v^2, y = T v, h = 1 - v y and one product h x. Relative to x: the roundings
+    of T and y and the left-out parts of T v and v y count twice, those of h and h x once: largest 2^-24 (2 * 4 + 2) = 6.0e-7.
+    Entries that no row reaches stay as they are, also those beyond the largest bf16 number."""
+    d, n, m = 512, 476, 704
+    rng = np.random.default_rng(110000)
+    V = np.zeros((n, d), np.float32)
+    V[np.arange(n), rng.permutation(d)[:n]] = (1 + rng.random(n)) * rng.choice([-1.0, 1.0], n)
+    X = rng.standard_normal((d, m)).astype(np.float32)
+    turned = V.any(axis=0)
+    X[~turned, 5] = np.float32(3.4e38)
+    X[~turned, 6] = -np.finfo(np.float32).max
+    A, _, dX = gpu_fasth(V, X, X, 4, False)
+    for got in (A, dX):
+        err = np.abs(got[turned] + X[turned]) / np.abs(X[turned])
+        print(f"  largest {err.max():.2e} rms {np.sqrt((err.astype(np.float64) ** 2).mean()):.2e}", flush=True)
+        assert err.max() <= 6.0e-7
+        assert np.array_equal(got[~turned], X[~turned])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transpose", [False, True])
+def test_rows_and_columns_of_any_magnitude(transpose):
+    """Rows of V over twelve decades, columns of X over fifty and those of G the other way round: every column of A and dX and every row of dV is as exact,
+    against its own norm, as the others. 1e-6: as for normal inputs above."""
+    d, n, m = 480, 470, 700
+    rng = np.random.default_rng(111000)
+    p = synthetic.householder_problem(d, n, m, seed=111000)
+    scale = 10.0 ** rng.permutation(np.linspace(-25, 25, m))
+    V = (p["V"] * 10.0 ** rng.uniform(-6, 6, (n, 1))).astype(np.float32)
+    X, G = (p["X"] * scale).astype(np.float32), (p["G"] / scale).astype(np.float32)
+    got = gpu_fasth(V, X, G, 10, transpose)
+    for name, g, r, axis in zip(("A", "dV", "dX"), got, orc.product_gradients(V, X, G, transpose=transpose), (0, 1, 0)):
+        size = np.abs(r).max(axis=axis, keepdims=True)
+        err = np.linalg.norm((g - r) / size, axis=axis) / np.linalg.norm(r / size, axis=axis)
+        print(f"  {name} largest {err.max():.2e}", flush=True)
+        assert err.max() <= 1e-6, (name, err.max())
+
+
+@pytest.mark.gpu
+def test_columns_near_the_ends_of_the_range():
+    """The largest and smallest columns that the products leave finite and normal, as on the kernels for few reflections: lower pieces below 2^-126 keep their
+    place, results do not (1e-35 is 2^10 above the smallest normal number)."""
+    d, n, m = 480, 470, 700
+    p = synthetic.householder_problem(d, n, m, seed=112000)
+    scale = 10.0 ** np.linspace(-35, 35, m)
+    X = (p["X"] * scale).astype(np.float32)
+    A, _, _ = gpu_fasth(p["V"], X, p["G"], 10, False)
+    A0 = orc.product_apply(p["V"], X)
+    err = np.linalg.norm((A - A0) / scale, axis=0) / np.linalg.norm(A0 / scale, axis=0)
+    print(f"  largest {err.max():.2e}", flush=True)
+    assert err.max() <= 1e-4, (err.argmax(), err.max())
+
+
 @pytest.mark.gpu
 def test_layers():
     d, n, m = 470, 450, 768
