@@ -385,7 +385,7 @@ struct SvdLayout {
 
 static SvdLayout make_svd_layout(int d, int n, int m, int k) {
   SvdLayout S;
-  S.dense = dense_serves(d, n, m);
+  S.dense = dense_serves_layer(d, n, m);
   const size_t one = workspace_of(d, n, m, k, S.dense);
   const size_t dm = align_up((size_t)d * m * sizeof(float), 256);
   S.off_U = 0;
@@ -521,7 +521,7 @@ static int check_rect_shape(const fasth_rect_shape* s, fasth_shape* u, fasth_sha
 
 static RectLayout make_rect_layout(const fasth_shape& u, const fasth_shape& v) {
   RectLayout S;
-  S.dense = dense_serves(u.d, u.n, u.m) && dense_serves(v.d, v.n, v.m);
+  S.dense = dense_serves_layer(u.d, u.n, u.m) && dense_serves_layer(v.d, v.n, v.m);
   S.off_U = 0;
   S.off_V = align_up(workspace_of(u.d, u.n, u.m, u.k, S.dense), 256);
   S.off_Z1 = S.off_V + align_up(workspace_of(v.d, v.n, v.m, v.k, S.dense), 256);

@@ -662,27 +662,43 @@ static int dense_dv(const Dense* const* D, const float* const* V, float* const* 
 static bool dense_fits(int d, int n, int m) {
   return d <= 4096 && 2 * n <= 3 * d && (size_t)d * m * sizeof(float) < 0x80000000u;
 }
-// Whether gradient steps (and what is prepared) run on the whole matrix: the m-dependent part of a step is 6 d^2 m operations instead of
-// 12 d n m, the rest is as much as a mini-batch of some 1.2 d columns. Where the lines lie depends on the chain that would run: teams of workgroups
-// serve up to 1280 columns (d <= 640, and 768), 1024 (d > 768) or 2048 (d <= 512), and are slower per column beyond. us per forward + backward, chain of blocks and
-// this, n / d in brackets:
-// d = 448: m = 640: 97, 99 (1); m = 1300: 107, 110 (0.7); m = 4096: 135, 147 (0.7). d = 464: m = 640: 106, 101 (1); 100, 101 (0.9); m = 1024: 112, 103 (0.7).
-// d = 512: m = 512: 85, 96 (1); m = 640: 113, 100 (1); 108, 100 (0.9); 98, 100 (0.8); m = 1024: 129, 104 (0.9); 110, 103 (0.7); m = 1500: 123, 110 (0.7).
-// d = 544: m = 704: 131, 126 (1); 121, 114 (0.85); 101, 106 (0.7); m = 1280: 119, 121 (0.7); m = 1500: 141, 123 (0.6). d = 640: m = 704: 139, 131 (1);
-// m = 768: 135, 137 (0.85); m = 1500: 143, 130 (0.6). d = 704: m = 768: 151, 152 (1); m = 1500: 167, 167 (0.7); m = 2200: 210, 174 (0.7); 195, 171 (0.6).
-// d = 768: m = 1280: 174, 186 (1); m = 2300: 287, 222 (1); 233, 203 (0.75). d = 864: m = 1024: 206, 202 (1); m = 1100: 241, 209 (1); 229, 207 (0.9).
-// d = 928: m = 1100: 243, 245 (0.9); 231, 243 (0.85). d = 960: m = 960: 231, 219 (1); 226, 218 (0.95); 207, 215 (0.9). d = 1001: m = 1100: 256, 263 (0.95).
-// d = 1024: m = 960: 227, 226 (1); m = 1024: 234, 226 (1); 226, 225 (0.9); m = 1280: 281, 256 (1); 264, 252 (0.9); 251, 247 (0.85); m = 4096: 552, 333 (1);
-// 425, 303 (0.75). d = 1152: m = 1280: 355, 384 (1). d = 1280: m = 1280: 390, 417 (1); m = 1500: 503, 429 (1). d = 1536: m = 1280: 536, 620 (1); m = 1500: 689, 665 (1); 493, 551
-// (0.75). d = 2048: m = 1024: 760, 906 (1); shorter vectors: d = 384: m = 1300: 112, 103 (1); m = 3000: 135, 148 (1).
-static bool dense_serves(int d, int n, int m) {
-  if (!dense_fits(d, n, m)) return false;
-  const auto at_least = [&](int twentieths) { return 20ll * n >= (long long)twentieths * d; };  // n / d
-  if (d <= 512) return d >= 448 && ((at_least(18) && m >= (d >= 464 ? 640 : 768)) || (d >= 464 && at_least(14) && m >= 1024 && m <= 2560));
-  if (d <= 640 && m >= 704 && at_least(d <= 560 ? 17 : 19)) return true;
-  if (d <= 704 && at_least(12) && m >= (d <= 640 ? 1281 : 2048)) return true;
-  if (d >= 864 && d <= 1024 && d % 4 == 0 && (m > 1024 ? at_least(18) : d >= 960 && m >= 1000 && at_least(19))) return true;
-  return m > 1280 && (double)m * n * n >= 1.25 * std::max(d, 1024) * d * d;
+// Whether a product runs on the whole matrix. Its part of a gradient step that depends on m is 6 d^2 m operations instead of 12 d n m, the rest is as much as a
+// mini-batch of some 1.2 d columns and falls on whoever forms H: fasth_forward and fasth_prepare, also where no gradients or few applies follow. The
+// lines lie where a gradient step gains at least as many us as a forward call by itself loses, and fasth_prepare with two applies is no slower (n / d of 0.5 to
+// 0.6: four to eight applies). They depend on the chain that would run: teams of workgroups serve up to 1280 columns (d <= 640, and 768), 1024 (d > 768) or
+// 2048 (d <= 512), and as parts of a tile some 2200 from d = 1025 on; beyond d = 2048 no kernel shares columns. Lengths that are no multiple of four load an operand one column at
+// a time (launch_gemm). us, chain of blocks and whole matrix; gradient step; forward alone; prepare and two applies:
+//   d = n =  512, m =   768: 117, 103;  47,  62;  84,  72     m = 1024: 128, 105;  56,  64;  87,  72
+//   n = 0.75 d,   m =  2048: 132, 115;  56,  65;  80,  78     m = 4096: 152, 146;  60,  78;  86, 100     m = 16384: 422, 268; 154, 125; 196, 188
+//   d = n =  640, m =  1280: 153, 151;  66,  86; 216, 101     m = 1500: 190, 156;  87,  87; 170, 103
+//   n = 0.75 d,   m =  2048: 174, 165;  76,  84; 140, 108     m = 3000: 220, 176;  95,  86; 146, 111
+//   n = 0.5 d,    m =  4096: 183, 197;  75,  96; 112, 128     m = 8192: 318, 283; 113, 129; 175, 195
+//   d = n =  768, m =  2048: 238, 220; 101, 114; 204, 141     m = 3000: 316, 263; 129, 129; 210, 171
+//   n = 0.75 d,   m =  3000: 255, 244; 104, 125; 170, 167     m = 4096: 291, 247; 117, 128; 179, 167
+//   d = n =  833, m =  1900: 267, 273; 115, 160; 237, 189     m = 3000: 384, 314; 149, 178; 242, 217
+//   d = n = 1024, m =  1500: 290, 266; 125, 151; 277, 183     m = 2048: 329, 285; 134, 156; 274, 189     m = 3000: 467, 319; 174, 172; 283, 220
+//   n = 0.75 d,   m =  2048: 257, 253; 108, 130; 212, 164     m = 3000: 351, 287; 137, 147; 222, 196
+//   n = 0.5 d,    m =  4096: 304, 266; 118, 126; 177, 182     m = 8192: 576, 422; 207, 182; 256, 291
+//   n = 0.3 d,    m = 16384: 776, 730; 281, 293; 355, 508     m = 65535: 3060, 2899; 1204, 1055; 1508, 1876
+//   d = n = 1408, m =  1900: 673, 564; 243, 326; 693, 393     m = 2250: 744, 585; 259, 336; 701, 404
+//   d = n = 2048, m =  1500: 1086, 997; 429, 561; 1224, 641   m = 2048: 1266, 1027; 529, 565; 1233, 658
+//   n = 0.5 d,    m =  4096: 1094, 956; 427, 434; 688, 629    m = 8192: 2083, 1493; 773, 632; 1307, 998
+//   d = n = 2052, m =  1280: 2654, 1408; 1219, 813; 2284, 895;  d = 2560, n = 1280: 1702, 966; 784, 551; 1495, 643;  d = 4096, n = 2048: 3616, 2842; 1631, 1626; 3096, 1896
+static bool dense_pays(int d, int n, long long columns) {
+  if (d < 448 || 2 * n < d) return false;
+  n = std::min(n, d);  // (more reflections cost both sides more)
+  if (d % 4) columns = columns * 4 / 5;
+  const auto at_least = [&](int per_n, int per_d, long long full) { return columns * ((long long)per_n * n - (long long)per_d * d) >= full * d; };
+  if (d <= 512) return (columns >= 1024 && 8 * n >= 7 * d) || at_least(5, 2, 16384);
+  if (d <= 640) return at_least(5, 2, 3 * 1281);
+  if (d <= 768) return at_least(4, 1, 3 * 2500);
+  return d <= 2048 ? at_least(1, 0, 2250) : columns >= 1280;
 }
+static bool dense_serves(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, m); }
+// A product of a layer of two: its launches serve both, so the lines lie at 0.6 of the columns. us per layer, W X, gradient step and forward alone:
+// d = n = 512, m = 512: 146, 142; 69, 78; m = 640: 194, 154; 88, 82. d = n = 640, m = 768: 253, 228; 115, 122. d = n = 768, m = 1280: 350, 326; 133, 172; m = 1500: 441, 380;
+// 180, 197. d = n = 1024, m = 1024: 486, 437; 190, 238; m = 1280: 596, 502; 239, 262; m = 1500: 636, 520; 238, 267; n = 0.75 d, m = 1800: 537, 465; 196, 231.
+// d = n = 2048, m = 1100: 2072, 1822; 927, 998. d = n = 4096, m = 768: 12247, 9692; 5872, 5537. Symmetric forms, one set of factors: d = n = 1024, m = 1280: 581, 436; 233, 193.
+static bool dense_serves_layer(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, 5ll * m / 3); }
 
 }  // namespace fasth

@@ -9,23 +9,28 @@ from paper_2009_13977_amd import synthetic
 
 # groups of 256 rows with a last one of 148, 194, 256, 1, 88, 65, 88, 69, 220, 144 and 167 rows; vectors of whole tiles of 64, one more, four less; columns likewise;
 # rows of whole 16-byte groups and not, in V and in X; the seventh has enough columns for the largest tiles of a product
-SHAPES = [(448, 404, 768, 4), (500, 450, 769, 50), (512, 768, 770, 64), (513, 513, 1281, 1), (577, 600, 1344, 24), (640, 577, 1601, 1), (640, 600, 4993, 24),
-          (464, 325, 1024, 25), (560, 476, 704, 28), (960, 912, 1000, 24), (704, 423, 2048, 47)]
+SHAPES = [(448, 404, 1024, 4), (500, 450, 1025, 50), (512, 768, 1026, 64), (513, 513, 1602, 1), (577, 600, 1604, 24), (640, 577, 1601, 1), (640, 600, 4993, 24),
+          (464, 325, 11268, 25), (560, 476, 1920, 28), (960, 912, 2372, 24), (704, 423, 5360, 47)]
 
 
 def test_the_rule_by_the_workspace():
     """No saved inputs per block: the workspace on the two sides of the rule's lines, whatever the block size."""
     from paper_2009_13977_amd import binding as B
     size = B.fasth_workspace_bytes
-    for (d, n, m), (d2, n2, m2) in (((1024, 1024, 1000), (1024, 1024, 999)), ((1000, 900, 1025), (1000, 900, 1024)), ((1024, 1024, 1025), (1025, 1025, 1025)),
-                                    ((512, 512, 640), (512, 512, 639)), ((448, 448, 900), (444, 444, 900)), ((464, 325, 1024), (464, 325, 1023)),
-                                    ((512, 461, 3000), (512, 460, 3000)), ((560, 476, 704), (560, 475, 704)), ((640, 608, 704), (640, 607, 704)),
-                                    ((640, 384, 1281), (640, 384, 1280)), ((704, 423, 2048), (704, 423, 2047)), ((1024, 768, 2276), (1024, 768, 2275)),
+    for (d, n, m), (d2, n2, m2) in (((1024, 1024, 2250), (1024, 1024, 2249)), ((1024, 1228, 2250), (1024, 1228, 2249)), ((1023, 1023, 2813), (1023, 1023, 2812)),
+                                    ((512, 512, 1024), (512, 512, 1023)), ((512, 448, 1024), (512, 447, 1024)), ((448, 448, 1500), (444, 444, 1500)),
+                                    ((512, 256, 32768), (512, 256, 32767)), ((640, 640, 1281), (640, 640, 1280)), ((640, 480, 2196), (640, 480, 2195)),
+                                    ((768, 768, 2500), (768, 768, 2499)), ((772, 772, 2250), (772, 772, 2249)), ((2048, 1024, 4500), (2048, 1023, 4500)),
+                                    ((2052, 1026, 1280), (2052, 1026, 1279)), ((4096, 4096, 1280), (4096, 4096, 1279)), ((1024, 512, 65535), (1024, 511, 65535)),
                                     ((600, 900, 1300), (600, 904, 1300))):
         for k in (1, 2, 4):
             if n % k == 0 and n2 % k == 0:
                 assert size(d, n, m, k) == size(d, n, m, 1)
         assert size(d, n, m, 1) < 0.75 * size(d2, n2, m2, 1)
+    for d, n, m in ((1024, 1024, 1350), (512, 448, 615), (640, 640, 769), (3072, 3072, 768)):  # layers: 0.6 of the columns
+        assert B.svd_layer_workspace_bytes(d, n, m, 1) < 0.75 * B.svd_layer_workspace_bytes(d, n, m - 1, 1)
+    rect = lambda n_v, m: B.svd_rect_workspace_bytes(1024, 512, 1024, n_v, m, 1)
+    assert rect(448, 1350) < 0.75 * min(rect(448, 1349), rect(447, 1350))
 
 
 @pytest.mark.gpu
@@ -49,8 +54,8 @@ def _far_from_orthogonal(kind, d, n):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,n,m,transpose,kind", [(512, 512, 800, False, "positive"), (512, 512, 800, True, "one direction"), (512, 512, 800, False, "rank 4"),
-                                                  (512, 461, 700, True, "rank 32"), (1024, 973, 1004, False, "positive")])
+@pytest.mark.parametrize("d,n,m,transpose,kind", [(512, 512, 1028, False, "positive"), (512, 512, 1028, True, "one direction"), (512, 512, 1028, False, "rank 4"),
+                                                  (512, 461, 1028, True, "rank 32"), (832, 832, 2256, False, "positive")])
 def test_rows_far_from_orthogonal(d, n, m, transpose, kind):
     """T grows with the angles between the rows that share it: the larger groups must not be less exact than the chain of blocks, which serves the
     two halves of the columns."""
@@ -73,7 +78,7 @@ def test_sums_of_one_term():
     """Rows with a single non-zero v: H turns the sign of n entries, through T = 2 / v^2, y = T v, h = 1 - v y and one product h x. Relative to x: the roundings
     of T and y and the left-out parts of T v and v y count twice, those of h and h x once: largest 2^-24 (2 * 4 + 2) = 6.0e-7.
     Entries that no row reaches stay as they are, also those beyond the largest bf16 number."""
-    d, n, m = 512, 476, 704
+    d, n, m = 512, 476, 1028
     rng = np.random.default_rng(110000)
     V = np.zeros((n, d), np.float32)
     V[np.arange(n), rng.permutation(d)[:n]] = (1 + rng.random(n)) * rng.choice([-1.0, 1.0], n)
@@ -94,7 +99,7 @@ def test_sums_of_one_term():
 def test_rows_and_columns_of_any_magnitude(transpose):
     """Rows of V over twelve decades, columns of X over fifty and those of G the other way round: every column of A and dX and every row of dV is as exact,
     against its own norm, as the others. 1e-6: as for normal inputs above."""
-    d, n, m = 480, 470, 700
+    d, n, m = 480, 470, 1028
     rng = np.random.default_rng(111000)
     p = synthetic.householder_problem(d, n, m, seed=111000)
     scale = 10.0 ** rng.permutation(np.linspace(-25, 25, m))
@@ -112,7 +117,7 @@ def test_rows_and_columns_of_any_magnitude(transpose):
 def test_columns_near_the_ends_of_the_range():
     """The largest and smallest columns that the products leave finite and normal, as on the kernels for few reflections: lower pieces below 2^-126 keep their
     place, results do not (1e-35 is 2^10 above the smallest normal number)."""
-    d, n, m = 480, 470, 700
+    d, n, m = 480, 470, 1028
     p = synthetic.householder_problem(d, n, m, seed=112000)
     scale = 10.0 ** np.linspace(-35, 35, m)
     X = (p["X"] * scale).astype(np.float32)
@@ -155,7 +160,7 @@ def test_prepared_products():
     each followed by its gradients; the matrix is still the one prepared afterwards."""
     import torch
     from paper_2009_13977_amd import binding as B
-    d, n, m, k = 500, 520, 800, 20
+    d, n, m, k = 500, 520, 1028, 20
     print(f"matrix prepared d={d} n={n} m={m}", flush=True)
     p = synthetic.householder_problem(d, n, m, seed=104000)
     V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
@@ -194,7 +199,7 @@ def test_saved_applies_after_a_forward_call(first, transpose):
     other call has seen."""
     import torch
     from paper_2009_13977_amd import binding as B
-    d, n, m, k = 500, 520, 800, 20
+    d, n, m, k = 500, 520, 1028, 20
     print(f"matrix forward then apply d={d} n={n} m={m} {first} {transpose}", flush=True)
     p = synthetic.householder_problem(d, n, m, seed=107000)
     V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
@@ -215,7 +220,7 @@ def test_saved_applies_form_nothing_again(transpose):
     """Prepared once, a saved apply is one product (and its operand), in either direction, and the two calls are exactly fasth_forward."""
     import torch
     from paper_2009_13977_amd import binding as B
-    d, n, m, k = 500, 520, 800, 20
+    d, n, m, k = 500, 520, 1028, 20
     print(f"matrix saved applies d={d} n={n} m={m} {transpose}", flush=True)
     p = synthetic.householder_problem(d, n, m, seed=108000)
     V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
@@ -244,7 +249,7 @@ def test_saved_applies_form_nothing_again(transpose):
 def test_captured_and_replayed():
     import torch
     from paper_2009_13977_amd import binding as B
-    d, n, m, k = 450, 430, 800, 10
+    d, n, m, k = 450, 430, 1284, 10
     print(f"matrix graph d={d} n={n} m={m}", flush=True)
     probs = [synthetic.householder_problem(d, n, m, seed=105000 + r) for r in range(3)]
     V, X, G = (to_gpu(probs[0][a]) for a in ("V", "X", "G"))
@@ -285,7 +290,7 @@ def test_bad_columns_stay_alone():
     """An infinity or NaN in X, or one in G, spoils its own column of A or dX and no other."""
     import torch
     from paper_2009_13977_amd import binding as B
-    d, n, m, k = 450, 430, 800, 10
+    d, n, m, k = 450, 430, 1284, 10
     print(f"matrix bad columns d={d} n={n} m={m}", flush=True)
     p = synthetic.householder_problem(d, n, m, seed=106000)
     V, X, G = (to_gpu(p[a]) for a in ("V", "X", "G"))
