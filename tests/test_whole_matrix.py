@@ -154,6 +154,50 @@ def test_rectangular_layers(rows, cols, n_u, n_v):
         assert_close(g, r, name, rows=name in ("dUv", "dVv"))
 
 
+def _fp64_product(V):
+    """H in fp64 with a graph back to V: blocks of 500 reflections, a triangular solve each."""
+    import torch
+    eye = lambda n: torch.eye(n, dtype=V.dtype, device=V.device)
+    H = eye(V.shape[1])
+    for W in torch.split(V / V.norm(dim=1, keepdim=True), 500):
+        Y = torch.linalg.solve_triangular(torch.triu(W @ W.T, 1) + 0.5 * eye(len(W)), W, upper=True)
+        H = H - (H @ W.T.contiguous()) @ Y
+    return H
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,n,m,transpose", [(2304, 2200, 1364, False), (4096, 4000, 1336, True)])
+def test_large_products(d, n, m, transpose):
+    """More groups than a launch takes problems (nine and sixteen), the largest tiles for H and its transpose."""
+    import torch
+    print(f"matrix large d={d} n={n} m={m} transpose={transpose}", flush=True)
+    gen = np.random.default_rng(d)
+    V, X, G = (gen.standard_normal(s).astype(np.float32) for s in ((n, d), (d, m), (d, m)))
+    got = gpu_fasth(V, X, G, 1, transpose)
+    V64, X64 = (to_gpu(a).double().requires_grad_(True) for a in (V, X))
+    H = _fp64_product(V64)
+    A = (H.T if transpose else H) @ X64
+    A.backward(to_gpu(G).double())
+    for name, g, r in zip(("A", "dV", "dX"), got, (A.detach(), V64.grad, X64.grad)):
+        assert_close(g, r.cpu().numpy(), name, rows=name == "dV")
+        assert np.linalg.norm(g - r.cpu().numpy()) <= 1e-6 * float(r.norm()), name
+
+
+@pytest.mark.gpu
+def test_large_layer():
+    """Two products of five groups each: more than a launch takes problems."""
+    import torch
+    d, n, m = 1100, 1090, 1370
+    print(f"matrix large layer d={d} n={n} m={m}", flush=True)
+    p = synthetic.svd_layer_problem(d, n, m, seed=113000)
+    got = gpu_svd_layer(p["Uv"], p["sigma"], p["Vv"], p["X"], p["G"], 10)
+    U, s, V, X = (to_gpu(p[a]).double().requires_grad_(True) for a in ("Uv", "sigma", "Vv", "X"))
+    Y = _fp64_product(U) @ (s[:, None] * (_fp64_product(V).T @ X))
+    Y.backward(to_gpu(p["G"]).double())
+    for name, g, r in zip(("Y", "dUv", "dsigma", "dVv", "dX"), got, (Y.detach(), U.grad, s.grad, V.grad, X.grad)):
+        assert_close(g, r.cpu().numpy(), name, rows=name in ("dUv", "dVv"))
+
+
 @pytest.mark.gpu
 def test_prepared_products():
     """Prepared once: unsaved applies on two streams that share the workspace and leave it alone; saved applies in either order,
