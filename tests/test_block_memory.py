@@ -23,7 +23,7 @@ def test_large_blocks_bound_the_workspace(d, n, m):
 
 def test_small_workspaces_are_not_split():
     """Within 1 GiB the library's own blocks serve every block size alike."""
-    assert B.fasth_workspace_bytes(1024, 1024, 4096, 128) == B.fasth_workspace_bytes(1024, 1024, 4096, 32)
+    assert B.fasth_workspace_bytes(1024, 384, 4096, 128) == B.fasth_workspace_bytes(1024, 384, 4096, 32) > 6 * 2 * 4096 * 1024 * 4
 
 
 @pytest.mark.gpu
