@@ -139,7 +139,8 @@ int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float*
                 void* workspace, size_t workspace_bytes, int save_for_backward, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, serving loops that
- * forbid it, harnesses without an allocator): A = H X (or H^T X) exactly as fasth_forward computes it,
+ * forbid it, harnesses without an allocator): A = H X (or H^T X) as fasth_forward computes it from block factors (also
+ * where fasth_forward forms H as one matrix: there the two agree up to rounding),
  * with the block factors in a fixed array of FASTH_STATIC_SCRATCH_BYTES that is part of the library's
  * GPU code (one copy per GPU, held until the process ends) instead of a caller's workspace. Nothing is
  * saved for a backward pass. The call allocates and frees nothing; its first use on a device looks up

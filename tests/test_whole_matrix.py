@@ -290,6 +290,24 @@ def test_saved_applies_form_nothing_again(transpose):
 
 
 @pytest.mark.gpu
+def test_static_forward_agrees():
+    """fasth_forward_static applies the blocks one after the other also where fasth_forward forms H: the same up to rounding."""
+    import torch
+    from paper_2009_13977_amd import binding as B
+    d, n, m, k = 500, 520, 1028, 20
+    print(f"matrix and static d={d} n={n} m={m}", flush=True)
+    p = synthetic.householder_problem(d, n, m, seed=114000)
+    V, X = to_gpu(p["V"]), to_gpu(p["X"])
+    for transpose in (False, True):
+        A, Z = torch.empty_like(X), torch.empty_like(X)
+        ws = B.new_workspace(B.fasth_workspace_bytes(d, n, m, k))
+        B.fasth_forward(V, X, A, ws, k, transpose)
+        B.fasth_forward_static(V, X, Z, k, transpose)
+        torch.cuda.synchronize()
+        assert (A - Z).norm() <= 2e-6 * A.norm()
+
+
+@pytest.mark.gpu
 def test_captured_and_replayed():
     import torch
     from paper_2009_13977_amd import binding as B
