@@ -56,7 +56,7 @@ enum {
  * padding the last one. A larger k still bounds the memory: where blocks of 32 or
  * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. Wide
  * mini-batches with n not below d / 2 (for n = d: from 1024 columns on where the vectors have 448 to
- * 512 elements, 1281 up to 640, 2500 up to 768, 2250 up to 2048, 1280 up to 4096; more columns for
+ * 512 elements, 1281 up to 640, 2048 up to 2048, 1280 up to 4096; more columns for
  * fewer reflections or a length that is no multiple of four; 0.6 of that in the layers of two
  * products) multiply by the whole H as one matrix, in any k's place. A call that forms H
  * (fasth_forward, fasth_prepare, the layers' apply calls) then takes some 10 to 100 us more than

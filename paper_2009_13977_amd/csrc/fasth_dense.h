@@ -666,8 +666,8 @@ static bool dense_fits(int d, int n, int m) {
 // mini-batch of some 1.2 d columns and falls on whoever forms H: fasth_forward and fasth_prepare, also where no gradients or few applies follow. The
 // lines lie where a gradient step gains at least as many us as a forward call by itself loses, and fasth_prepare with two applies is no slower (n / d of 0.5 to
 // 0.6: four to eight applies). They depend on the chain that would run: teams of workgroups serve up to 1280 columns (d <= 640, and 768), 1024 (d > 768) or
-// 2048 (d <= 512), and as parts of a tile some 2200 from d = 1025 on; beyond d = 2048 no kernel shares columns. Lengths that are no multiple of four load an operand one column at
-// a time (launch_gemm). us, chain of blocks and whole matrix; gradient step; forward alone; prepare and two applies:
+// 2048 (d <= 512), and as parts of a tile some 2200 from d = 1025 on, where a forward call alone loses more up to there (d = 1088, 1536); beyond d = 2048 no kernel shares columns.
+// Lengths that are no multiple of four load an operand one column at a time (launch_gemm). us, chain of blocks and whole matrix; gradient step; forward alone; prepare and two applies:
 //   d = n =  512, m =   768: 117, 103;  47,  62;  84,  72     m = 1024: 128, 105;  56,  64;  87,  72
 //   n = 0.75 d,   m =  2048: 132, 115;  56,  65;  80,  78     m = 4096: 152, 146;  60,  78;  86, 100     m = 16384: 422, 268; 154, 125; 196, 188
 //   d = n =  640, m =  1280: 153, 151;  66,  86; 216, 101     m = 1500: 190, 156;  87,  87; 170, 103
@@ -680,7 +680,7 @@ static bool dense_fits(int d, int n, int m) {
 //   n = 0.75 d,   m =  2048: 257, 253; 108, 130; 212, 164     m = 3000: 351, 287; 137, 147; 222, 196
 //   n = 0.5 d,    m =  4096: 304, 266; 118, 126; 177, 182     m = 8192: 576, 422; 207, 182; 256, 291
 //   n = 0.3 d,    m = 16384: 776, 730; 281, 293; 355, 508     m = 65535: 3060, 2899; 1204, 1055; 1508, 1876
-//   d = n = 1408, m =  1900: 673, 564; 243, 326; 693, 393     m = 2250: 744, 585; 259, 336; 701, 404
+//   d = n = 1088, m =  2250: 486, 451; 188, 257; 544, 315;    d = 1408: 744, 585; 259, 336; 701, 404;   d = 1536, m = 2048: 800, 713; 283, 390; 759, 454
 //   d = n = 2048, m =  1500: 1086, 997; 429, 561; 1224, 641   m = 2048: 1266, 1027; 529, 565; 1233, 658
 //   n = 0.5 d,    m =  4096: 1094, 956; 427, 434; 688, 629    m = 8192: 2083, 1493; 773, 632; 1307, 998
 //   d = n = 2052, m =  1280: 2654, 1408; 1219, 813; 2284, 895;  d = 2560, n = 1280: 1702, 966; 784, 551; 1495, 643;  d = 4096, n = 2048: 3616, 2842; 1631, 1626; 3096, 1896
@@ -691,8 +691,8 @@ static bool dense_pays(int d, int n, long long columns) {
   const auto at_least = [&](int per_n, int per_d, long long full) { return columns * ((long long)per_n * n - (long long)per_d * d) >= full * d; };
   if (d <= 512) return (columns >= 1024 && 8 * n >= 7 * d) || at_least(5, 2, 16384);
   if (d <= 640) return at_least(5, 2, 3 * 1281);
-  if (d <= 768) return at_least(4, 1, 3 * 2500);
-  return d <= 2048 ? at_least(1, 0, 2250) : columns >= 1280;
+  if (d <= 768) return at_least(4, 1, 3 * 2048);
+  return d <= 2048 ? at_least(1, 0, 2048) : at_least(1, -1, 2 * 1280);
 }
 static bool dense_serves(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, m); }
 // A product of a layer of two: its launches serve both, so the lines lie at 0.6 of the columns. us per layer, W X, gradient step and forward alone:
