@@ -56,7 +56,7 @@ def f_exec(d, n, m, k):
 
 def kernel_flops(slot, launched, d, n, m, k):
     """Algorithmic FLOP of one launch of the kernel in a profiler slot."""
-    if (launched or "").startswith(("gemm_kernel", "pack_kernel", "block_", "skew_kernel")):  # H as one matrix
+    if (launched or "").startswith(("gemm_kernel", "pack_kernel", "gram_kernel", "block_", "skew_kernel")):  # H as one matrix
         return 2.0 * d * d * m if slot == "chain_kernel" else None  # H X; the other slots' launches are of many sizes
     if slot == "chain_kernel":
         return 4.0 * d * n * m                       # B = V_i a and a -= V_i^T C over all blocks

@@ -113,8 +113,8 @@ int fasth_set_wait_limit(int polls);
  * mini-batch, partial sums of dV; where d is no multiple of 4 or n no multiple
  * of the library's blocks, a padded copy of V; for more than 1024 columns of up to
  * 2048 elements a copy of V as operands of the matrix cores, 12 bytes per
- * element; where H is one matrix, H and some more matrices of its size, and X and
- * dL/dX as operands, 6 bytes per element, in the place of all saved inputs). Returns 0 if the shape is invalid or unsupported. */
+ * element; where H is one matrix, H and some more matrices of its size, and two of the
+ * mini-batch's size as operands, 6 bytes per element, in the place of all saved inputs). Returns 0 if the shape is invalid or unsupported. */
 size_t fasth_workspace_bytes(const fasth_shape* shape);
 
 /* Algorithm 1. A = H X (or H^T X). Step 1 builds, for every block i, the

@@ -18,7 +18,7 @@
 //                        per workgroup or team on the matrix cores (quad, tile, team_tile, trio)
 //   trio_rows_kernel     the rows of V as operands of chain_trio_kernel, part of Step 1
 //   dv_*                 Algorithm 2 Step 2 as dense products per block (MFMA)
-//   gemm_kernel, pack_kernel, block_factor_kernel, block_inverse_kernel, skew_kernel
+//   gemm_kernel, pack_kernel, gram_kernel, block_factor_kernel, block_inverse_kernel, skew_kernel
 //                        wide mini-batches: H as one matrix, and Algorithms 1 and 2 as products with it (MFMA)
 //   seq_*                the one-reflection-at-a-time comparison
 //   dsigma_kernel        the diagonal step of the SVD layer

@@ -239,8 +239,9 @@ __device__ __forceinline__ void gemm_range(const GemmTerm& g, int r0, int split,
 // the compute unit's cache. BF: B is fp32 [k][cols], split in registers: 1, a load per column; 2, where its rows are made of groups of four, a
 // load per lane takes the columns of all column tiles, so that lane i's are CT i, CT i + 1, ... of the wave's.
 // 1024 x 4096 x 1024: 54 us packed; BF 58 .. 60 us (62 with loads of one column each), 143 TF/s of fp32 products, which are six bf16 products each
-// (the matrix cores' limit: 335, 25 us). Bound by what the waves issue: without the split 47 us, without the loads 45, with every load from the
-// same addresses 57, so neither memory nor the L2s; some 8 are launch, first fetch and the way out. 1024 x 1024 x 1024: 17 us; 1024 x 256 x 1024: 7.2;
+// (the matrix cores' limit: 335, 25 us). Bound by what the waves issue, vector and matrix instructions after one another: of 108 thousand cycles in which a
+// compute unit is busy a SIMD spends 49 on matrix instructions and 50 on others (packed: 83, 49 and 17; counters). Without the split 47 us, without the loads 45, with
+// every load from the same addresses 57, so neither memory nor the L2s; some 8 are launch, first fetch and the way out. 1024 x 1024 x 1024: 17 us; 1024 x 256 x 1024: 7.2;
 // the smallest: 4.9, launch and code fetch. The same products with both operands staged in LDS took 57 us at 1024 x 4096 x 1024 (packed) and 67 us
 // (split on the way); a barrier per tile of k, for waves that share an operand to fetch it together: 63.
 template <int RT, int CT, int WM, int WN, int KS, int BF>
