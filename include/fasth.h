@@ -55,11 +55,10 @@ enum {
  * own, 32 or 64 rows (8, 16 or 24 for few reflections in small blocks, k < 32),
  * padding the last one. A larger k still bounds the memory: where blocks of 32 or
  * 64 would save more than 1 GiB more inputs than the caller's, larger ones serve. Wide
- * mini-batches with n not below d / 2 (for n = d: from 1024 columns on where the vectors have 448 to
- * 512 elements, 1281 up to 640, 2048 up to 2048, 1280 up to 4096; more columns for
- * fewer reflections or a length that is no multiple of four; 0.6 of that in the layers of two
- * products) multiply by the whole H as one matrix, in any k's place. A call that forms H
- * (fasth_forward, fasth_prepare, the layers' apply calls) then takes some 10 to 100 us more than
+ * mini-batches with n not below d / 2 (for n = d: from 7168 columns on where the vectors have 448 to
+ * 512 elements, 2049 up to 768, 4097 falling to 2560 up to 1024, 2700 up to 2048, 1280 up to 4096; more columns for
+ * fewer reflections or a length that is no multiple of four; fewer in some layers of two
+ * products) multiply by the whole H as one matrix, in any k's place. Forming H takes some 10 to 100 us more than
  * block factors do, and every product with it less. dV comes from a d x d matrix of sums of products
  * of X and dL/dA: the products of their entries need to lie within some 1e-33 to 1e38. */
 typedef struct fasth_shape {
@@ -132,7 +131,7 @@ int fasth_forward(const fasth_shape* shape, const float* V, const float* X, floa
  * the block inputs, so fasth_prepare + fasth_apply(save) is exactly fasth_forward; with 0 nothing
  * but A is written (inference). Where H is one matrix (see fasth_shape) fasth_prepare forms it, and an
  * apply is one product, saved or not, in either direction: the former takes longer and the latter less than with block factors, which
- * pays from two applies on (four to eight where n is little more than d / 2). */
+ * pays from two applies on. */
 int fasth_prepare(const fasth_shape* shape, const float* V, void* workspace, size_t workspace_bytes,
                   void* stream);
 int fasth_apply(const fasth_shape* shape, const float* V, const float* X, float* A,

@@ -663,42 +663,60 @@ static bool dense_fits(int d, int n, int m) {
   return d <= 4096 && 2 * n <= 3 * d && (size_t)d * m * sizeof(float) < 0x80000000u;
 }
 // Whether a product runs on the whole matrix. Its part of a gradient step that depends on m is 6 d^2 m operations instead of 12 d n m, the rest is as much as a
-// mini-batch of some 1.2 d columns and falls on whoever forms H: fasth_forward and fasth_prepare, also where no gradients or few applies follow. The
-// lines lie where a gradient step gains at least as many us as a forward call by itself loses, and fasth_prepare with two applies is no slower (n / d of 0.5 to
-// 0.6: four to eight applies). They depend on the chain that would run: teams of workgroups serve up to 1280 columns (d <= 640, and 768), 1024 (d > 768) or
-// 2048 (d <= 512), and as parts of a tile some 2200 from d = 1025 on, where a forward call alone loses more up to there (d = 1088, 1536); beyond d = 2048 no kernel shares columns.
-// Lengths that are no multiple of four load an operand one column at a time (launch_gemm). us, chain of blocks and whole matrix; gradient step; forward alone; prepare and two applies:
-//   d = n =  512, m =   768: 117, 103;  47,  62;  84,  72     m = 1024: 128, 105;  56,  64;  87,  72
-//   n = 0.75 d,   m =  2048: 132, 115;  56,  65;  80,  78     m = 4096: 152, 146;  60,  78;  86, 100     m = 16384: 422, 268; 154, 125; 196, 188
-//   d = n =  640, m =  1280: 153, 151;  66,  86; 216, 101     m = 1500: 190, 156;  87,  87; 170, 103
-//   n = 0.75 d,   m =  2048: 174, 165;  76,  84; 140, 108     m = 3000: 220, 176;  95,  86; 146, 111
-//   n = 0.5 d,    m =  4096: 183, 197;  75,  96; 112, 128     m = 8192: 318, 283; 113, 129; 175, 195
-//   d = n =  768, m =  2048: 238, 220; 101, 114; 204, 141     m = 3000: 316, 263; 129, 129; 210, 171
-//   n = 0.75 d,   m =  3000: 255, 244; 104, 125; 170, 167     m = 4096: 291, 247; 117, 128; 179, 167
-//   d = n =  833, m =  1900: 267, 273; 115, 160; 237, 189     m = 3000: 384, 314; 149, 178; 242, 217
-//   d = n = 1024, m =  1500: 290, 266; 125, 151; 277, 183     m = 2048: 329, 285; 134, 156; 274, 189     m = 3000: 467, 319; 174, 172; 283, 220
-//   n = 0.75 d,   m =  2048: 257, 253; 108, 130; 212, 164     m = 3000: 351, 287; 137, 147; 222, 196
-//   n = 0.5 d,    m =  4096: 304, 266; 118, 126; 177, 182     m = 8192: 576, 422; 207, 182; 256, 291
-//   n = 0.3 d,    m = 16384: 776, 730; 281, 293; 355, 508     m = 65535: 3060, 2899; 1204, 1055; 1508, 1876
-//   d = n = 1088, m =  2250: 486, 451; 188, 257; 544, 315;    d = 1408: 744, 585; 259, 336; 701, 404;   d = 1536, m = 2048: 800, 713; 283, 390; 759, 454
-//   d = n = 2048, m =  1500: 1086, 997; 429, 561; 1224, 641   m = 2048: 1266, 1027; 529, 565; 1233, 658
-//   n = 0.5 d,    m =  4096: 1094, 956; 427, 434; 688, 629    m = 8192: 2083, 1493; 773, 632; 1307, 998
-//   d = n = 2052, m =  1280: 2654, 1408; 1219, 813; 2284, 895;  d = 2560, n = 1280: 1702, 966; 784, 551; 1495, 643;  d = 4096, n = 2048: 3616, 2842; 1631, 1626; 3096, 1896
-static bool dense_pays(int d, int n, long long columns) {
+// mini-batch of some 1.2 d columns and falls on whoever forms H: fasth_forward and fasth_prepare, also where no gradients or few applies follow. So the lines lie
+// where a gradient step is faster and a forward call alone, or fasth_prepare with two unsaved applies, is not slower (by more than the 5 % that runs on different machines
+// differ); fasth_prepare with a single unsaved apply loses up to 1.3 times below some 8000 columns. Beside the lines the chain's times jump: its workgroups take another round
+// beyond 2048 and 4096 columns (d <= 1024) or some 2600 and 4096 (d > 1024), and beyond d = 2048 no kernel shares columns. Lengths that are no multiple of four load an operand
+// one column at a time (launch_gemm). us, chain of blocks and whole matrix; gradient step; forward alone; prepare and one unsaved apply:
+//   d = n =  512, m =  1000: 128, 107;  56,  64;  53,  63     m =  5960: 232, 175;  88,  89;  74,  86      m =  7450: 283, 174;  98,  88;  81,  84
+//   d = 448, n = 336, m =  7947: 218, 180;  79,  85;  67,  81   m =  9934: 340, 238; 124, 110; 102, 105
+//   d = 512, n = 256, m = 23841: 484, 368; 157, 152; 126, 133   m = 29802: 616, 462; 212, 186; 156, 162
+//   d = n =  640, m =  1953: 197, 183;  87,  99;  98,  96     m =  2441: 248, 186; 110, 100; 100,  97
+//   n = 0.625 d,  m =  4882: 315, 206; 129,  96; 111,  94     m =  7629: 408, 288; 141, 129; 115, 126
+//   n = 0.5 d,    m =  7812: 321, 280; 112, 127;  97, 123     m =  9765: 502, 299; 199, 132; 169, 125
+//   d = n =  768, m =  2000: 233, 218; 100, 114; 112, 111     m =  2500: 295, 225; 128, 115; 115, 113
+//   n = 0.75 d,   m =  3333: 259, 249; 106, 126;  96, 124     m =  4166: 380, 252; 155, 125; 129, 122
+//   d = n =  833, m =  3906: 435, 323; 156, 176; 137, 172     m =  4882: 623, 407; 221, 214; 168, 211      m =  6103: 712, 421; 259, 216; 170, 212
+//   d = n =  896, m =  2500: 356, 281; 147, 154; 132, 151     m =  3906: 460, 301; 166, 157; 143, 153
+//   n = 0.75 d,   m =  3333: 329, 276; 127, 139; 113, 136     m =  4166: 500, 280; 190, 137; 148, 134
+//   n = 0.5 d,    m =  6400: 402, 340; 140, 154; 113, 149     m =  8000: 482, 362; 170, 158; 122, 151      m = 10000: 736, 482; 292, 206; 215, 196
+//   d = n = 1024, m =  1024: 231, 228; 100, 135;  90, 133     m =  2000: 328, 274; 136, 154; 149, 152      m =  2500: 427, 308; 168, 169; 151, 166
+//   n = 0.75 d,   m =  3333: 385, 292; 141, 146; 126, 144     m =  4166: 567, 392; 211, 193; 158, 188
+//   n = 0.5 d,    m =  6400: 490, 373; 166, 169; 123, 163     m = 10000: 880, 549; 343, 232; 240, 220
+//   d = n = 1088, m =  2500: 531, 445; 199, 251; 280, 248     m =  3125: 782, 457; 312, 252; 284, 248
+//   d = 1280, n = 960, m = 3333: 753, 571; 295, 296; 256, 291   m = 4166: 1245, 593; 532, 297; 476, 291
+//   d = n = 1536, m =  2500: 906, 717; 332, 398; 402, 389     m =  3125: 1267, 852; 505, 460; 397, 449
+//   d = n = 2048, m =  2000: 1242, 1031; 494, 562; 641, 549     m = 2500: 1654, 1189; 689, 629; 633, 621
+//   n = 0.625 d,  m =  4000: 1333, 1024; 514, 500; 453, 484     m = 5000: 2221, 1230; 908, 590; 776, 561
+//   d = n = 2052, m =  1280: 2663, 1374; 1215, 816; 1157, 810   d = 2560, n = 1280, m = 4096: 5325, 1566; 2462, 765; 2371, 750
+//   d = n = 3072, m =  1280: 4394, 2668; 1959, 1547; 1833, 1535;  d = n = 4096: 9588, 5199; 4464, 2897; 3063, 2882
+// Products of a layer of two: their launches serve both, so some lines lie at fewer columns. us per layer W X, gradient step and forward alone:
+//   d = n =  512, m =   500: 142, 139;  61,  77     m =   625: 196, 152;  87,  82;    d = 512, n = 384, m = 7761: 517, 353; 144, 146
+//   d = n =  640, m =  1907: 378, 312; 156, 155     m =  2384: 470, 311; 199, 152;    d = n =  768, m = 1953: 485, 398; 182, 201    m = 2441: 608, 414; 238, 204
+//   d = n = 1024, m =  1953: 730, 531; 258, 272     m =  2441: 914, 618; 348, 306;    n = 0.75 d,   m = 3255: 805, 573; 291, 268
+//   d = n = 1536, m =  1562: 1506, 1233; 620, 652   m =  1953: 1620, 1272; 655, 663;  d = 1280, n = 960, m = 2083: 976, 765; 380, 386; m = 2604: 1436, 782; 594, 382
+//   d = n = 2048, m =  1562: 2322, 1844; 1020, 977;   d = n = 2560, m = 512: 3055, 3112; 1367, 1866; m = 800: 5498, 3299; 2573, 1945;   d = n = 4096, m = 800: 14780, 9834; 7123, 5428
+// (symmetric forms, one set of factors, gain more: d = n = 768, m = 1953: 478, 388; 181, 155).
+static bool dense_pays(int d, int n, int m, bool layer) {
   if (d < 448 || 2 * n < d) return false;
   n = std::min(n, d);  // (more reflections cost both sides more)
-  if (d % 4) columns = columns * 4 / 5;
-  const auto at_least = [&](int per_n, int per_d, long long full) { return columns * ((long long)per_n * n - (long long)per_d * d) >= full * d; };
-  if (d <= 512) return (columns >= 1024 && 8 * n >= 7 * d) || at_least(5, 2, 16384);
-  if (d <= 640) return at_least(5, 2, 3 * 1281);
-  if (d <= 768) return at_least(4, 1, 3 * 2048);
-  return d <= 2048 ? at_least(1, 0, 2048) : at_least(1, -1, 2 * 1280);
+  const bool odd = d % 4 != 0;
+  // columns (per_n n / d - per_d) >= full
+  const auto at_least = [&](long long columns, int per_n, int per_d, long long full) { return columns * ((long long)per_n * n - (long long)per_d * d) >= full * d; };
+  if (d <= 1024) {
+    const long long columns = odd ? m * 5ll / 8 : m, least = d <= 512 ? 7168 : 4097;
+    if (columns >= least && at_least(columns, 8, 3, (d <= 512 ? 4 : 3) * least)) return true;
+    if (d > 512 && columns >= 2 * least) return true;
+    // nearly as many reflections as elements
+    if (odd || (d <= 512 && !layer)) return false;
+    if (d <= 512) return at_least(m, 16, 15, 640);
+    return at_least(m, 8, 7, d <= 768 || layer ? 2049 : 2560ll * 1024 * 1024 / (d * d));
+  }
+  if (d <= 2048) return at_least(layer ? (odd ? m : m * 3ll / 2) : odd ? m * 4ll / 5 : m, 1, 0, 2700);
+  const long long columns = layer ? m * 3ll / 2 : m;
+  return at_least(odd ? columns * 4 / 5 : columns, 1, -1, 2560);
 }
-static bool dense_serves(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, m); }
-// A product of a layer of two: its launches serve both, so the lines lie at 0.6 of the columns. us per layer, W X, gradient step and forward alone:
-// d = n = 512, m = 512: 146, 142; 69, 78; m = 640: 194, 154; 88, 82. d = n = 640, m = 768: 253, 228; 115, 122. d = n = 768, m = 1280: 350, 326; 133, 172; m = 1500: 441, 380;
-// 180, 197. d = n = 1024, m = 1024: 486, 437; 190, 238; m = 1280: 596, 502; 239, 262; m = 1500: 636, 520; 238, 267; n = 0.75 d, m = 1800: 537, 465; 196, 231.
-// d = n = 2048, m = 1100: 2072, 1822; 927, 998. d = n = 4096, m = 768: 12247, 9692; 5872, 5537. Symmetric forms, one set of factors: d = n = 1024, m = 1280: 581, 436; 233, 193.
-static bool dense_serves_layer(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, 5ll * m / 3); }
+static bool dense_serves(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, m, false); }
+static bool dense_serves_layer(int d, int n, int m) { return dense_fits(d, n, m) && dense_pays(d, n, m, true); }
 
 }  // namespace fasth
